@@ -63,10 +63,9 @@ int vio_mlp_gradient(vio_mlp* m, const float* d_x, const float* d_targets, int32
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * results as vio_mlp_gradient (bit for bit), with the training scratch (the
- * transposed bfloat16 operands, the output and loss gradients, the loss) in a
- * device array the library holds, one per GPU, for the life of the process
- * (VIO_MLP_NOALLOC_MAX_ROWS rows, about 4.4 MB), instead of the handle's
- * buffers; k may exceed the handle's max_batch up to that maximum. Allocates
+ * workgroups' partial gradients) in a device array the library holds, one per
+ * GPU, for the life of the process (about 5.4 MB), instead of the handle's
+ * buffer; k may exceed the handle's max_batch up to that maximum. Allocates
  * nothing (no hipMalloc, hipFree or allocating library call); the first call
  * on a device looks the array's address up. Every call on a GPU shares that
  * GPU's array: calls that overlap on one GPU (on different streams or

@@ -22,13 +22,10 @@ constexpr int OFF_W1 = 0, OFF_B1 = MH * MI, OFF_W2 = OFF_B1 + MH, OFF_B2 = OFF_W
               OFF_B3 = OFF_W3 + MO * MH;
 static_assert(OFF_B3 + MO == NP, "parameter layout");
 
-// float -> bfloat16 bits, round to nearest even (NaN stays NaN)
-__device__ __forceinline__ uint16_t bf16_bits(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7F800000u) == 0x7F800000u) return (uint16_t)((u >> 16) | ((u & 0xFFFFu) ? 0x40u : 0u));
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// float -> bfloat16 bits, round to nearest even (NaN stays NaN): one
+// v_cvt_pk_bf16_f32, without the special-value branch that kept the loads and
+// results around it apart
+__device__ __forceinline__ uint16_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
 __device__ __forceinline__ bf16x8 load8(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
@@ -40,6 +37,25 @@ __device__ __forceinline__ bf16x8 pack8(const uint16_t v[8]) {
   u.y = v[2] | ((uint32_t)v[3] << 16);
   u.z = v[4] | ((uint32_t)v[5] << 16);
   u.w = v[6] | ((uint32_t)v[7] << 16);
+  return __builtin_bit_cast(bf16x8, u);
+}
+
+// Eight consecutive floats at a 4-byte aligned address (two 16-byte loads), and
+// as bf16, zeros instead where !keep (a mask, so that no load waits behind a
+// branch).
+struct __attribute__((packed, aligned(4))) F32x8 {
+  float v[8];
+};
+__device__ __forceinline__ bf16x8 pack_f32(const float v[8], bool keep) {
+  uint16_t h[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) h[e] = bf16_bits(v[e]);
+  uint4 u = __builtin_bit_cast(uint4, pack8(h));
+  const uint32_t m = keep ? 0xFFFFFFFFu : 0u;
+  u.x &= m;
+  u.y &= m;
+  u.z &= m;
+  u.w &= m;
   return __builtin_bit_cast(bf16x8, u);
 }
 

@@ -6,121 +6,35 @@
 // segment of 8 bf16), B[8(l/16) .. +7][l%16] (a column segment) and returns
 // D[4(l/16) + q][l%16], q = 0..3.
 //
-// Forward: one wave per 16 rows. Layer 1 is one MFMA per 16 hidden units
+// Inference: one wave per 16 rows. Layer 1 is one MFMA per 16 hidden units
 // (K = 32 is one step); the ReLU'd bf16 activations go through the wave's LDS
-// to become the next layer's A operand. Backward: a data pass (dH2 = dY W3,
-// dH1 = dH2 W2, masked by the ReLUs) writes the bf16 operands transposed, and
-// the weight gradients are MFMA tiles reduced over the batch
-// (dW = dH^T H_prev); bias gradients are the same product against a ones
-// operand. Every sum has a fixed order: no atomics, deterministic results.
+// to become the next layer's A operand.
+//
+// Training: one kernel (k_mlp_grad) takes 32 rows at a time through the
+// forward pass, the loss, the data gradients (dH2 = dY W3, dH1 = dH2 W2,
+// masked by the ReLUs) and the weight gradients (dW = dH^T H_prev, MFMA with
+// the rows as the K dimension; bias gradients against a ones operand), and a
+// second one adds the workgroups' partial gradients and, in a training step,
+// runs Adam. Every sum has a fixed order: no atomics, deterministic results.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
-#include <vector>
 
 #include "fe_common.h"
 #include "mfma_ops.h"
 #include "vio_mlp.h"
+#include "wave_ops.h"
 
 namespace vio {
 
-constexpr int kMlpWaves = 4;
-
 __device__ __forceinline__ bool relu_active(uint16_t h) { return h != 0 && !(h & 0x8000u); }
 
-// Training scratch, transposed bf16 operands with leading dimension ldt.
-struct MlpScratch {
-  int ldt;
-  uint16_t *Xt, *H1t, *H2t, *dYt, *dH2t, *dH1t;  // [32|128|128|3|128|128][ldt]
-  float* dY;                                     // [ldt][3]
-  float* loss;                                   // [1]
-};
-
 // ---------------------------------------------------------------------------
-// forward
-// ---------------------------------------------------------------------------
-template <bool kTrain>
-__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_fwd(MlpDev M, const float* __restrict__ X, int K, int Kpad,
-                                                            float* __restrict__ Y, MlpScratch S) {
-  __shared__ __align__(16) uint16_t sH[kMlpWaves][2][16][MH];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i0 = ((int)blockIdx.x * kMlpWaves + wv) * 16;
-  if (i0 >= Kpad) return;
-  const int r = lane & 15, g = lane >> 4;
-  uint16_t (*h1)[MH] = sH[wv][0];
-  uint16_t (*h2)[MH] = sH[wv][1];
-  // A operand of layer 1: row i0 + r, features 8g .. 8g+7
-  uint16_t xv[8];
-  {
-    const int i = i0 + r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) xv[e] = i < K ? bf16_bits(X[(size_t)i * MI + 8 * g + e]) : (uint16_t)0;
-    if (kTrain) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) S.Xt[(size_t)(8 * g + e) * S.ldt + i] = xv[e];
-    }
-  }
-  const bf16x8 a = pack8(xv);
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  // layer 1: 8 tiles of 16 hidden units
-#pragma unroll
-  for (int jt = 0; jt < MH / 16; ++jt) {
-    const int j = 16 * jt + r;
-    const f32x4 acc = mfma(a, load8(M.W1b + (size_t)j * MI + 8 * g), zero);
-    const float b = M.P[OFF_B1 + j];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      h1[row][j] = (i0 + row) < K ? bf16_bits(fmaxf(acc[q] + b, 0.f)) : (uint16_t)0;
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-  // layer 2: K = 128 in four MFMA steps
-#pragma unroll
-  for (int jt = 0; jt < MH / 16; ++jt) {
-    const int j = 16 * jt + r;
-    f32x4 acc = zero;
-#pragma unroll
-    for (int kc = 0; kc < MH / 32; ++kc)
-      acc = mfma(load8(&h1[r][32 * kc + 8 * g]), load8(M.W2b + (size_t)j * MH + 32 * kc + 8 * g), acc);
-    const float b = M.P[OFF_B2 + j];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      h2[row][j] = (i0 + row) < K ? bf16_bits(fmaxf(acc[q] + b, 0.f)) : (uint16_t)0;
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-  // layer 3: 3 outputs padded to a 16-column tile
-  f32x4 acc = zero;
-  const uint16_t z8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int kc = 0; kc < MH / 32; ++kc) {
-    const bf16x8 b = r < MO ? load8(M.W3b + (size_t)r * MH + 32 * kc + 8 * g) : pack8(z8);
-    acc = mfma(load8(&h2[r][32 * kc + 8 * g]), b, acc);
-  }
-  if (r < MO) {
-    const float b = M.P[OFF_B3 + r];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = i0 + 4 * g + q;
-      if (i < K) Y[(size_t)i * MO + r] = acc[q] + b;
-    }
-  }
-  if (kTrain) {
-    for (int idx = lane; idx < 16 * MH; idx += 64) {
-      const int row = idx & 15, j = idx >> 4;
-      S.H1t[(size_t)j * S.ldt + i0 + row] = h1[row][j];
-      S.H2t[(size_t)j * S.ldt + i0 + row] = h2[row][j];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// inference forward: the same MFMA sequence as k_mlp_fwd (so the same
-// results). The bf16 weights and the biases (42 KB, L2-resident) are read
+// inference forward: the same MFMA sequence as k_mlp_grad's forward pass (so
+// the same results). The bf16 weights and the biases (42 KB, L2-resident) are read
 // straight from global memory as MFMA operands, so a workgroup holds only its
 // waves' 4 KB activation tiles in LDS and fits beside the pyramid kernel's
 // workgroups when both run at once; layer 2's eight output tiles stay in
@@ -199,171 +113,272 @@ __global__ __launch_bounds__(64 * kInferWaves) void k_mlp_infer(MlpDev M, const 
 }
 
 // ---------------------------------------------------------------------------
-// loss: Huber (1 px) on (16 y0, 16 y1) - target plus BCE of y2 against
-// [|guess - target| <= 2 px]; mean over the batch. One workgroup.
+// training: loss and partial gradients
+//
+// A workgroup of eight waves takes chunks of 32 rows (two 16-row MFMA tiles);
+// wave w owns hidden units 16 w .. 16 w + 15 of both hidden layers, with its
+// slices of W1, W2, W2^T and W3 in registers for all its chunks. A chunk's
+// activations and gradients never leave the compute unit: a wave holds its own
+// units' as MFMA results, and passes them on through LDS, by rows to become the
+// next layer's A operand, and packed to become a B operand of the weight
+// gradients. Those are MFMAs whose K dimension is the chunk's 32 rows, and the
+// order of K is free as long as both operands share it: with row 4 g + e of
+// tile 0 at k = 8 g + e and of tile 1 at k = 8 g + 4 + e, what lane (r, g) must
+// hold of an operand is exactly what it holds of two MFMA results (row 4 g + q,
+// column r), so nothing is transposed. The wave accumulates its 16 x 128 rows of dW2, 16 x 32 of dW1,
+// 3 x 16 of dW3 and its biases' over its chunks and writes them once, to the
+// workgroup's partial gradient.
+//
+// Bound by latency: the weights' loads and a chunk's chain (four dependent
+// layers, five barriers, about 4.4 us with two waves per SIMD). Measured:
+// 1,024 rows 10.9 us and 50,000 rows 33.5 us for this kernel, where the forward
+// pass, loss, data gradient and weight gradient as four kernels with transposed
+// operands in memory took 59 and 748 us (the weight gradient's 105 waves walked
+// the whole batch each, the loss ran in one workgroup).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_mlp_loss(const float* __restrict__ Y, const float* __restrict__ T, int K,
-                                                   int Kpad, MlpScratch S) {
-  __shared__ float red[1024];
-  float part = 0.f;
+constexpr int kGradWaves = MH / 16;  // one 16-unit hidden tile per wave
+constexpr int kChunk = 32;           // rows per chunk: one MFMA K step of the weight gradients
+// A partial gradient: the parameters in their order, then the loss sum, padded
+// to whole 64-float lines.
+constexpr int kPartLoss = NP;
+constexpr int kPartStride = (NP + 1 + 63) / 64 * 64;
+
+// Workgroups (and partial gradients) of a batch of k rows: one chunk each up
+// to 64 (a batch of 1024 rows: 32 compute units, the least time), then up to four
+// chunks each, so that the partials' traffic stays below the chunks' work,
+// and at most 256, one per compute unit (their accumulators fill its registers).
+int grad_groups(int k) {
+  const int chunks = (k + kChunk - 1) / kChunk;
+  return std::min(chunks, std::max(64, std::min(256, chunks / 4)));
+}
+
+__device__ __forceinline__ bf16x8 pack_tiles(const uint16_t t0[4], const uint16_t t1[4]) {
+  const uint16_t v[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
+  return pack8(v);
+}
+
+__global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const float* __restrict__ X,
+                                                              const float* __restrict__ T, int K, int n_chunks,
+                                                              float* __restrict__ part) {
+  // rows padded by 8 entries: the 16 rows of an operand read start 4 banks apart
+  __shared__ __align__(16) uint16_t sA[kChunk][MH + 8];  // h1 by rows, then dH2
+  __shared__ __align__(16) uint16_t sH2[kChunk][MH + 8];
+  __shared__ uint4 sB[kGradWaves][64];  // h1 as B operands, by hidden tile
+  __shared__ uint4 sX[MI / 16][64];     // x as B operands, by 16 features
+  __shared__ uint4 sW3[MH / 32][64];
+  __shared__ float sY[kChunk][4];
+  __shared__ __align__(16) uint16_t sdY[4][kChunk];  // dY by output (bf16)
+  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int unit = 16 * wv + r;  // this lane's hidden unit, as a column of its wave's tiles
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const bf16x8 zb = __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+
+  // the wave's weights, in the order they are needed
+  const bf16x8 w1 = load8(M.W1b + (size_t)unit * MI + 8 * g);
+  const float b1 = M.P[OFF_B1 + unit], b2 = M.P[OFF_B2 + unit];
+  bf16x8 w2[MH / 32], w2t[MH / 32];
+#pragma unroll
+  for (int kc = 0; kc < MH / 32; ++kc) w2[kc] = load8(M.W2b + (size_t)unit * MH + 32 * kc + 8 * g);
+  // W3 as the output tile's B operand, in LDS (columns 3..15 are zero): waves 0
+  // and 1 compute the outputs of the two row tiles
+  if (wv < MH / 32) sW3[wv][lane] = r < MO ? *reinterpret_cast<const uint4*>(M.W3b + (size_t)r * MH + 32 * wv + 8 * g)
+                                          : make_uint4(0u, 0u, 0u, 0u);
+  const float b3 = M.P[OFF_B3 + min(r, MO - 1)];
+  bf16x8 w3c = zb;  // W3's entries of the lane's unit: B operand of dH2 = dY W3 (K = 3, padded)
+  if (g == 0) {
+    uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < MO; ++c) v[c] = M.W3b[(size_t)c * MH + unit];
+    w3c = pack8(v);
+  }
+#pragma unroll
+  for (int kc = 0; kc < MH / 32; ++kc) w2t[kc] = load8(M.W2tb + (size_t)unit * MH + 32 * kc + 8 * g);
+
+  f32x4 dW2[MH / 16], dW1[MI / 16], dW3 = zero, db1 = zero, db2 = zero, db3 = zero;
+#pragma unroll
+  for (int t = 0; t < MH / 16; ++t) dW2[t] = zero;
+#pragma unroll
+  for (int t = 0; t < MI / 16; ++t) dW1[t] = zero;
+  float loss = 0.f;
   const float inv = 1.f / (float)K;
-  for (int i = threadIdx.x; i < Kpad; i += 1024) {
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-    if (i < K) {
-      const float gx = 16.f * Y[i * MO], gy = 16.f * Y[i * MO + 1], z = Y[i * MO + 2];
-      const float ex = gx - T[2 * i], ey = gy - T[2 * i + 1];
+
+  // a chunk's inputs, loaded one chunk ahead (rows past the batch read its last
+  // row and count as zero): x by rows, by columns (waves 2 and 3: features
+  // 16 (wv - 2) + r of the rows this lane packs) and the targets (row 16 t + r of
+  // tile t: waves 0 and 4, 1 and 5)
+  F32x8 xr[2];
+  float xc[8], tx = 0.f, ty = 0.f;
+  const auto fetch = [&](int ch) {
+    const int i0 = ch * kChunk;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      xr[t] = *reinterpret_cast<const F32x8*>(X + (size_t)min(i0 + 16 * t + r, K - 1) * MI + 8 * g);
+    if ((wv & 2) == 0) {
+      const size_t i = (size_t)min(i0 + 16 * (wv & 1) + r, K - 1);
+      tx = T[2 * i];
+      ty = T[2 * i + 1];
+    } else if (wv < 2 + MI / 16) {  // waves 2 and 3
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        xc[e] = X[(size_t)min(i0 + 16 * (e >> 2) + 4 * g + (e & 3), K - 1) * MI + 16 * (wv - 2) + r];
+    }
+  };
+  fetch((int)blockIdx.x);
+  for (int ch = (int)blockIdx.x; ch < n_chunks; ch += (int)gridDim.x) {
+    const int i0 = ch * kChunk;
+    // ---- layer 1 ----
+    bf16x8 h1p, h2p;
+    uint16_t h1[2][4], h2[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 acc = mfma(pack_f32(xr[t].v, i0 + 16 * t + r < K), w1, zero);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 16 * t + 4 * g + q;
+        h1[t][q] = i0 + row < K ? bf16_bits(fmaxf(acc[q] + b1, 0.f)) : (uint16_t)0;
+        sA[row][unit] = h1[t][q];
+      }
+    }
+    h1p = pack_tiles(h1[0], h1[1]);
+    sB[wv][lane] = __builtin_bit_cast(uint4, h1p);
+    if (wv >= 2 && wv < 2 + MI / 16) {
+      uint16_t v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = i0 + 16 * (e >> 2) + 4 * g + (e & 3) < K ? bf16_bits(xc[e]) : (uint16_t)0;
+      sX[wv - 2][lane] = __builtin_bit_cast(uint4, pack8(v));
+    }
+    const float gtx = tx, gty = ty;
+    if (ch + (int)gridDim.x < n_chunks) fetch(ch + (int)gridDim.x);
+    __syncthreads();
+    // ---- layer 2 ----
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x4 acc = zero;
+#pragma unroll
+      for (int kc = 0; kc < MH / 32; ++kc) acc = mfma(load8(&sA[16 * t + r][32 * kc + 8 * g]), w2[kc], acc);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 16 * t + 4 * g + q;
+        h2[t][q] = i0 + row < K ? bf16_bits(fmaxf(acc[q] + b2, 0.f)) : (uint16_t)0;
+        sH2[row][unit] = h2[t][q];
+      }
+    }
+    h2p = pack_tiles(h2[0], h2[1]);
+    __syncthreads();
+    // ---- layer 3 and the loss: wave t < 2 takes row tile t, lane l < 16 its row l ----
+    if (wv < 2) {
+      f32x4 acc = zero;
+#pragma unroll
+      for (int kc = 0; kc < MH / 32; ++kc)
+        acc = mfma(load8(&sH2[16 * wv + r][32 * kc + 8 * g]), __builtin_bit_cast(bf16x8, sW3[kc][lane]), acc);
+      if (r < MO) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sY[16 * wv + 4 * g + q][r] = acc[q] + b3;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (lane < 16) {
+        // gradient of Huber (1 px) on (16 y0, 16 y1) - target plus BCE of y2
+        // against [|guess - target| <= 2 px], mean over the batch; the loss
+        // itself is left to waves 4 and 5, off this chain
+        const int row = 16 * wv + lane;
+        float d0 = 0.f, d1 = 0.f, d2 = 0.f;
+        if (i0 + row < K) {
+          const float ex = 16.f * sY[row][0] - gtx, ey = 16.f * sY[row][1] - gty, z = sY[row][2];
+          const float c = sqrtf(ex * ex + ey * ey) <= 2.f ? 1.f : 0.f;
+          d0 = 16.f * fmaxf(-1.f, fminf(1.f, ex)) * inv;
+          d1 = 16.f * fmaxf(-1.f, fminf(1.f, ey)) * inv;
+          d2 = (1.f / (1.f + expf(-z)) - c) * inv;
+        }
+        sdY[0][row] = bf16_bits(d0);
+        sdY[1][row] = bf16_bits(d1);
+        sdY[2][row] = bf16_bits(d2);
+      }
+    }
+    __syncthreads();
+    // ---- dH2 = (dY W3) * [h2 > 0] ----
+    uint16_t d2[2][4], d1[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      uint16_t av[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int c = 0; c < MO; ++c) av[c] = g == 0 ? sdY[c][16 * t + r] : (uint16_t)0;
+      const f32x4 acc = mfma(pack8(av), w3c, zero);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        d2[t][q] = relu_active(h2[t][q]) ? bf16_bits(acc[q]) : (uint16_t)0;
+        sA[16 * t + 4 * g + q][unit] = d2[t][q];
+      }
+    }
+    const bf16x8 d2p = pack_tiles(d2[0], d2[1]);
+    __syncthreads();
+    // ---- dH1 = (dH2 W2) * [h1 > 0] ----
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x4 acc = zero;
+#pragma unroll
+      for (int kc = 0; kc < MH / 32; ++kc) acc = mfma(load8(&sA[16 * t + r][32 * kc + 8 * g]), w2t[kc], acc);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d1[t][q] = relu_active(h1[t][q]) ? bf16_bits(acc[q]) : (uint16_t)0;
+    }
+    const bf16x8 d1p = pack_tiles(d1[0], d1[1]);
+    // ---- weight gradients over the chunk's rows ----
+#pragma unroll
+    for (int t = 0; t < MH / 16; ++t) dW2[t] = mfma(d2p, __builtin_bit_cast(bf16x8, sB[t][lane]), dW2[t]);
+#pragma unroll
+    for (int t = 0; t < MI / 16; ++t) dW1[t] = mfma(d1p, __builtin_bit_cast(bf16x8, sX[t][lane]), dW1[t]);
+    bf16x8 dyp = zb;  // A operand: row r < 3 is output r
+    if (r < MO) {
+      const uint2 lo = *reinterpret_cast<const uint2*>(&sdY[r][4 * g]);
+      const uint2 hi = *reinterpret_cast<const uint2*>(&sdY[r][16 + 4 * g]);
+      dyp = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    }
+    dW3 = mfma(dyp, h2p, dW3);
+    db1 = mfma(d1p, ones, db1);
+    db2 = mfma(d2p, ones, db2);
+    db3 = mfma(dyp, ones, db3);
+    if ((wv & 6) == 4 && lane < 16 && i0 + 16 * (wv - 4) + lane < K) {
+      const float* y = sY[16 * (wv - 4) + lane];
+      const float ex = 16.f * y[0] - gtx, ey = 16.f * y[1] - gty, z = y[2];
       const float hx = fabsf(ex) <= 1.f ? 0.5f * ex * ex : fabsf(ex) - 0.5f;
       const float hy = fabsf(ey) <= 1.f ? 0.5f * ey * ey : fabsf(ey) - 0.5f;
       const float c = sqrtf(ex * ex + ey * ey) <= 2.f ? 1.f : 0.f;
-      const float bce = (z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - c * z;
-      part += hx + hy + bce;
-      d0 = 16.f * fmaxf(-1.f, fminf(1.f, ex)) * inv;
-      d1 = 16.f * fmaxf(-1.f, fminf(1.f, ey)) * inv;
-      d2 = (1.f / (1.f + expf(-z)) - c) * inv;
+      loss += hx + hy + ((z > 0.f ? z : 0.f) + log1pf(expf(-fabsf(z))) - c * z);
     }
-    S.dY[i * MO] = d0;
-    S.dY[i * MO + 1] = d1;
-    S.dY[i * MO + 2] = d2;
-    S.dYt[(size_t)0 * S.ldt + i] = bf16_bits(d0);
-    S.dYt[(size_t)1 * S.ldt + i] = bf16_bits(d1);
-    S.dYt[(size_t)2 * S.ldt + i] = bf16_bits(d2);
+    __syncthreads();  // the next chunk overwrites sA, sB, sX
   }
-  red[threadIdx.x] = part;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *S.loss = red[0] * inv;
-}
 
-// ---------------------------------------------------------------------------
-// backward, data pass: dH2 = (dY W3) * [h2 > 0], dH1 = (dH2 W2) * [h1 > 0]
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_bwd_data(MlpDev M, int Kpad, MlpScratch S) {
-  __shared__ __align__(16) uint16_t sD[kMlpWaves][16][MH];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i0 = ((int)blockIdx.x * kMlpWaves + wv) * 16;
-  if (i0 >= Kpad) return;
-  const int r = lane & 15, g = lane >> 4;
-  uint16_t (*d2)[MH] = sD[wv];
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  uint16_t av[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int c = 8 * g + e;
-    av[e] = c < MO ? bf16_bits(S.dY[(size_t)(i0 + r) * MO + c]) : (uint16_t)0;
-  }
-  const bf16x8 a = pack8(av);
-#pragma unroll
-  for (int kt = 0; kt < MH / 16; ++kt) {
-    const int k = 16 * kt + r;
-    uint16_t bv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int c = 8 * g + e;
-      bv[e] = c < MO ? M.W3b[(size_t)c * MH + k] : (uint16_t)0;
-    }
-    const f32x4 acc = mfma(a, pack8(bv), zero);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      const uint16_t d = relu_active(S.H2t[(size_t)k * S.ldt + i0 + row]) ? bf16_bits(acc[q]) : (uint16_t)0;
-      d2[row][k] = d;
-      S.dH2t[(size_t)k * S.ldt + i0 + row] = d;
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int kt = 0; kt < MH / 16; ++kt) {
-    const int k = 16 * kt + r;
-    f32x4 acc = zero;
-#pragma unroll
-    for (int jc = 0; jc < MH / 32; ++jc)
-      acc = mfma(load8(&d2[r][32 * jc + 8 * g]), load8(M.W2tb + (size_t)k * MH + 32 * jc + 8 * g), acc);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      S.dH1t[(size_t)k * S.ldt + i0 + row] =
-          relu_active(S.H1t[(size_t)k * S.ldt + i0 + row]) ? bf16_bits(acc[q]) : (uint16_t)0;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// backward, weight gradients: one wave per 16x16 tile of dW (or of a bias,
-// against a ones operand), reduced over the padded batch in steps of 32.
-// ---------------------------------------------------------------------------
-struct GradTile {
-  int a_src, b_src;  // 0 Xt, 1 H1t, 2 H2t, 3 dYt, 4 dH2t, 5 dH1t, 6 ones
-  int m0, n0;        // tile origin in the gradient matrix
-  int rows, cols;    // valid extent of the matrix
-  int off;           // parameter offset; bias tiles write column 0 only
-  int bias;
-};
-
-__constant__ GradTile c_tiles[105];
-
-__device__ __forceinline__ const uint16_t* src_of(const MlpScratch& S, int s) {
-  switch (s) {
-    case 0: return S.Xt;
-    case 1: return S.H1t;
-    case 2: return S.H2t;
-    case 3: return S.dYt;
-    case 4: return S.dH2t;
-    default: return S.dH1t;
-  }
-}
-
-__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_wgrad(int n_tiles, int Kpad, MlpScratch S,
-                                                              float* __restrict__ G) {
-  const int lane = threadIdx.x & 63;
-  const int t = (int)blockIdx.x * kMlpWaves + (int)(threadIdx.x >> 6);
-  if (t >= n_tiles) return;
-  const GradTile T = c_tiles[t];
-  const int r = lane & 15, g = lane >> 4;
-  const uint16_t* A = src_of(S, T.a_src);
-  const uint16_t* B = T.b_src == 6 ? nullptr : src_of(S, T.b_src);
-  const bool arow = T.m0 + r < T.rows;
-  const bool bcol = T.b_src == 6 || T.n0 + r < T.cols;
-  const uint16_t z8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const uint16_t one8[8] = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = 0; i0 < Kpad; i0 += 32) {
-    const bf16x8 a = arow ? load8(A + (size_t)(T.m0 + r) * S.ldt + i0 + 8 * g) : pack8(z8);
-    const bf16x8 b = T.b_src == 6 ? pack8(one8) : (bcol ? load8(B + (size_t)(T.n0 + r) * S.ldt + i0 + 8 * g) : pack8(z8));
-    acc = mfma(a, b, acc);
-  }
+  // ---- the workgroup's partial gradient ----
+  float* P = part + (size_t)blockIdx.x * kPartStride;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int m = T.m0 + 4 * g + q, n = T.n0 + r;
-    if (m >= T.rows) continue;
-    if (T.bias) {
-      if (r == 0) G[T.off + m] = acc[q];
-    } else if (n < T.cols) {
-      G[T.off + (size_t)m * T.cols + n] = acc[q];
+    const int m = 16 * wv + 4 * g + q;  // the gradient row this lane holds
+#pragma unroll
+    for (int t = 0; t < MI / 16; ++t) P[OFF_W1 + m * MI + 16 * t + r] = dW1[t][q];
+#pragma unroll
+    for (int t = 0; t < MH / 16; ++t) P[OFF_W2 + m * MH + 16 * t + r] = dW2[t][q];
+    if (r == 0) {
+      P[OFF_B1 + m] = db1[q];
+      P[OFF_B2 + m] = db2[q];
+    }
+    if (4 * g + q < MO) {
+      P[OFF_W3 + (4 * g + q) * MH + unit] = dW3[q];
+      if (wv == 0 && r == 0) P[OFF_B3 + q] = db3[q];
     }
   }
+  if ((wv & 6) == 4) {
+    loss = wave_sum(lane < 16 ? loss : 0.f, lane);
+    if (lane == 0) sY[wv - 4][0] = loss;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) P[kPartLoss] = sY[0][0] + sY[1][0];
 }
 
-// ---------------------------------------------------------------------------
-// Adam on the master weights; refreshes the bf16 copies. t >= 1; step == 0
-// only refreshes the copies.
-// ---------------------------------------------------------------------------
-__global__ void k_mlp_adam(MlpDev M, const float* __restrict__ G, int step, float lr, float b1, float b2, float eps,
-                           float c1, float c2) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= NP) return;
-  float p = M.P[i];
-  if (step > 0) {
-    const float g = G[i];
-    const float m = b1 * M.m[i] + (1.f - b1) * g;
-    const float v = b2 * M.v[i] + (1.f - b2) * g * g;
-    M.m[i] = m;
-    M.v[i] = v;
-    p -= lr * (m / c1) / (sqrtf(v / c2) + eps);
-    M.P[i] = p;
-  }
+// Master parameter i and its bf16 copies.
+__device__ __forceinline__ void store_copies(const MlpDev& M, int i, float p) {
   const uint16_t b = bf16_bits(p);
   if (i < OFF_B1) {
     M.W1b[i] = b;
@@ -376,27 +391,58 @@ __global__ void k_mlp_adam(MlpDev M, const float* __restrict__ G, int step, floa
   }
 }
 
-std::vector<GradTile> grad_tiles() {
-  std::vector<GradTile> t;
-  // dW3 [3][128] = dY^T H2 and db3
-  for (int n0 = 0; n0 < MH; n0 += 16) t.push_back({3, 2, 0, n0, MO, MH, OFF_W3, 0});
-  t.push_back({3, 6, 0, 0, MO, 1, OFF_B3, 1});
-  // dW2 [128][128] = dH2^T H1 and db2
-  for (int m0 = 0; m0 < MH; m0 += 16) {
-    for (int n0 = 0; n0 < MH; n0 += 16) t.push_back({4, 1, m0, n0, MH, MH, OFF_W2, 0});
-    t.push_back({4, 6, m0, 0, MH, 1, OFF_B2, 1});
+__global__ void k_mlp_pack(MlpDev M) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < NP) store_copies(M, i, M.P[i]);
+}
+
+// ---------------------------------------------------------------------------
+// The sum of the partial gradients, in a fixed order: 64 parameters per
+// workgroup, each wave the partials w, w + 8, ..., then the eight waves' sums.
+// With step == 0 the gradient goes to G; with step >= 1 the parameters take an
+// Adam step (beta1 b1, beta2 b2, bias corrections c1, c2) and their bf16
+// copies are refreshed. The batch loss goes to *loss (mapped host memory) when
+// given. Bound by latency at 32 partials (2.7 MB, 3.9 us) and by reading them at
+// 256 (21.7 MB, 4.5 us).
+// ---------------------------------------------------------------------------
+constexpr int kSumWaves = 8;
+__global__ __launch_bounds__(64 * kSumWaves) void k_mlp_sum(MlpDev M, const float* __restrict__ part, int groups,
+                                                            float* __restrict__ G, float* loss, float inv, int step,
+                                                            float lr, float b1, float b2, float eps, float c1,
+                                                            float c2) {
+  __shared__ float s[kSumWaves][64];
+  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+  const int i = (int)blockIdx.x * 64 + lane;  // < kPartStride
+  float a = 0.f;
+  if (i <= kPartLoss) {
+    const float* src = part + (size_t)wv * kPartStride + i;
+#pragma unroll 8
+    for (int p = wv; p < groups; p += kSumWaves, src += (size_t)kSumWaves * kPartStride) a += *src;
   }
-  // dW1 [128][32] = dH1^T X and db1
-  for (int m0 = 0; m0 < MH; m0 += 16) {
-    for (int n0 = 0; n0 < MI; n0 += 16) t.push_back({5, 0, m0, n0, MH, MI, OFF_W1, 0});
-    t.push_back({5, 6, m0, 0, MH, 1, OFF_B1, 1});
+  s[wv][lane] = a;
+  __syncthreads();
+  if (wv != 0) return;
+#pragma unroll
+  for (int w = 1; w < kSumWaves; ++w) a += s[w][lane];
+  if (i == kPartLoss) {
+    if (loss) *loss = a * inv;
+  } else if (i < NP) {
+    if (step == 0) {
+      G[i] = a;
+    } else {
+      const float m = b1 * M.m[i] + (1.f - b1) * a;
+      const float v = b2 * M.v[i] + (1.f - b2) * a * a;
+      M.m[i] = m;
+      M.v[i] = v;
+      const float p = M.P[i] - lr * (m / c1) / (sqrtf(v / c2) + eps);
+      M.P[i] = p;
+      store_copies(M, i, p);
+    }
   }
-  return t;
 }
 
 hipError_t mlp_pack_launch(const MlpDev& M, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_adam, dim3((NP + 255) / 256), dim3(256), 0, s, M, (const float*)nullptr, 0, 0.f, 0.f, 0.f,
-                     0.f, 1.f, 1.f);
+  hipLaunchKernelGGL(k_mlp_pack, dim3((NP + 255) / 256), dim3(256), 0, s, M);
   return hipGetLastError();
 }
 
@@ -407,16 +453,8 @@ hipError_t mlp_pack_launch(const MlpDev& M, hipStream_t s) {
 // device address hipGetSymbolAddress returns (per device, at the first call on
 // that device); the array's name itself is not a device address on the host.
 // ---------------------------------------------------------------------------
-namespace {
-constexpr size_t up256c(size_t v) { return (v + 255) / 256 * 256; }
-// bytes of the scratch for a padded batch of kp rows (kp a multiple of 32)
-constexpr size_t noalloc_bytes(size_t kp) {
-  return up256c(2 * (size_t)MI * kp) + 4 * up256c(2 * (size_t)MH * kp) + up256c(2 * (size_t)MO * kp) +
-         2 * up256c(4 * (size_t)MO * kp) + up256c(4);
-}
-constexpr size_t kNoallocBytes = noalloc_bytes(VIO_MLP_NOALLOC_MAX_ROWS);
-static_assert(VIO_MLP_NOALLOC_MAX_ROWS % 32 == 0, "row maximum is a whole number of MFMA batch steps");
-}  // namespace
+static_assert(VIO_MLP_NOALLOC_MAX_ROWS <= 64 * 4 * kChunk, "at most 64 partial gradients (grad_groups)");
+constexpr size_t kNoallocBytes = sizeof(float) * 64 * kPartStride;
 
 static __device__ __align__(256) unsigned char scratch[kNoallocBytes];
 
@@ -439,33 +477,6 @@ void* noalloc_scratch(int* dev_out) {
   }
   return g_scratch_ptr[dev];
 }
-
-// The training scratch laid out in `base` for a padded batch of kp rows: the
-// same sub-buffers as a handle's arena, with the batch as leading dimension.
-struct NoallocLayout {
-  MlpScratch S;
-  float* y;
-};
-NoallocLayout noalloc_layout(unsigned char* base, int kp) {
-  size_t off = 0;
-  auto take = [&](size_t b) {
-    unsigned char* p = base + off;
-    off = up256c(off + b);
-    return p;
-  };
-  NoallocLayout L{};
-  L.S.ldt = kp;
-  L.S.Xt = reinterpret_cast<uint16_t*>(take(2 * (size_t)MI * kp));
-  L.S.H1t = reinterpret_cast<uint16_t*>(take(2 * (size_t)MH * kp));
-  L.S.H2t = reinterpret_cast<uint16_t*>(take(2 * (size_t)MH * kp));
-  L.S.dYt = reinterpret_cast<uint16_t*>(take(2 * (size_t)MO * kp));
-  L.S.dH2t = reinterpret_cast<uint16_t*>(take(2 * (size_t)MH * kp));
-  L.S.dH1t = reinterpret_cast<uint16_t*>(take(2 * (size_t)MH * kp));
-  L.S.dY = reinterpret_cast<float*>(take(4 * (size_t)MO * kp));
-  L.y = reinterpret_cast<float*>(take(4 * (size_t)MO * kp));
-  L.S.loss = reinterpret_cast<float*>(take(4));
-  return L;
-}
 }  // namespace
 
 hipError_t mlp_forward_launch(const MlpDev& M, const float* X, int K, float* Y, hipStream_t s) {
@@ -487,12 +498,10 @@ struct vio_mlp {
   int max_batch = 0;
   void* arena = nullptr;
   MlpDev M{};
-  MlpScratch S{};
-  float* d_y = nullptr;   // [ldt][3]
-  float* d_g = nullptr;   // [NP]
-  float* h_loss = nullptr;
+  float* d_part = nullptr;   // partial gradients [grad_groups(max_batch)][kPartStride]
+  float* h_loss = nullptr;   // pinned; the sum kernel writes it through hm_loss
+  float* hm_loss = nullptr;
   int step = 0;
-  int n_tiles = 0;
 };
 
 namespace {
@@ -507,7 +516,6 @@ int vio_mlp_create(int32_t max_batch, vio_mlp** out) {
   auto* m = new (std::nothrow) vio_mlp();
   if (!m) return VIO_ENOMEM;
   m->max_batch = max_batch;
-  const int ldt = (max_batch + 31) / 32 * 32;
   size_t off = 0;
   auto take = [&](size_t b) {
     const size_t o = off;
@@ -515,16 +523,15 @@ int vio_mlp_create(int32_t max_batch, vio_mlp** out) {
     return o;
   };
   const size_t oP = take(4 * NP), om = take(4 * NP), ov = take(4 * NP), oW1 = take(2 * MH * MI), oW2 = take(2 * MH * MH),
-               oW2t = take(2 * MH * MH), oW3 = take(2 * MO * MH), oXt = take(2 * (size_t)MI * ldt),
-               oH1 = take(2 * (size_t)MH * ldt), oH2 = take(2 * (size_t)MH * ldt), odYt = take(2 * (size_t)MO * ldt),
-               odH2 = take(2 * (size_t)MH * ldt), odH1 = take(2 * (size_t)MH * ldt), odY = take(4 * (size_t)MO * ldt),
-               oL = take(4), oy = take(4 * (size_t)MO * ldt), og = take(4 * NP);
+               oW2t = take(2 * MH * MH), oW3 = take(2 * MO * MH),
+               opart = take(sizeof(float) * kPartStride * (size_t)grad_groups(max_batch));
   if (hipMalloc(&m->arena, off) != hipSuccess) {
     delete m;
     return VIO_ENOMEM;
   }
   if (hipMemset(m->arena, 0, off) != hipSuccess ||
-      hipHostMalloc((void**)&m->h_loss, sizeof(float)) != hipSuccess) {
+      hipHostMalloc((void**)&m->h_loss, sizeof(float)) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&m->hm_loss, m->h_loss, 0) != hipSuccess) {
     vio_mlp_destroy(m);
     return VIO_EDEVICE;
   }
@@ -532,23 +539,7 @@ int vio_mlp_create(int32_t max_batch, vio_mlp** out) {
   m->M = {reinterpret_cast<float*>(b + oP), reinterpret_cast<float*>(b + om), reinterpret_cast<float*>(b + ov),
           reinterpret_cast<uint16_t*>(b + oW1), reinterpret_cast<uint16_t*>(b + oW2),
           reinterpret_cast<uint16_t*>(b + oW2t), reinterpret_cast<uint16_t*>(b + oW3)};
-  m->S = {ldt,
-          reinterpret_cast<uint16_t*>(b + oXt),
-          reinterpret_cast<uint16_t*>(b + oH1),
-          reinterpret_cast<uint16_t*>(b + oH2),
-          reinterpret_cast<uint16_t*>(b + odYt),
-          reinterpret_cast<uint16_t*>(b + odH2),
-          reinterpret_cast<uint16_t*>(b + odH1),
-          reinterpret_cast<float*>(b + odY),
-          reinterpret_cast<float*>(b + oL)};
-  m->d_y = reinterpret_cast<float*>(b + oy);
-  m->d_g = reinterpret_cast<float*>(b + og);
-  const std::vector<GradTile> tiles = grad_tiles();
-  m->n_tiles = (int)tiles.size();
-  if (hipMemcpyToSymbol(HIP_SYMBOL(c_tiles), tiles.data(), sizeof(GradTile) * tiles.size()) != hipSuccess) {
-    vio_mlp_destroy(m);
-    return VIO_EDEVICE;
-  }
+  m->d_part = reinterpret_cast<float*>(b + opart);
   *out = m;
   return VIO_OK;
 }
@@ -582,67 +573,54 @@ int vio_mlp_forward(vio_mlp* m, const float* d_x, int32_t k, float* d_y, void* h
                                                                                                   : VIO_EDEVICE;
 }
 
-// Forward, loss, backward and weight gradients of a batch through the
-// training scratch S (every scratch row the kernels read, padding rows
-// included, is written earlier in the same sequence) and forward output y.
-static int gradient_impl(vio_mlp* m, const float* d_x, const float* d_t, int k, float* d_grad, const MlpScratch& S,
-                         float* y, hipStream_t s) {
-  const int Kpad = (k + 31) / 32 * 32;
-  const int blocks = (Kpad / 16 + kMlpWaves - 1) / kMlpWaves;
-  hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(blocks), dim3(64 * kMlpWaves), 0, s, m->M, d_x, k, Kpad, y, S);
-  hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(1024), 0, s, (const float*)y, d_t, k, Kpad, S);
-  hipLaunchKernelGGL(k_mlp_bwd_data, dim3(blocks), dim3(64 * kMlpWaves), 0, s, m->M, Kpad, S);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((m->n_tiles + kMlpWaves - 1) / kMlpWaves), dim3(64 * kMlpWaves), 0, s,
-                     m->n_tiles, Kpad, S, d_grad);
+// The batch's partial gradients in `part`, then their sum: the gradient in
+// d_grad (step == 0) or an Adam step on the parameters (step >= 1); the loss in
+// the handle's pinned word.
+static int train_impl(vio_mlp* m, const float* d_x, const float* d_t, int k, float* part, float* d_grad, int step,
+                      float lr, hipStream_t s) {
+  const int chunks = (k + kChunk - 1) / kChunk, groups = grad_groups(k);
+  const float b1 = 0.9f, b2 = 0.999f;
+  const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
+  hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(64 * kGradWaves), 0, s, m->M, d_x, d_t, k, chunks, part);
+  hipLaunchKernelGGL(k_mlp_sum, dim3(kPartStride / 64), dim3(64 * kSumWaves), 0, s, m->M, (const float*)part, groups,
+                     d_grad, m->hm_loss, 1.f / (float)k, step, lr, b1, b2, 1e-8f, c1, c2);
   return hipGetLastError() == hipSuccess ? VIO_OK : VIO_EDEVICE;
+}
+
+static int gradient_impl(vio_mlp* m, const float* d_x, const float* d_t, int k, float* part, float* d_grad, float* loss,
+                         hipStream_t s) {
+  const int rc = train_impl(m, d_x, d_t, k, part, d_grad, 0, 0.f, s);
+  if (rc != VIO_OK) return rc;
+  if (hipStreamSynchronize(s) != hipSuccess) return VIO_EDEVICE;
+  if (loss) *loss = *m->h_loss;
+  return VIO_OK;
 }
 
 int vio_mlp_gradient(vio_mlp* m, const float* d_x, const float* d_targets, int32_t k, float* d_grad, float* loss,
                      void* hip_stream) {
   if (!m || !d_x || !d_targets || !d_grad || k < 1 || k > m->max_batch) return VIO_EINVAL;
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  int rc = gradient_impl(m, d_x, d_targets, k, d_grad, m->S, m->d_y, s);
-  if (rc != VIO_OK) return rc;
-  if (hipMemcpyAsync(m->h_loss, m->S.loss, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return VIO_EDEVICE;
-  if (loss) *loss = *m->h_loss;
-  return VIO_OK;
+  return gradient_impl(m, d_x, d_targets, k, m->d_part, d_grad, loss, static_cast<hipStream_t>(hip_stream));
 }
 
 int vio_mlp_gradient_noalloc(vio_mlp* m, const float* d_x, const float* d_targets, int32_t k, float* d_grad,
                              float* loss, void* hip_stream) {
   if (!m || !d_x || !d_targets || !d_grad || k < 1 || k > VIO_MLP_NOALLOC_MAX_ROWS) return VIO_EINVAL;
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
   int dev = 0;
   void* base = noalloc_scratch(&dev);
   if (!base) return VIO_EDEVICE;
-  const NoallocLayout L = noalloc_layout(static_cast<unsigned char*>(base), (k + 31) / 32 * 32);
-  int rc = gradient_impl(m, d_x, d_targets, k, d_grad, L.S, L.y, s);
-  if (rc != VIO_OK) return rc;
-  if (hipMemcpyAsync(m->h_loss, L.S.loss, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return VIO_EDEVICE;
-  if (loss) *loss = *m->h_loss;
-  return VIO_OK;
+  return gradient_impl(m, d_x, d_targets, k, static_cast<float*>(base), d_grad, loss,
+                       static_cast<hipStream_t>(hip_stream));
 }
 
 int vio_mlp_train_step(vio_mlp* m, const float* d_x, const float* d_targets, int32_t k, float lr, float* loss,
                        void* hip_stream) {
   if (!m || !d_x || !d_targets || k < 1 || k > m->max_batch || !(lr > 0.f)) return VIO_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  int rc = gradient_impl(m, d_x, d_targets, k, m->d_g, m->S, m->d_y, s);
+  const int rc = train_impl(m, d_x, d_targets, k, m->d_part, nullptr, m->step + 1, lr, s);
   if (rc != VIO_OK) return rc;
   m->step += 1;
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - std::pow(b1, (float)m->step), c2 = 1.f - std::pow(b2, (float)m->step);
-  hipLaunchKernelGGL(k_mlp_adam, dim3((NP + 255) / 256), dim3(256), 0, s, m->M, (const float*)m->d_g, m->step, lr, b1,
-                     b2, 1e-8f, c1, c2);
-  if (hipGetLastError() != hipSuccess) return VIO_EDEVICE;
   if (loss) {
-    if (hipMemcpyAsync(m->h_loss, m->S.loss, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return VIO_EDEVICE;
+    if (hipStreamSynchronize(s) != hipSuccess) return VIO_EDEVICE;
     *loss = *m->h_loss;
   }
   return VIO_OK;
