@@ -40,6 +40,13 @@ __device__ __forceinline__ bf16x8 pack8(const uint16_t v[8]) {
   return __builtin_bit_cast(bf16x8, u);
 }
 
+// Two floats as bf16 in the low and high half of a word: one instruction.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+}
+
 // Eight consecutive floats at a 4-byte aligned address (two 16-byte loads), and
 // as bf16, zeros instead where !keep (a mask, so that no load waits behind a
 // branch).
@@ -47,16 +54,9 @@ struct __attribute__((packed, aligned(4))) F32x8 {
   float v[8];
 };
 __device__ __forceinline__ bf16x8 pack_f32(const float v[8], bool keep) {
-  uint16_t h[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = bf16_bits(v[e]);
-  uint4 u = __builtin_bit_cast(uint4, pack8(h));
   const uint32_t m = keep ? 0xFFFFFFFFu : 0u;
-  u.x &= m;
-  u.y &= m;
-  u.z &= m;
-  u.w &= m;
-  return __builtin_bit_cast(bf16x8, u);
+  return __builtin_bit_cast(bf16x8, make_uint4(bf16_pair(v[0], v[1]) & m, bf16_pair(v[2], v[3]) & m,
+                                               bf16_pair(v[4], v[5]) & m, bf16_pair(v[6], v[7]) & m));
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {

@@ -6,9 +6,9 @@
 // segment of 8 bf16), B[8(l/16) .. +7][l%16] (a column segment) and returns
 // D[4(l/16) + q][l%16], q = 0..3.
 //
-// Inference: one wave per 16 rows. Layer 1 is one MFMA per 16 hidden units
-// (K = 32 is one step); the ReLU'd bf16 activations go through the wave's LDS
-// to become the next layer's A operand.
+// Inference (k_mlp_infer): layer 1 is one MFMA per 16 hidden units (K = 32 is one
+// step); the ReLU'd bf16 activations go through LDS to become the next layer's A
+// operand.
 //
 // Training: one kernel (k_mlp_grad) takes 32 rows at a time through the
 // forward pass, the loss, the data gradients (dH2 = dY W3, dH1 = dH2 W2,
@@ -30,93 +30,120 @@
 
 namespace vio {
 
-__device__ __forceinline__ bool relu_active(uint16_t h) { return h != 0 && !(h & 0x8000u); }
+// An MFMA result tile's four values of a lane (rows 4 g + q, q = 0..3, of its
+// column) as bf16, two to a word.
+struct Quad {
+  uint32_t w[2];
+};
+__device__ __forceinline__ Quad quad_of(f32x4 v) { return {bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])}; }
+__device__ __forceinline__ Quad quad_relu(f32x4 v, float b) {
+  return {bf16_pair(fmaxf(v[0] + b, 0.f), fmaxf(v[1] + b, 0.f)), bf16_pair(fmaxf(v[2] + b, 0.f), fmaxf(v[3] + b, 0.f))};
+}
+// the values of d where h (never negative: a ReLU's result) is not zero
+__device__ __forceinline__ Quad quad_where(Quad d, Quad h) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const u16x2 one = {1, 1};
+    const u16x2 on = __builtin_elementwise_min(__builtin_bit_cast(u16x2, h.w[k]), one);
+    d.w[k] &= __builtin_bit_cast(uint32_t, (u16x2)(-on));
+  }
+  return d;
+}
+// to column `unit` of rows row .. row + 3 of an LDS tile
+__device__ __forceinline__ void store_quad(uint16_t (*rows)[MH + 8], int row, int unit, Quad v) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    rows[row + 2 * k][unit] = (uint16_t)v.w[k];
+    rows[row + 2 * k + 1][unit] = (uint16_t)(v.w[k] >> 16);
+  }
+}
 
 // ---------------------------------------------------------------------------
-// inference forward: the same MFMA sequence as k_mlp_grad's forward pass (so
-// the same results). The bf16 weights and the biases (42 KB, L2-resident) are read
-// straight from global memory as MFMA operands, so a workgroup holds only its
-// waves' 4 KB activation tiles in LDS and fits beside the pyramid kernel's
-// workgroups when both run at once; layer 2's eight output tiles stay in
-// registers so its output reuses the wave's layer-1 tile.
+// inference forward, with the MFMA sequence of the training kernel and of the
+// frontend's learned stage (so the same results row by row). A workgroup of
+// eight waves takes chunks of 32 rows; wave w owns hidden units 16 w .. 16 w + 15
+// of both hidden layers and keeps its slices of W1 and W2 in registers for all
+// its chunks (a wave per 16 rows, each reading all 42 KB of weights, took 8.7 us
+// for 600 rows and 23.8 us for 65,536). The activations pass through LDS by
+// rows; the two output tiles of a chunk go to another pair of waves each time.
+// Bound by latency at small batches (the weights' loads, two barriers a chunk:
+// 4.4 us for 600 rows); 65,536 rows take 12.5 us.
 // ---------------------------------------------------------------------------
-constexpr int kInferWaves = 4;
-__global__ __launch_bounds__(64 * kInferWaves) void k_mlp_infer(MlpDev M, const float* __restrict__ X, int K,
-                                                               int Kpad, float* __restrict__ Y) {
-  __shared__ __align__(16) uint16_t sH[kInferWaves][16][MH];
-  const int tid = (int)threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int i0 = ((int)blockIdx.x * kInferWaves + wv) * 16;
-  if (i0 >= Kpad) return;  // no barrier follows
+constexpr int kHidWaves = MH / 16;  // one 16-unit hidden tile per wave
+constexpr int kChunk = 32;          // rows per chunk: two MFMA row tiles
+// workgroups at most: two per compute unit (65,536 rows: 512 workgroups 12.8 us,
+// 768 13.3, 1,024 14.2, one per chunk 19.4: each loads the weights once)
+constexpr int kInferGroups = 512;
+__global__ __launch_bounds__(64 * kHidWaves) void k_mlp_infer(MlpDev M, const float* __restrict__ X, int K,
+                                                              int n_chunks, float* __restrict__ Y) {
+  // rows padded by 8 entries: the 16 rows of an operand read start 4 banks apart
+  __shared__ __align__(16) uint16_t sH1[kChunk][MH + 8];
+  __shared__ __align__(16) uint16_t sH2[kChunk][MH + 8];
+  __shared__ uint4 sW3[MH / 32][64];  // W3 as the output tile's B operand (columns 3..15 are zero)
+  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
   const int r = lane & 15, g = lane >> 4;
-  uint16_t (*h)[MH] = sH[wv];
-  uint16_t xv[8];
-  {
-    const int i = i0 + r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) xv[e] = i < K ? bf16_bits(X[(size_t)i * MI + 8 * g + e]) : (uint16_t)0;
-  }
-  const bf16x8 a = pack8(xv);
+  const int unit = 16 * wv + r;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  // layer 1
+  F32x8 xr[2];  // a chunk's rows, loaded one chunk ahead (rows past the batch read its last row)
+  const auto fetch = [&](int ch) {
 #pragma unroll
-  for (int jt = 0; jt < MH / 16; ++jt) {
-    const int j = 16 * jt + r;
-    const f32x4 acc = mfma(a, load8(&M.W1b[j * MI + 8 * g]), zero);
-    const float b = M.P[OFF_B1 + j];
+    for (int t = 0; t < 2; ++t)
+      xr[t] = *reinterpret_cast<const F32x8*>(X + (size_t)min(ch * kChunk + 16 * t + r, K - 1) * MI + 8 * g);
+  };
+  fetch((int)blockIdx.x);
+  const bf16x8 w1 = load8(M.W1b + (size_t)unit * MI + 8 * g);
+  const float b1 = M.P[OFF_B1 + unit], b2 = M.P[OFF_B2 + unit], b3 = M.P[OFF_B3 + min(r, MO - 1)];
+  bf16x8 w2[MH / 32];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      h[row][j] = (i0 + row) < K ? bf16_bits(fmaxf(acc[q] + b, 0.f)) : (uint16_t)0;
+  for (int kc = 0; kc < MH / 32; ++kc) w2[kc] = load8(M.W2b + (size_t)unit * MH + 32 * kc + 8 * g);
+  if (wv < MH / 32) {
+    const uint4 w = *reinterpret_cast<const uint4*>(M.W3b + (size_t)min(r, MO - 1) * MH + 32 * wv + 8 * g);
+    sW3[wv][lane] = r < MO ? w : make_uint4(0u, 0u, 0u, 0u);
+  }
+  int turn = 0;  // the pair of waves whose turn the output tiles are
+  for (int ch = (int)blockIdx.x; ch < n_chunks; ch += (int)gridDim.x) {
+    const int i0 = ch * kChunk;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 acc = mfma(pack_f32(xr[t].v, i0 + 16 * t + r < K), w1, zero);
+      store_quad(sH1, 16 * t + 4 * g, unit, quad_relu(acc, b1));
     }
-  }
-  __builtin_amdgcn_wave_barrier();
-  // layer 2: all eight output tiles in registers, then written over h1
-  f32x4 acc2[MH / 16];
+    if (ch + (int)gridDim.x < n_chunks) fetch(ch + (int)gridDim.x);
+    __syncthreads();
 #pragma unroll
-  for (int jt = 0; jt < MH / 16; ++jt) {
-    const int j = 16 * jt + r;
-    f32x4 acc = zero;
+    for (int t = 0; t < 2; ++t) {
+      f32x4 acc = zero;
 #pragma unroll
-    for (int kc = 0; kc < MH / 32; ++kc)
-      acc = mfma(load8(&h[r][32 * kc + 8 * g]), load8(&M.W2b[j * MH + 32 * kc + 8 * g]), acc);
-    acc2[jt] = acc;
-  }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int jt = 0; jt < MH / 16; ++jt) {
-    const int j = 16 * jt + r;
-    const float b = M.P[OFF_B2 + j];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 4 * g + q;
-      h[row][j] = (i0 + row) < K ? bf16_bits(fmaxf(acc2[jt][q] + b, 0.f)) : (uint16_t)0;
+      for (int kc = 0; kc < MH / 32; ++kc) acc = mfma(load8(&sH1[16 * t + r][32 * kc + 8 * g]), w2[kc], acc);
+      store_quad(sH2, 16 * t + 4 * g, unit, quad_relu(acc, b2));
     }
-  }
-  __builtin_amdgcn_wave_barrier();
-  // layer 3: 3 outputs padded to a 16-column tile (zero weight rows)
-  f32x4 acc = zero;
+    // (the next chunk's h1 is written after this barrier, its h2 after the next
+    // one, which the waves that read h2 here reach last)
+    __syncthreads();
+    if ((wv >> 1) == turn) {
+      const int t = wv & 1;
+      f32x4 acc = zero;
 #pragma unroll
-  for (int kc = 0; kc < MH / 32; ++kc) {
-    // output columns 3..15 are zero weight rows
-    const bf16x8 w = r < MO ? load8(&M.W3b[r * MH + 32 * kc + 8 * g]) : __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
-    acc = mfma(load8(&h[r][32 * kc + 8 * g]), w, acc);
-  }
-  if (r < MO) {
-    const float b = M.P[OFF_B3 + r];
+      for (int kc = 0; kc < MH / 32; ++kc)
+        acc = mfma(load8(&sH2[16 * t + r][32 * kc + 8 * g]), __builtin_bit_cast(bf16x8, sW3[kc][lane]), acc);
+      if (r < MO) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = i0 + 4 * g + q;
-      if (i < K) Y[(size_t)i * MO + r] = acc[q] + b;
+        for (int q = 0; q < 4; ++q) {
+          const int i = i0 + 16 * t + 4 * g + q;
+          if (i < K) Y[(size_t)i * MO + r] = acc[q] + b3;
+        }
+      }
     }
+    turn = (turn + 1) & 3;
   }
 }
 
 // ---------------------------------------------------------------------------
 // training: loss and partial gradients
 //
-// A workgroup of eight waves takes chunks of 32 rows (two 16-row MFMA tiles);
-// wave w owns hidden units 16 w .. 16 w + 15 of both hidden layers, with its
+// A workgroup of eight waves takes chunks of 32 rows (two 16-row MFMA tiles, one
+// K step of the weight gradients); wave w owns hidden units 16 w .. 16 w + 15 of both hidden layers, with its
 // slices of W1, W2, W2^T and W3 in registers for all its chunks. A chunk's
 // activations and gradients never leave the compute unit: a wave holds its own
 // units' as MFMA results, and passes them on through LDS, by rows to become the
@@ -136,8 +163,6 @@ __global__ __launch_bounds__(64 * kInferWaves) void k_mlp_infer(MlpDev M, const 
 // operands in memory took 59 and 748 us (the weight gradient's 105 waves walked
 // the whole batch each, the loss ran in one workgroup).
 // ---------------------------------------------------------------------------
-constexpr int kGradWaves = MH / 16;  // one 16-unit hidden tile per wave
-constexpr int kChunk = 32;           // rows per chunk: one MFMA K step of the weight gradients
 // A partial gradient: the parameters in their order, then the loss sum, padded
 // to whole 64-float lines.
 constexpr int kPartLoss = NP;
@@ -152,18 +177,18 @@ int grad_groups(int k) {
   return std::min(chunks, std::max(64, std::min(256, chunks / 4)));
 }
 
-__device__ __forceinline__ bf16x8 pack_tiles(const uint16_t t0[4], const uint16_t t1[4]) {
-  const uint16_t v[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
-  return pack8(v);
+// both row tiles' values as one operand (k = 8 g + e: rows 4 g + e of tile 0, then of tile 1)
+__device__ __forceinline__ bf16x8 pack_tiles(Quad t0, Quad t1) {
+  return __builtin_bit_cast(bf16x8, make_uint4(t0.w[0], t0.w[1], t1.w[0], t1.w[1]));
 }
 
-__global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const float* __restrict__ X,
+__global__ __launch_bounds__(64 * kHidWaves) void k_mlp_grad(MlpDev M, const float* __restrict__ X,
                                                               const float* __restrict__ T, int K, int n_chunks,
                                                               float* __restrict__ part) {
   // rows padded by 8 entries: the 16 rows of an operand read start 4 banks apart
   __shared__ __align__(16) uint16_t sA[kChunk][MH + 8];  // h1 by rows, then dH2
   __shared__ __align__(16) uint16_t sH2[kChunk][MH + 8];
-  __shared__ uint4 sB[kGradWaves][64];  // h1 as B operands, by hidden tile
+  __shared__ uint4 sB[kHidWaves][64];  // h1 as B operands, by hidden tile
   __shared__ uint4 sX[MI / 16][64];     // x as B operands, by 16 features
   __shared__ uint4 sW3[MH / 32][64];
   __shared__ float sY[kChunk][4];
@@ -229,25 +254,32 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const fl
   for (int ch = (int)blockIdx.x; ch < n_chunks; ch += (int)gridDim.x) {
     const int i0 = ch * kChunk;
     // ---- layer 1 ----
-    bf16x8 h1p, h2p;
-    uint16_t h1[2][4], h2[2][4];
+    Quad h1[2], h2[2];
+    // rows of a batch's ragged last chunk that exist, as masks of the lane's words
+    const bool whole = i0 + kChunk <= K;
+    Quad rows[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int row = i0 + 16 * t + 4 * g + 2 * k;
+        rows[t].w[k] = (row < K ? 0xFFFFu : 0u) | (row + 1 < K ? 0xFFFF0000u : 0u);
+      }
+    const auto only_rows = [&](Quad v, int t) {
+      if (!whole) v = {v.w[0] & rows[t].w[0], v.w[1] & rows[t].w[1]};
+      return v;
+    };
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const f32x4 acc = mfma(pack_f32(xr[t].v, i0 + 16 * t + r < K), w1, zero);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = 16 * t + 4 * g + q;
-        h1[t][q] = i0 + row < K ? bf16_bits(fmaxf(acc[q] + b1, 0.f)) : (uint16_t)0;
-        sA[row][unit] = h1[t][q];
-      }
+      h1[t] = only_rows(quad_relu(acc, b1), t);
+      store_quad(sA, 16 * t + 4 * g, unit, h1[t]);
     }
-    h1p = pack_tiles(h1[0], h1[1]);
-    sB[wv][lane] = __builtin_bit_cast(uint4, h1p);
+    sB[wv][lane] = __builtin_bit_cast(uint4, pack_tiles(h1[0], h1[1]));
     if (wv >= 2 && wv < 2 + MI / 16) {
-      uint16_t v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = i0 + 16 * (e >> 2) + 4 * g + (e & 3) < K ? bf16_bits(xc[e]) : (uint16_t)0;
-      sX[wv - 2][lane] = __builtin_bit_cast(uint4, pack8(v));
+      const Quad x0 = only_rows({bf16_pair(xc[0], xc[1]), bf16_pair(xc[2], xc[3])}, 0);
+      const Quad x1 = only_rows({bf16_pair(xc[4], xc[5]), bf16_pair(xc[6], xc[7])}, 1);
+      sX[wv - 2][lane] = __builtin_bit_cast(uint4, pack_tiles(x0, x1));
     }
     const float gtx = tx, gty = ty;
     if (ch + (int)gridDim.x < n_chunks) fetch(ch + (int)gridDim.x);
@@ -258,14 +290,10 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const fl
       f32x4 acc = zero;
 #pragma unroll
       for (int kc = 0; kc < MH / 32; ++kc) acc = mfma(load8(&sA[16 * t + r][32 * kc + 8 * g]), w2[kc], acc);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = 16 * t + 4 * g + q;
-        h2[t][q] = i0 + row < K ? bf16_bits(fmaxf(acc[q] + b2, 0.f)) : (uint16_t)0;
-        sH2[row][unit] = h2[t][q];
-      }
+      h2[t] = only_rows(quad_relu(acc, b2), t);
+      store_quad(sH2, 16 * t + 4 * g, unit, h2[t]);
     }
-    h2p = pack_tiles(h2[0], h2[1]);
+    const bf16x8 h2p = pack_tiles(h2[0], h2[1]);
     __syncthreads();
     // ---- layer 3 and the loss: wave t < 2 takes row tile t, lane l < 16 its row l ----
     if (wv < 2) {
@@ -300,18 +328,14 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const fl
     }
     __syncthreads();
     // ---- dH2 = (dY W3) * [h2 > 0] ----
-    uint16_t d2[2][4], d1[2][4];
+    Quad d2[2], d1[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       uint16_t av[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
       for (int c = 0; c < MO; ++c) av[c] = g == 0 ? sdY[c][16 * t + r] : (uint16_t)0;
-      const f32x4 acc = mfma(pack8(av), w3c, zero);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        d2[t][q] = relu_active(h2[t][q]) ? bf16_bits(acc[q]) : (uint16_t)0;
-        sA[16 * t + 4 * g + q][unit] = d2[t][q];
-      }
+      d2[t] = quad_where(quad_of(mfma(pack8(av), w3c, zero)), h2[t]);
+      store_quad(sA, 16 * t + 4 * g, unit, d2[t]);
     }
     const bf16x8 d2p = pack_tiles(d2[0], d2[1]);
     __syncthreads();
@@ -321,8 +345,7 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(MlpDev M, const fl
       f32x4 acc = zero;
 #pragma unroll
       for (int kc = 0; kc < MH / 32; ++kc) acc = mfma(load8(&sA[16 * t + r][32 * kc + 8 * g]), w2t[kc], acc);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) d1[t][q] = relu_active(h1[t][q]) ? bf16_bits(acc[q]) : (uint16_t)0;
+      d1[t] = quad_where(quad_of(acc), h1[t]);
     }
     const bf16x8 d1p = pack_tiles(d1[0], d1[1]);
     // ---- weight gradients over the chunk's rows ----
@@ -481,9 +504,8 @@ void* noalloc_scratch(int* dev_out) {
 
 hipError_t mlp_forward_launch(const MlpDev& M, const float* X, int K, float* Y, hipStream_t s) {
   if (K <= 0) return hipSuccess;
-  const int Kpad = (K + 15) / 16 * 16;
-  const int blocks = (Kpad / 16 + kInferWaves - 1) / kInferWaves;
-  launch_kernel(k_mlp_infer, dim3(blocks), dim3(64 * kInferWaves), 0, s, M, X, K, Kpad, Y);
+  const int chunks = (K + kChunk - 1) / kChunk;
+  launch_kernel(k_mlp_infer, dim3(std::min(chunks, kInferGroups)), dim3(64 * kHidWaves), 0, s, M, X, K, chunks, Y);
   return hipGetLastError();
 }
 
@@ -581,7 +603,7 @@ static int train_impl(vio_mlp* m, const float* d_x, const float* d_t, int k, flo
   const int chunks = (k + kChunk - 1) / kChunk, groups = grad_groups(k);
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
-  hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(64 * kGradWaves), 0, s, m->M, d_x, d_t, k, chunks, part);
+  hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(64 * kHidWaves), 0, s, m->M, d_x, d_t, k, chunks, part);
   hipLaunchKernelGGL(k_mlp_sum, dim3(kPartStride / 64), dim3(64 * kSumWaves), 0, s, m->M, (const float*)part, groups,
                      d_grad, m->hm_loss, 1.f / (float)k, step, lr, b1, b2, 1e-8f, c1, c2);
   return hipGetLastError() == hipSuccess ? VIO_OK : VIO_EDEVICE;

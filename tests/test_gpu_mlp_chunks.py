@@ -53,3 +53,25 @@ def test_gradient_and_step_at_chunk_edges(n):
     move = want.astype(np.float64) - P
     tol = 1e-2 * np.abs(move) + 2.0 ** -22 * np.abs(P)
     assert (np.abs(got.astype(np.float64) - want) <= tol).all()
+
+
+# more chunks than workgroups (512) with a ragged last one; exactly two rounds; one row
+@pytest.mark.parametrize("n", [1, 33, 16385, 32768])
+def test_forward_at_chunk_edges(n):
+    """Outputs within 2e-2 of the mean magnitude of the oracle's (bfloat16
+    flips), the median within 1e-3 of it, and nothing written past row n."""
+    import torch
+    import paper_2609_30459_amd as vf
+    P = oracle.mlp_init(23)
+    P[-3:] = [0.05, -0.02, 0.1]
+    X, _ = _data(n, 500 + n)
+    want, _, _ = oracle.mlp_forward(P, X)
+    with vf.Mlp(16) as net:
+        net.set_params(P)
+        y = torch.full((n + 8, 3), 7.0, device="cuda")
+        net.forward(torch.from_numpy(X).cuda(), y)
+        got = y.cpu().numpy()
+    assert (got[n:] == 7.0).all()
+    scale = np.abs(want).mean() + 1e-3
+    err = np.abs(got[:n] - want)
+    assert err.max() <= 2e-2 * scale and np.median(err) <= 1e-3 * scale, (err.max(), scale)
