@@ -14,6 +14,8 @@ constexpr int kMaxLevels = VIO_MAX_LEVELS;
 constexpr int kMaxCams = VIO_MAX_CAMERAS;
 constexpr int kPatch = 52;      // pattern points (Sec. III-E)
 constexpr int kTileDefault = 64;  // level-0 tile edge of the pyramid/detector kernel unless chosen
+// Row pitch of a pyramid level `width` pixels wide.
+__host__ __device__ constexpr int level_pitch(int width) { return (width + 63) & ~63; }
 // Kernel timing: while set, the frontend's kernel launches on this thread
 // attach these events to the dispatch itself (the kernel's own start and end
 // timestamps, without the gaps between launches); null for plain launches and

@@ -422,7 +422,7 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
       c.tile_begin = tiles;
       tiles += c.tiles_x * c.tiles_y;
       for (int l = 0; l < P.levels; ++l) {
-        c.pitch[l] = (int)round_up((size_t)(si.w >> l), 64);
+        c.pitch[l] = level_pitch(si.w >> l);
         // one guard row: the tracker's template window reads up to one row and
         // one column past a level (with weight 0)
         for (int ps = 0; ps < kPyrSlots; ++ps)

@@ -9,7 +9,11 @@
 //
 // A keypoint's time is its chain of dependent steps (2 passes x L levels x N
 // iterations), each a gather, a reduction and a little wave-uniform math, with
-// about one wave per SIMD at these sizes. The kernel is shaped for that chain:
+// about one wave per SIMD at these sizes: 995 items of 4 levels x 5 iterations
+// take 22.3 us (49k cycles an item, 720 of them per iteration of about 85
+// instructions; 29.2 us with samples gathered from global memory, the templates
+// of each level loaded after the last one's and control flow through lane
+// masks). The kernel is shaped for that chain:
 //  * one copy of the alignment code per kernel: the learned attempt and the
 //    plain one, and the forward and backward passes, run it in a loop with the
 //    level count as an argument, so it is inlined and every descriptor field,
@@ -32,9 +36,17 @@
 //    unaligned 32-bit rows;
 //  * wave-uniform math uses the hardware reciprocal and sine/cosine, and a
 //    series for the SE(2) exponential;
-//  * gathers are global loads at a 32-bit offset from the level's scalar base,
-//    through the L1 cache (the patch's lines stay hot across a level's
-//    iterations).
+//  * pixels come through LDS: a track's forward and backward passes read the
+//    same two places, so every level's window of 24 x 21 pixels around the
+//    keypoint and around the start goes straight to the wave's LDS when the
+//    track begins (asynchronous loads, no registers, one wait). The forward
+//    pass takes its templates from the first and its samples from the second,
+//    the backward pass the other way round; a level whose position has moved
+//    out of its window loads a new one, and an iteration whose samples leave it
+//    (a wave vote in the shadow of the reads) reads global memory;
+//  * a pass's keypoint, start and budget are scalars to the compiler, so its
+//    control flow is scalar branches, few of them, with the rare sides out of
+//    line; per-level uniform math runs in lanes, lane l on level l.
 // Decisions (template fit, degeneracy, leaving the image) are taken in the
 // same order as a level-by-level pass, so the status is that of the paper's
 // procedure.
@@ -76,10 +88,24 @@ __device__ __forceinline__ uint32_t ld32(gbytes p, uint32_t off) {
   return ((const __attribute__((address_space(1))) U32*)(p + off))->v;
 }
 
-__device__ __forceinline__ bool wave_all(bool p) { return __all(p); }
-__device__ __forceinline__ bool wave_any(bool p) { return __any(p); }
+// votes of the whole wave (all 64 lanes active)
+__device__ __forceinline__ bool wave_all(bool p) { return __builtin_amdgcn_ballot_w64(p) == ~0ull; }
+__device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0ull; }
+// a value every lane holds, marked so for the compiler
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// x - floor(x), exact for the non-negative positions it is used on
+__device__ __forceinline__ float fract(float x) { return __builtin_amdgcn_fractf(x); }
+// the hardware's truncation, any value (NaN: 0, out of range: saturated)
+__device__ __forceinline__ int trunc_i(float x) {
+  int i;
+  asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+  return i;
+}
 
 __device__ __forceinline__ void pattern_of(int lane, float& u, float& v, float& w) {
   // rows v = -3.5 .. 3.5 hold 4, 6, 8, 8, 8, 8, 6, 4 points; row starts 0, 4,
@@ -123,21 +149,111 @@ __device__ __forceinline__ float bilinear(const Level& I, float x, float y) {
   return (1.f - fy) * ((1.f - fx) * a + fx * b) + fy * ((1.f - fx) * c + fx * d);
 }
 
+// ---- a level's window of pixels in the wave's LDS ----------------------------
+// kWinW x kWinH bytes from (x, y), x a multiple of 4; rows of six dwords, loaded
+// as 128 dwords by two asynchronous loads of the wave (the last two are not
+// used). The samples of a patch of radius 3.81 around the window's centre keep a
+// slack of at least 5 px on every side, a template (two more pixels) of 3.5 px.
+constexpr int kWinW = 24, kWinH = 21, kWinLead = 9;
+constexpr int kWinWords = 128;
+constexpr int kWinBytes = 4 * kWinWords;
+static_assert(kWinW % 4 == 0 && kWinW / 4 * kWinH <= kWinWords, "a window is two loads of 64 dwords");
+// a block's windows, [wave][image][level], aligned to a window; a template's
+// reads run up to three rows and one dword past its first
+template <int L>
+constexpr int kWinBlock = kTrackWaves * 2 * L * kWinWords + 3 * (kWinW / 4) + 2;
+typedef __attribute__((address_space(3))) uint32_t* lds_words;
+
+// The windows of one image's levels: lane l holds level l's position (a wave's
+// uniform math over the levels runs in its lanes; lanes past the levels are not
+// used).
+struct Windows {
+  int x, y;
+};
+__device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_of(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
+// Position of the window around (cx, cy) in a w x h image.
+__device__ __forceinline__ Windows window_around(int w, int h, float cx, float cy) {
+  return {((int)fminf(fmaxf(cx, 0.f), (float)(w - 1)) - kWinLead) & ~3,
+          (int)fminf(fmaxf(cy, 0.f), (float)(h - 1)) - kWinLead};
+}
+
+// Row and byte column of this lane's two dwords (lane and lane + 64) of a window.
+struct WinTask {
+  int row[2], col[2];
+};
+__device__ __forceinline__ WinTask window_task(int lane) {
+  WinTask t;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    t.row[k] = (lane + kW * k) / (kWinW / 4);
+    t.col[k] = 4 * (lane + kW * k - t.row[k] * (kWinW / 4));
+  }
+  return t;
+}
+
+// Starts the loads of the window at (x, y) of a w x h level (pixels at p) into
+// `win`, all wave-uniform; rows and columns outside the image repeat its edge
+// (no sample in the image's domain uses them with a weight). The caller waits
+// for them (window_wait) before it reads.
+__device__ __forceinline__ void window_load(gbytes p, int w, int h, int x, int y, lds_words win, const WinTask& wt) {
+  const int pitch = level_pitch(w);
+  // (row 21 holds the two unused dwords)
+  const bool whole = (x >= 0) & (x + kWinW <= pitch) & (y >= 0) & (y + kWinH < h);
+  const gbytes base = whole ? p + (y * pitch + x) : p;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    uint32_t o = __umul24((uint32_t)wt.row[k], (uint32_t)pitch) + (uint32_t)wt.col[k];
+    if (!whole) {
+      const int yy = min(max(y + wt.row[k], 0), h - 1), xx = min(max(x + wt.col[k], 0), pitch - 4);
+      o = (uint32_t)(yy * pitch + xx);
+    }
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + o), win + kW * k, 4, 0,
+                                     0);
+  }
+}
+// The wave's windows have arrived (it wrote and reads them itself: no barrier).
+__device__ __forceinline__ void window_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// y kWinW + x for a pixel (one 24-bit multiply-add)
+__device__ __forceinline__ uint32_t window_offset(int x, int y) {
+  uint32_t o;
+  static_assert(kWinW == 24, "the multiplier below");
+  asm("v_mad_u32_u24 %0, %1, 24, %2" : "=v"(o) : "v"(y), "v"(x));
+  return o;
+}
+
+// bilinear() from the window at LDS byte address `base` whose first pixel is
+// byte -`first` (first = w.y * kWinW + w.x); valid where the sample lies in the
+// window and the image's domain (elsewhere the address stays in the window). At
+// x = W-1 the pixels are W-1 with weight 1 and W with weight 0, the value of
+// the clamped form; likewise y.
+__device__ __forceinline__ float bilinear_win(uint32_t base, int first, float x, float y) {
+  const float fx = fract(x), fy = fract(y);
+  const uint32_t o = window_offset(trunc_i(x), trunc_i(y)) - (uint32_t)first;
+  const lds_words p = (lds_words)(uintptr_t)((o & (uint32_t)(kWinBytes - 4)) | base);
+  const uint32_t r0 = __builtin_amdgcn_alignbyte(p[1], p[0], o);
+  const uint32_t r1 = __builtin_amdgcn_alignbyte(p[kWinW / 4 + 1], p[kWinW / 4], o);
+  const float a = (float)(r0 & 0xFFu), b = (float)((r0 >> 8) & 0xFFu), c = (float)(r1 & 0xFFu),
+              d = (float)((r1 >> 8) & 0xFFu);
+  return (1.f - fy) * ((1.f - fx) * a + fx * b) + fy * ((1.f - fx) * c + fx * d);
+}
+
 // Template samples at (x, y): I(x, y) and the central differences
 // (I(x+1, y) - I(x-1, y)) / 2, (I(x, y+1) - I(x, y-1)) / 2, all bilinear as
-// above. The caller has checked that x +- 1 and y +- 1 lie in the domain, so
-// floor(x) - 1 >= 0 and floor(y) - 1 >= 0. The five samples share the 4x4
-// window from (floor(x) - 1, floor(y) - 1) and the fractions of (x, y). At
-// x = W-2 exactly the right sample's clamped form (ix = W-2, fx = 1) equals
-// this one (ix = W-1, fx = 0), and the window's last column (x = W) enters
-// with weight 0; likewise y = H-2 and the window's last row (y = H): each
-// level buffer has a guard row, so these reads stay inside it.
-__device__ __forceinline__ void template_samples(const Level& I, float x, float y, float& i0, float& gx, float& gy) {
-  const int fxi = (int)floorf(x), fyi = (int)floorf(y);
-  const float fx = x - (float)fxi, fy = y - (float)fyi;
-  const uint32_t o = (uint32_t)((fyi - 1) * I.pitch + (fxi - 1));
-  const uint32_t pt = (uint32_t)I.pitch;
-  const uint32_t w0 = ld32(I.p, o), w1 = ld32(I.p, o + pt), w2 = ld32(I.p, o + 2u * pt), w3 = ld32(I.p, o + 3u * pt);
+// above. They share the 4x4 pixels from (floor(x) - 1, floor(y) - 1) and the
+// fractions of (x, y). The caller has checked that x +- 1 and y +- 1 lie in the
+// domain. At x = W-2 exactly the right sample's clamped form (ix = W-2, fx = 1)
+// equals this one (ix = W-1, fx = 0), and the last of the four columns (x = W)
+// enters with weight 0; likewise y = H-2 and the last row (y = H).
+struct Window4 {
+  uint32_t w[4];  // four rows of four pixels
+};
+__device__ __forceinline__ void template_samples(const Window4& q, float fx, float fy, float& i0, float& gx, float& gy) {
+  const uint32_t w0 = q.w[0], w1 = q.w[1], w2 = q.w[2], w3 = q.w[3];
   const float gfx = 1.f - fx, gfy = 1.f - fy;
   auto px = [](uint32_t w, int c) { return (float)((w >> (8 * c)) & 0xFFu); };
   auto h = [&](uint32_t w, int c) { return gfx * px(w, c) + fx * px(w, c + 1); };
@@ -148,6 +264,23 @@ __device__ __forceinline__ void template_samples(const Level& I, float x, float 
   const float iyp = gfy * h21 + fy * h31, iym = gfy * h01 + fy * h11;
   gx = (ixp - ixm) * 0.5f;
   gy = (iyp - iym) * 0.5f;
+}
+// the 4x4 pixels from global memory (each level buffer has a guard row, so row H
+// stays inside it)
+__device__ __forceinline__ Window4 template_load(const Level& I, float x, float y) {
+  const uint32_t o = (uint32_t)(((int)floorf(y) - 1) * I.pitch + ((int)floorf(x) - 1));
+  const uint32_t pt = (uint32_t)I.pitch;
+  return {{ld32(I.p, o), ld32(I.p, o + pt), ld32(I.p, o + 2u * pt), ld32(I.p, o + 3u * pt)}};
+}
+// the 4x4 pixels from the window at `base` (see bilinear_win)
+__device__ __forceinline__ Window4 template_win(uint32_t base, int first, float x, float y) {
+  const uint32_t o = window_offset(trunc_i(x), trunc_i(y)) - (uint32_t)(first + kWinW + 1);
+  const lds_words p = (lds_words)(uintptr_t)((o & (uint32_t)(kWinBytes - 4)) | base);
+  Window4 q;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    q.w[r] = __builtin_amdgcn_alignbyte(p[r * (kWinW / 4) + 1], p[r * (kWinW / 4)], o);
+  return q;
 }
 
 // Camera descriptors are read-only while the tracker runs: read through the
@@ -175,21 +308,21 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
   return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
 }
 
-// Sums of K values per level (level-major v[K*l + k]) over the first nl of L
-// levels: all L levels in one call when all are used (the plain budget), else
-// two levels at a time behind wave-uniform tests, so a short learned budget
-// does not reduce the levels it never visits.
-template <int L, int K, int l = 0>
-__device__ __forceinline__ void level_pair_sums(float* v, int nl, int lane) {
+// Sums of K values per level, gen(K l + k) being a lane's value k of level l,
+// over the first nl of L levels: all L levels in one call when all are used (the
+// plain budget), else two levels at a time behind wave-uniform tests, so a short
+// learned budget does not reduce the levels it never visits.
+template <int L, int K, int l = 0, class Gen>
+__device__ __forceinline__ void level_pair_sums(float* out, const Gen& gen, int nl, int lane) {
   if constexpr (l < L) {
-    if (l < nl) wave_sums<(l + 1 < L ? 2 : 1) * K>(v + K * l, lane);
-    level_pair_sums<L, K, l + 2>(v, nl, lane);
+    if (l < nl) wave_sums_of<(l + 1 < L ? 2 : 1) * K, K * l>(out, gen, lane);
+    level_pair_sums<L, K, l + 2>(out, gen, nl, lane);
   }
 }
-template <int L, int K>
-__device__ __forceinline__ void level_sums(float* v, int nl, int lane) {
-  if (nl >= L) wave_sums<K * L>(v, lane);
-  else level_pair_sums<L, K>(v, nl, lane);
+template <int L, int K, class Gen>
+__device__ __forceinline__ void level_sums(float* out, const Gen& gen, int nl, int lane) {
+  if (nl >= L) wave_sums_of<K * L, 0>(out, gen, lane);
+  else level_pair_sums<L, K>(out, gen, nl, lane);
 }
 
 struct PassOut {
@@ -199,9 +332,10 @@ struct PassOut {
 
 // SE(2) exponential of (d0, d1, phi): translation V(phi) (d0, d1) with
 // V = [[a, -b], [b, a]], a = sin(phi)/phi, b = (1 - cos(phi))/phi.
-__device__ __forceinline__ void se2_v(float phi, float& a, float& b) {
+// small: |phi| < 0.25 (in every lane that uses the result)
+__device__ __forceinline__ void se2_v(float phi, bool small, float& a, float& b) {
   const float p2 = phi * phi;
-  if (fabsf(phi) < 0.25f) {  // series, error below 2e-9 here
+  if (__builtin_expect(small, 1)) {  // series, error below 2e-9 here
     a = 1.f - p2 * (1.f / 6.f - p2 * (1.f / 120.f - p2 * (1.f / 5040.f)));
     b = phi * (0.5f - p2 * (1.f / 24.f - p2 * (1.f / 720.f - p2 * (1.f / 40320.f))));
   } else {
@@ -217,34 +351,79 @@ __device__ __forceinline__ void se2_v(float phi, float& a, float& b) {
 // a level whose template does not fit is skipped.
 template <int L>
 __device__ __forceinline__ PassOut klt_pass(const CamDesc& csrc_in, int ssrc_in, const CamDesc& cdst_in, int sdst_in,
-                                            float px, float py, float ix, float iy, float ith, int nl, int N, float u,
-                                            float v, float wgt, int lane) {
+                                            float px_in, float py_in, float ix_in, float iy_in, float ith_in,
+                                            int nl_in, int N_in, float u, float v, float wgt, int lane,
+                                            bool fresh, lds_words sw, Windows& ws, lds_words dw, Windows& wd) {
   // the pass's cameras and slots are the wave's (the passes swap them)
   const cdesc_k csrc = (cdesc_k)uniform_ptr(&csrc_in);
   const cdesc_k cdst = (cdesc_k)uniform_ptr(&cdst_in);
-  const int ssrc = __builtin_amdgcn_readfirstlane(ssrc_in), sdst = __builtin_amdgcn_readfirstlane(sdst_in);
+  const int ssrc = uniform(ssrc_in), sdst = uniform(sdst_in);
+  // so are its keypoint, start and budget: the pass's control flow is scalar
+  const float px = uniform(px_in), py = uniform(py_in), ix = uniform(ix_in), iy = uniform(iy_in), ith = uniform(ith_in);
+  const int nl = uniform(nl_in), N = uniform(N_in);
   PassOut o{VIO_TRACKED, 0.f, 0.f, 0.f, 0.f};
-  // ---- templates of all levels (Sec. III-E) ------------------------------
+  // ---- the windows: around the keypoint in the source image (in LDS at sw,
+  // positions ws) and around the start in the destination (dw, wd) -----------
+  const int src_w = csrc->w, src_h = csrc->h, dst_w = cdst->w, dst_h = cdst->h;
   bool fits[L], valid[L];
+  {
+    gbytes sp[L], dp[L];  // every level's pixels (one wait for the scalar loads)
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      sp[l] = (gbytes)csrc->lvl[ssrc][l];
+      dp[l] = (gbytes)cdst->lvl[sdst][l];
+    }
+    // lane l: level l
+    const int lv = lane & 7;
+    const float sc = ldexpf(1.f, -lv);
+    const int sw_l = src_w >> lv, sh_l = src_h >> lv;
+    const float cx = px * sc, cy = py * sc;
+    const float x0 = cx - 3.5f, x1 = cx + 3.5f, y0 = cy - 3.5f, y1 = cy + 3.5f;
+    // the template fits where every point's x +- 1 and y +- 1 lie in the domain:
+    // the pattern's outermost points' (a point's position rises with its offset)
+    const uint64_t fit = __builtin_amdgcn_ballot_w64((x0 - 1.f >= 0.f) & (x1 + 1.f <= (float)(sw_l - 1)) &
+                                                     (y0 - 1.f >= 0.f) & (y1 + 1.f <= (float)(sh_l - 1)));
+    // its pixels are in the window there is (after a forward pass)
+    const bool have = (!fresh) & (x0 - 1.f >= (float)ws.x) & (x1 + 3.f <= (float)(ws.x + kWinW)) &
+                      (y0 - 1.f >= (float)ws.y) & (y1 + 3.f <= (float)(ws.y + kWinH));
+    const uint64_t need = ~__builtin_amdgcn_ballot_w64(have) & ((1u << nl) - 1u);
+    const Windows at = window_around(sw_l, sh_l, cx, cy);
+    ws.x = have ? ws.x : at.x;
+    ws.y = have ? ws.y : at.y;
+#pragma unroll
+    for (int l = 0; l < L; ++l) fits[l] = (fit >> l) & 1;
+    if (need != 0) {
+      const WinTask wt = window_task(lane);
+#pragma unroll
+      for (int l = 0; l < L; ++l)
+        if ((need >> l) & 1)
+          window_load(sp[l], src_w >> l, src_h >> l, lane_of(ws.x, l), lane_of(ws.y, l), sw + kWinWords * l, wt);
+      if (fresh) {
+        wd = window_around(dst_w >> lv, dst_h >> lv, ix * sc, iy * sc);
+#pragma unroll
+        for (int l = 0; l < L; ++l)
+          if (l < nl)
+            window_load(dp[l], dst_w >> l, dst_h >> l, lane_of(wd.x, l), lane_of(wd.y, l), dw + kWinWords * l, wt);
+      }
+      window_wait();
+    }
+  }
+  const uint32_t sbase = (uint32_t)uniform((int)(uint32_t)(uintptr_t)sw);
+  const uint32_t dbase = (uint32_t)uniform((int)(uint32_t)(uintptr_t)dw);
+  const int sfirst = ws.y * kWinW + ws.x;
+  // ---- templates of all levels (Sec. III-E) ------------------------------
   float T[L], G0[L], G1[L], G2[L], k[3 * L];
   float I0[L], gxr[L], gyr[L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    fits[l] = false;
-    I0[l] = gxr[l] = gyr[l] = 0.f;
-    if (l < nl) {
-      const Level S = level_of(csrc, ssrc, l);
-      const float sc = 1.f / (float)(1 << l);
-      const float sx = px * sc + u, sy = py * sc + v;
-      fits[l] = wave_all(in_dom(S, sx - 1.f, sy) & in_dom(S, sx + 1.f, sy) & in_dom(S, sx, sy - 1.f) &
-                         in_dom(S, sx, sy + 1.f));
-      if (fits[l]) template_samples(S, sx, sy, I0[l], gxr[l], gyr[l]);
-    }
+    const float sc = 1.f / (float)(1 << l);
+    const float sx = px * sc + u, sy = py * sc + v;
+    template_samples(template_win(sbase + kWinBytes * l, lane_of(sfirst, l), sx, sy), fract(sx), fract(sy), I0[l], gxr[l], gyr[l]);
   }
   float mean[L];
 #pragma unroll
-  for (int l = 0; l < L; ++l) mean[l] = wgt * I0[l];
-  level_sums<L, 1>(mean, nl, lane);
+  for (int l = 0; l < L; ++l) mean[l] = 0.f;
+  level_sums<L, 1>(mean, [&](int l) { return wgt * I0[l]; }, nl, lane);
   float J0[L], J1[L], J2[L], hs[6 * L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
@@ -254,14 +433,19 @@ __device__ __forceinline__ PassOut klt_pass(const CamDesc& csrc_in, int ssrc_in,
     J0[l] = gxr[l] * im;
     J1[l] = gyr[l] * im;
     J2[l] = J1[l] * u - J0[l] * v;
-    hs[6 * l + 0] = wgt * J0[l] * J0[l];
-    hs[6 * l + 1] = wgt * J0[l] * J1[l];
-    hs[6 * l + 2] = wgt * J0[l] * J2[l];
-    hs[6 * l + 3] = wgt * J1[l] * J1[l];
-    hs[6 * l + 4] = wgt * J1[l] * J2[l];
-    hs[6 * l + 5] = wgt * J2[l] * J2[l];
   }
-  level_sums<L, 6>(hs, nl, lane);
+  // H_l = sum w J^T J: (00, 01, 02, 11, 12, 22) of level l at 6 l .. 6 l + 5
+#pragma unroll
+  for (int i = 0; i < 6 * L; ++i) hs[i] = 0.f;
+  level_sums<L, 6>(
+      hs,
+      [&](int i) {
+        const int l = i / 6, m = i % 6;
+        const float a = m < 3 ? J0[l] : m < 5 ? J1[l] : J2[l];
+        const float b = m == 0 ? J0[l] : m == 1 || m == 3 ? J1[l] : J2[l];
+        return wgt * a * b;
+      },
+      nl, lane);
 #pragma unroll
   for (int l = 0; l < L; ++l) {
     valid[l] = false;
@@ -285,15 +469,31 @@ __device__ __forceinline__ PassOut klt_pass(const CamDesc& csrc_in, int ssrc_in,
     G0[l] = wgt * (i00 * J0[l] + i01 * J1[l] + i02 * J2[l]);
     G1[l] = wgt * (i01 * J0[l] + i11 * J1[l] + i12 * J2[l]);
     G2[l] = wgt * (i02 * J0[l] + i12 * J1[l] + i22 * J2[l]);
-    valid[l] = mean[l] > 0.f && det > 1e-6f * tr3 * tr3 * tr3 &&
-               wave_all(isfinite(G0[l]) & isfinite(G1[l]) & isfinite(G2[l]));
-    k[3 * l + 0] = G0[l] * T[l];
-    k[3 * l + 1] = G1[l] * T[l];
-    k[3 * l + 2] = G2[l] * T[l];
+    valid[l] = wave_all((mean[l] > 0.f) & (det > 1e-6f * tr3 * tr3 * tr3) & isfinite(G0[l]) & isfinite(G1[l]) &
+                        isfinite(G2[l]));
   }
-  level_sums<L, 3>(k, nl, lane);
+  // c_l = sum G_i T_i
+  level_sums<L, 3>(
+      k,
+      [&](int i) {
+        const int l = i / 3, m = i % 3;
+        return (m == 0 ? G0[l] : m == 1 ? G1[l] : G2[l]) * T[l];
+      },
+      nl, lane);
   // ---- coarse-to-fine Gauss-Newton (eqs. 4-5) ------------------------------
   float tx = ldexpf(ix, 1 - nl), ty = ldexpf(iy, 1 - nl), th = ith;
+  float cs = __cosf(th), sn = __sinf(th);
+  const bool odd = lane & 1;
+  // lane l: positions whose samples lie in level l's window (and so in the image)
+  float vlox, vhix, vloy, vhiy;
+  const auto bounds = [&] {
+    const int lv = lane & 7;
+    vlox = (float)max(wd.x, 0);
+    vhix = (float)min(wd.x + kWinW - 2, (dst_w >> lv) - 1);
+    vloy = (float)max(wd.y, 0);
+    vhiy = (float)min(wd.y + kWinH - 2, (dst_h >> lv) - 1);
+  };
+  bounds();
 #pragma unroll
   for (int l = L - 1; l >= 0; --l) {
     if (l >= nl) continue;
@@ -312,34 +512,78 @@ __device__ __forceinline__ PassOut klt_pass(const CamDesc& csrc_in, int ssrc_in,
       o.status = VIO_LOST_DEGENERATE;
       return o;
     }
-    const Level D = level_of(cdst, sdst, l);
-    for (int it = 0; it < N; ++it) {
-      const float cs = __cosf(th), sn = __sinf(th);
+    // a position that has moved away from its window's middle (a stereo match
+    // from the disparity prior, usually) takes a new one
+    const float wxf = (float)lane_of(wd.x, l), wyf = (float)lane_of(wd.y, l);
+    if (!wave_all((tx - 6.f >= wxf) & (tx - (kWinW - 8.f) <= wxf) & (ty - 6.f >= wyf) & (ty - (kWinH - 8.f) <= wyf))) {
+      const Level D = level_of(cdst, sdst, l);
+      const Windows q = window_around(D.w, D.h, tx, ty);
+      const int x = uniform(q.x), y = uniform(q.y);
+      if ((x != lane_of(wd.x, l)) | (y != lane_of(wd.y, l))) {
+        wd.x = (lane & 7) == l ? x : wd.x;
+        wd.y = (lane & 7) == l ? y : wd.y;
+        bounds();
+        window_load(D.p, D.w, D.h, x, y, dw + kWinWords * l, window_task(lane));
+        window_wait();
+      }
+    }
+    const float lox = lane_of(vlox, l), hix = lane_of(vhix, l), loy = lane_of(vloy, l), hiy = lane_of(vhiy, l);
+    const uint32_t base = dbase + kWinBytes * l;
+    const int first = lane_of(wd.y, l) * kWinW + lane_of(wd.x, l);
+    // the first exchange stage of the sums of (w, G0, G1, G2) I' selects between
+    // neighbouring lanes' products: the gains are selected instead, once
+    const float keep0 = odd ? G0[l] : wgt, send0 = odd ? wgt : G0[l];
+    const float keep1 = odd ? G2[l] : G1[l], send1 = odd ? G1[l] : G2[l];
+    uint32_t mw_min = 0xFFFFFFFFu;  // the smallest mean's bits (a mean of pixels is never negative)
+    float Iw = 0.f, imw = 0.f;
+    int n_it = N;
+    // one block but for two rare sides: a taken branch costs as much as several
+    // instructions here, so a track that leaves the image ends its level by the
+    // trip count and the residual is taken after the loop
+#pragma unroll 1
+    for (int it = 0; it < n_it; ++it) {
       const float wx = (cs * u - sn * v) + tx, wy = (sn * u + cs * v) + ty;
-      if (wave_any(!in_dom(D, wx, wy))) {
-        o.status = VIO_LOST_OOB;
-        return o;
+      // (the vote below runs while these reads are on their way)
+      Iw = bilinear_win(base, first, wx, wy);
+      if (__builtin_expect(!wave_all((wx >= lox) & (wx <= hix) & (wy >= loy) & (wy <= hiy)), 0)) {
+        const Level far = level_of(cdst, sdst, l);
+        if (wave_all(in_dom(far, wx, wy))) {
+          Iw = bilinear(far, wx, wy);
+        } else {
+          n_it = 0;
+          mw_min = 0u;
+        }
       }
-      const float Iw = bilinear(D, wx, wy);
-      float S[4] = {wgt * Iw, G0[l] * Iw, G1[l] * Iw, G2[l] * Iw};
-      wave_sums<4>(S, lane);
-      const float mw = S[0] * (1.f / 52.f);
-      if (!(mw > 0.f)) {
-        o.status = VIO_LOST_OOB;
-        return o;
-      }
-      const float imw = rcp(mw);
-      if (l == 0 && it == N - 1) {
-        const float e = Iw * imw - T[l];
-        o.resid = sqrtf(wave_sum(wgt * e * e, lane) * (1.f / 52.f));
-      }
-      const float d0 = k[3 * l + 0] - S[1] * imw, d1 = k[3 * l + 1] - S[2] * imw, d2 = k[3 * l + 2] - S[3] * imw;
+      const float a0 = keep0 * Iw, b0 = send0 * Iw, a1 = keep1 * Iw, b1 = send1 * Iw;
+      float S4[4];
+      wave_sums4_paired(a0, b0, a1, b1, S4, lane);
+      const float mw = S4[0] * (1.f / 52.f);
+      mw_min = min(mw_min, __float_as_uint(mw));
+      imw = rcp(mw);
+      const float d0 = k[3 * l + 0] - S4[1] * imw, d1 = k[3 * l + 1] - S4[2] * imw, d2 = k[3 * l + 2] - S4[3] * imw;
+      // the next iteration's sine and cosine need only d2: they run beside the
+      // exponential below
+      const float thn = th + d2;
+      float csn = __cosf(thn), snn = __sinf(thn);
+      asm("" : "+v"(csn), "+v"(snn));  // (keeps them ahead of the branch below)
       float a, b;
-      se2_v(d2, a, b);
+      se2_v(d2, wave_all(fabsf(d2) < 0.25f), a, b);
       const float vx = a * d0 - b * d1, vy = b * d0 + a * d1;
       tx = tx + (cs * vx - sn * vy);
       ty = ty + (sn * vx + cs * vy);
-      th = th + d2;
+      th = thn;
+      cs = csn;
+      sn = snn;
+    }
+    // a sample outside the image, or a mean that was not positive, ends the
+    // track (its later steps were not used)
+    if (mw_min == 0u) {
+      o.status = VIO_LOST_OOB;
+      return o;
+    }
+    if (l == 0) {
+      const float e = Iw * imw - T[l];
+      o.resid = sqrtf(wave_sum(wgt * e * e, lane) * (1.f / 52.f));
     }
   }
   o.tx = tx;
@@ -456,7 +700,7 @@ __device__ __forceinline__ bool model_start(const Model& s, const Model& d, cons
 template <int L>
 __device__ __forceinline__ TrackRes track_fb(const CamDesc& csrc, int ssrc, const CamDesc& cdst, int sdst, float px,
                                              float py, float ix, float iy, float ith, int nl, int N, float fb_thr,
-                                             float u, float v, float wgt, int lane) {
+                                             float u, float v, float wgt, int lane, lds_words win) {
   TrackRes r;
   r.x = ix;
   r.y = iy;
@@ -469,9 +713,15 @@ __device__ __forceinline__ TrackRes track_fb(const CamDesc& csrc, int ssrc, cons
   const CamDesc* B = &cdst;
   int sa = ssrc, sb = sdst;
   float qx = px, qy = py, gx = ix, gy = iy, gth = ith;
+  Windows wa{}, wb{};
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {
-    const PassOut o = klt_pass<L>(*A, sa, *B, sb, qx, qy, gx, gy, gth, nl, N, u, v, wgt, lane);
+    // the backward pass reads the forward one's windows, each in the other role
+    const PassOut o = klt_pass<L>(*A, sa, *B, sb, qx, qy, gx, gy, gth, nl, N, u, v, wgt, lane, pass == 0,
+                                  win + pass * (L * kWinWords), wa, win + (1 - pass) * (L * kWinWords), wb);
+    const Windows wt = wa;
+    wa = wb;
+    wb = wt;
     if (o.status != VIO_TRACKED) {
       r.status = o.status;
       break;
@@ -863,29 +1113,37 @@ __device__ __forceinline__ Plan plan_item(const CamDesc* __restrict__ cams, cons
   return pl;
 }
 
-// One work item per wave.
+// One work item per wave. Its plan parks in the wave's LDS (every lane writes the
+// same values) and is read back where an attempt starts, so it does not hold
+// registers through the tracking.
 template <int L, bool F>
 __device__ __forceinline__ void process_item(const CamDesc* __restrict__ cams, const FrameTable* __restrict__ frame,
                                              const Counters* __restrict__ cnt, const TrackSeg* __restrict__ segs,
                                              int n_segs, const Prediction* __restrict__ pred, const Tuning& tune,
-                                             int item, int lane, float u, float v, float wgt, uint16_t* sx) {
-  const Plan pl = plan_item<F, kW>(cams, frame, cnt, segs, n_segs, pred, tune, item, true, lane, sx);
-  if (!pl.out) return;
+                                             int item, int lane, float u, float v, float wgt, uint16_t* sx,
+                                             lds_words win, Plan* sp) {
+  {
+    const Plan pl = plan_item<F, kW>(cams, frame, cnt, segs, n_segs, pred, tune, item, true, lane, sx);
+    if (!pl.out) return;
+    *sp = pl;
+    wave_sync_lds();
+  }
   TrackRes r;
-  int fell_back = pl.pad0;
+  int fell_back = sp->pad0;
+  const int last = sp->last;
 #pragma unroll 1
-  for (int a = pl.first; a <= pl.last; ++a) {
+  for (int a = sp->first; a <= last; ++a) {
     const bool short_run = a == 0;
-    r = track_fb<L>(*pl.src, pl.ssrc, *pl.dst, pl.sdst, pl.px, pl.py, short_run ? pl.gx : pl.ix,
-                    short_run ? pl.gy : pl.iy, short_run ? pl.gth : pl.ith, short_run ? pl.sl : pl.fl,
-                    short_run ? pl.si : pl.fi, tune.fb_threshold, u, v, wgt, lane);
+    r = track_fb<L>(*sp->src, sp->ssrc, *sp->dst, sp->sdst, sp->px, sp->py, short_run ? sp->gx : sp->ix,
+                    short_run ? sp->gy : sp->iy, short_run ? sp->gth : sp->ith, short_run ? sp->sl : sp->fl,
+                    short_run ? sp->si : sp->fi, tune.fb_threshold, u, v, wgt, lane, win);
     if (short_run) {
-      if (r.status == VIO_TRACKED && r.resid <= pl.srho) break;
+      if (r.status == VIO_TRACKED && r.resid <= sp->srho) break;
       fell_back = 1;
     }
   }
   r.pad[0] = fell_back;
-  store_result(pl.out, r, lane);
+  store_result(sp->out, r, lane);
 }
 
 // ---- two keypoints per wave -------------------------------------------------
@@ -949,7 +1207,8 @@ __device__ __forceinline__ PassOut klt_pass2(const CamDesc& csrc_in, int ssrc_in
       fits[l] = half_all(in, lane) && live;
       if (fits[l]) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) template_samples(S, sx[q], sy[q], I0[l][q], gxr[l][q], gyr[l][q]);
+        for (int q = 0; q < 2; ++q)
+          template_samples(template_load(S, sx[q], sy[q]), fract(sx[q]), fract(sy[q]), I0[l][q], gxr[l][q], gyr[l][q]);
       }
     }
   }
@@ -1076,7 +1335,7 @@ __device__ __forceinline__ PassOut klt_pass2(const CamDesc& csrc_in, int ssrc_in
       }
       const float d0 = k[3 * l + 0] - S[1] * imw, d1 = k[3 * l + 1] - S[2] * imw, d2 = k[3 * l + 2] - S[3] * imw;
       float a, b;
-      se2_v(d2, a, b);
+      se2_v(d2, fabsf(d2) < 0.25f, a, b);
       const float vx = a * d0 - b * d1, vy = b * d0 + a * d1;
       const float ntx = tx + (cs * vx - sn * vy);
       const float nty = ty + (sn * vx + cs * vy);
@@ -1251,6 +1510,8 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track(const CamDesc* __rest
   // registers, loaded through the scalar cache)
   const int k = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (int)(blockDim.x / kW) + (int)(threadIdx.x / kW));
   if (k >= n_items) return;
+  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L>];
+  __shared__ Plan sPlan[kTrackWaves];
   uint16_t* sx = nullptr;
   if constexpr (F) {
     __shared__ __align__(16) uint16_t sLearn[kTrackWaves][MI + MH];
@@ -1258,7 +1519,9 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track(const CamDesc* __rest
   }
   float u, v, wgt;
   pattern_of(lane, u, v, wgt);
-  process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx);
+  process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx,
+                     (lds_words)sWin + uniform((int)threadIdx.x / kW) * (2 * L * kWinWords),
+                     &sPlan[uniform((int)threadIdx.x / kW)]);
 }
 
 // Persistent grid: every wave pops items from the frame's queue counter until
@@ -1275,6 +1538,8 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamD
                                                                      const Prediction* __restrict__ pred,
                                                                      Tuning tune, int queue) {
   const int lane = threadIdx.x & (kW - 1);
+  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L>];
+  __shared__ Plan sPlan[kTrackWaves];
   uint16_t* sx = nullptr;
   if constexpr (F) {
     __shared__ __align__(16) uint16_t sLearn[kTrackWaves][MI + MH];
@@ -1285,7 +1550,10 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamD
   for (;;) {
     const int k = __builtin_amdgcn_readfirstlane(atomicAdd(&frame->queue_head[queue], lane == 0 ? 1 : 0));
     if (k >= n_items) break;
-    process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx);
+    process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx,
+                       (lds_words)sWin + uniform((int)threadIdx.x / kW) * (2 * L * kWinWords),
+                     &sPlan[uniform((int)threadIdx.x / kW)]);
+    wave_sync_lds();  // the next item's plan overwrites this one's
   }
 }
 

@@ -76,6 +76,21 @@ __device__ __forceinline__ void wave_sums_pow2(float* v, int lane) {
   for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
 }
 
+// wave_sums_pow2<4> of values whose first exchange stage is already selected: for
+// the pair (v0, v1), keep0 is the member the lane's bit 0 keeps and send0 the
+// other; likewise (v2, v3).
+__device__ __forceinline__ void wave_sums4_paired(float keep0, float send0, float keep1, float send1, float* out,
+                                                  int lane) {
+  float w[2] = {keep0 + dpp<0xB1>(send0), keep1 + dpp<0xB1>(send1)};
+  xstage<0x4E, 1, 2>(w, lane);
+  xstage<0x124, 2, 1>(w, lane);
+  xstage<0x128, 3, 1>(w, lane);
+  const float x = rowswap_sum16(rowswap_sum32(w[0]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    out[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
+}
+
 // v[i] <- wave sum of v[i] for i < M, in chunks of 16, 8, 4, 2, 1
 template <int M>
 __device__ __forceinline__ void wave_sums(float* v, int lane) {
@@ -83,6 +98,22 @@ __device__ __forceinline__ void wave_sums(float* v, int lane) {
     constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
     wave_sums_pow2<C>(v, lane);
     wave_sums<M - C>(v + C, lane);
+  }
+}
+
+// out[i] <- wave sum of gen(i) for i in [OFF, OFF + M), chunked and summed as
+// wave_sums<M>, each chunk's values made just before its stages.
+template <int M, int OFF, class Gen>
+__device__ __forceinline__ void wave_sums_of(float* out, const Gen& gen, int lane) {
+  if constexpr (M > 0) {
+    constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
+    float w[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) w[i] = gen(OFF + i);
+    wave_sums_pow2<C>(w, lane);
+#pragma unroll
+    for (int i = 0; i < C; ++i) out[OFF + i] = w[i];
+    wave_sums_of<M - C, OFF + C>(out, gen, lane);
   }
 }
 
