@@ -166,7 +166,10 @@ typedef struct vio_frontend_params {
    * stream waits for a count the pyramid stream writes (stream value
    * operations: the least host time per frame). VIO_PYRAMID_EVENT (1): the
    * same with an event record and wait. VIO_PYRAMID_SAME_STREAM (2): on the
-   * launch stream, in order (no cross-stream dependency). */
+   * launch stream, in order (no cross-stream dependency). A frame that is pushed
+   * or stepped (and so waited for) with none in flight runs in order on one
+   * stream in any case, unless the learned stage's own launch runs beside its
+   * pyramid. */
   int32_t pyramid_stream;
   /* Launch choice that never changes the records: keypoints per tracking
    * wavefront. 1 (or 0): one wave64 per keypoint, a lane per pattern point
@@ -189,10 +192,11 @@ typedef struct vio_frontend_params {
 #define VIO_TOPOLOGY_STAR 1
 
 /* vio_frontend_params.flags */
-#define VIO_FLAG_EAGER 1u /* launch the per-frame kernels one by one, each with dispatch timestamps, instead
-                             of replaying a captured hipGraph */
-#define VIO_FLAG_PLAIN 2u /* launch the per-frame kernels one by one without timestamps (fewer host calls
-                             than a graph launch for small frames); excludes VIO_FLAG_EAGER */
+#define VIO_FLAG_EAGER 1u /* launch the per-frame kernels one by one, each with dispatch timestamps (without
+                             it the batched step replays a captured hipGraph, and a pushed frame's kernels
+                             are launched one by one) */
+#define VIO_FLAG_PLAIN 2u /* launch the kernels one by one without timestamps (fewer host calls than a
+                             graph launch for small frames); excludes VIO_FLAG_EAGER */
 
 /* Output record: one per previous keypoint of each camera (tracked or lost) and
  * one per new detection / stereo match, sorted by (camera, id). */

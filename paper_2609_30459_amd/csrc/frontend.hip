@@ -6,9 +6,10 @@
 // pyramid stream runs the pyramid+detector kernel (which copies the table to
 // the device and, for a host push, reads the staged images); the launch
 // stream runs the learned stage, then, once the pyramid stream's signal says
-// the pyramid is done, the tracker and the selection. The selection writes
-// the records into mapped pinned host memory, so nothing is copied back; the
-// host fences on an event after the selection.
+// the pyramid is done, the tracker and the selection. A frame that is waited for
+// at once with none in flight runs on one stream: nothing else would use the
+// other. The selection writes the records into mapped pinned host memory, so
+// nothing is copied back; the host fences on an event after the selection.
 //
 // Per camera the arena holds: pyramid levels and per-cell winner keys by
 // pyramid slot, keypoint state by frame parity, temporal and stereo results.
@@ -40,11 +41,10 @@ static_assert(kMaxCellsAbi * kMaxPerCell <= 65536, "the selection kernel keeps k
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Captured submit of a launch set: the whole frame as one graph.
-// Captured launches of one submission slot: the learned stage (features and
-// network) and the tracking part (tracker and selection) of a frame. The
-// frame-table copy and the pyramid/detector run as plain launches on the
-// pyramid stream (a captured copy-and-kernel graph launched slower).
+// Captured launches of one submission slot of the batched step: the learned
+// stage (features and network) and the tracking part (tracker and selection).
+// The pyramid/detector runs as a plain launch on the pyramid stream (a captured
+// copy-and-kernel graph launched slower).
 struct Graphs {
   hipGraphExec_t learn = nullptr, trk = nullptr;
   bool captured = false;
@@ -69,7 +69,8 @@ struct StreamInfo {
   bool staged = false;     // a frame is staged for the next vio_frontend_step
   int64_t staged_t = 0;
   size_t rec_off = 0, rec_n = 0;  // record range (in vio_track units) of the stream's cameras
-  Graphs graph[kInFlight];         // captured per-frame submit by submission slot, replayed every frame
+  size_t l0_stride = 0;    // bytes from one camera's level 0 to the next one's (device and staging)
+  size_t stage_off = 0;    // the stream's place in a staging slot
   // camera-model start for the next frame (vio_frontend_set_motion)
   std::vector<vio_camera_motion> motion;  // at most one per camera
   std::vector<vio_kp_depth> depths;       // sorted by (camera, id)
@@ -158,6 +159,7 @@ struct vio_frontend {
   KpDepth* h_depth = nullptr;    // [slot][pred_cap]
   hipStream_t stream = nullptr;   // the launch stream: learned stage, tracking, selection
   hipStream_t pstream = nullptr;  // frame-table copies and pyramids/detections
+  bool staged_uploads = false;    // images of a staged frame were queued on pstream since its last pyramid
   hipEvent_t ev_pyr[kInFlight] = {}, ev_in = nullptr;  // per slot: pyramid done; a caller stream's images ready
   // the pyramid stream's completion count in signal memory (stream value
   // operations; null: events ev_pyr instead)
@@ -336,8 +338,6 @@ void vio_frontend_destroy(vio_frontend* h) {
   if (!h) return;
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   if (h->pstream) (void)hipStreamSynchronize(h->pstream);
-  for (auto& si : h->streams)
-    for (Graphs& g : si.graph) g.destroy();
   for (Graphs& g : h->graph_all) g.destroy();
   if (h->arena) {
     if (h->P.dev_free) h->P.dev_free(h->arena, h->P.alloc_ctx);
@@ -425,7 +425,7 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
         c.pitch[l] = level_pitch(si.w >> l);
         // one guard row: the tracker's template window reads up to one row and
         // one column past a level (with weight 0)
-        for (int ps = 0; ps < kPyrSlots; ++ps)
+        for (int ps = 0; ps < kPyrSlots && l > 0; ++ps)
           co[cam].lvl[ps][l] = take((size_t)c.pitch[l] * (size_t)((si.h >> l) + 1));
       }
       for (int par = 0; par < 2; ++par) co[cam].state[par] = take(sizeof(Kp) * si.cap);
@@ -443,7 +443,15 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
       rows_total += si.cap;
       co[cam].rec = rec_total;
       rec_total += c.rec_cap;
-      stage += (size_t)si.w * si.h;
+    }
+    // level 0 of the stream's cameras, one after the other in each pyramid slot:
+    // staged host images have the same layout, so they go up in linear copies
+    si.l0_stride = round_up((size_t)level_pitch(si.w) * (size_t)(si.h + 1), kAlign);
+    si.stage_off = stage;
+    stage += si.l0_stride * si.n_cams;
+    for (int ps = 0; ps < kPyrSlots; ++ps) {
+      const size_t o = take(si.l0_stride * si.n_cams);
+      for (int k = 0; k < si.n_cams; ++k) co[si.first_cam + k].lvl[ps][0] = o + k * si.l0_stride;
     }
     // tracking work items: stereo matches of the left cameras' cell winners
     // (one per key slot) first (they run the full budget), then the temporal
@@ -791,17 +799,21 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
 // and the selection. The pyramid slots rotate over kPyrSlots frames, so the
 // pyramids of the later frames in flight can run beside this frame's
 // tracking.
-static hipError_t enqueue_pyr_part(vio_frontend* h, const LaunchSet& ls, int slot, bool timed, hipStream_t st) {
+//
+// ps: the frame's pyramid stream; the launch stream st itself for a frame that
+// runs on one stream (stream order then suffices).
+static hipError_t enqueue_pyr_part(vio_frontend* h, const LaunchSet& ls, int slot, bool timed, hipStream_t ps,
+                                   hipStream_t st) {
   hipError_t e;
-  if ((e = enqueue_stage(h, ls, h->pstream, 1, timed))) return e;
-  if (h->pstream == st) return hipSuccess;  // the launch stream itself: stream order suffices
+  if ((e = enqueue_stage(h, ls, ps, 1, timed))) return e;
+  if (ps == st) return hipSuccess;
   if (h->pyr_sig) return hipStreamWriteValue32(h->pstream, h->pyr_sig, ++h->pyr_epoch, 0);
   return hipEventRecord(h->ev_pyr[slot], h->pstream);
 }
 
 // The launch stream waits for the pyramid part of the frame just enqueued.
-static hipError_t wait_pyr_part(vio_frontend* h, hipStream_t st, int slot) {
-  if (h->pstream == st) return hipSuccess;
+static hipError_t wait_pyr_part(vio_frontend* h, hipStream_t ps, hipStream_t st, int slot) {
+  if (ps == st) return hipSuccess;
   if (h->pyr_sig) return hipStreamWaitValue32(st, h->pyr_sig, h->pyr_epoch, hipStreamWaitValueGte, 0xFFFFFFFFu);
   return hipStreamWaitEvent(st, h->ev_pyr[slot], 0);
 }
@@ -844,9 +856,10 @@ static int complete_all(vio_frontend* h);
 // Submits one frame of a launch set whose inputs are in the current slot's
 // frame table (h_frame) without waiting: the slot's captured graph, or eager
 // launches with per-kernel timing. The next slot becomes the staging slot.
-// At most two submissions are outstanding; eager ones are completed before
-// the next submission (their kernel timing events are shared).
-static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStream_t st) {
+// Eager submissions are completed before the next one (their kernel timing
+// events are shared). gr == nullptr: direct launches. one_stream: the frame's
+// pyramid runs on st too.
+static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStream_t st, bool one_stream) {
   if (h->n_pend == kInFlight) return fail(h, VIO_ESTATE, "%d frames in flight: call vio_frontend_wait first", kInFlight);
   if (h->pyr_sig && h->pyr_epoch >= 0x80000000u) {
     // long before the 32-bit count could wrap: drain, then restart it at zero
@@ -859,31 +872,33 @@ static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStrea
   const int slot = (int)(h->sub % kInFlight);
   h->d_frame = h->d_frames[slot];
   h->hm_frame = h->hm_frames[slot];
-  ensure_graph(h, ls, &gr[slot]);
-  const bool graphed = gr[slot].any();
+  if (gr) ensure_graph(h, ls, &gr[slot]);
+  const bool graphed = gr && gr[slot].any();
   // eager launches time each kernel with shared events: one frame at a time
-  const bool timed = !graphed && !h->plain;
+  const bool timed = h->eager;
+  const hipStream_t ps = one_stream ? st : h->pstream;
   if (timed && h->n_pend > 0) {
     const int rc = complete_all(h);
     if (rc != VIO_OK) return rc;
   }
   if (timed)
     for (bool& r : h->kran) r = false;
-  if (st != h->stream) {
+  if (st != h->stream && ps != st) {
     // a caller's stream: the pyramid reads images produced there
     HIP_CHECK(h, hipEventRecord(h->ev_in, st));
-    HIP_CHECK(h, hipStreamWaitEvent(h->pstream, h->ev_in, 0));
+    HIP_CHECK(h, hipStreamWaitEvent(ps, h->ev_in, 0));
   }
   // the frame's start timestamp (last_gpu_ms), not taken with plain launches
-  if (!h->plain) HIP_CHECK(h, hipEventRecord(h->ev[slot][0], h->pstream));
-  HIP_CHECK(h, enqueue_pyr_part(h, ls, slot, timed, st));
+  if (!h->plain) HIP_CHECK(h, hipEventRecord(h->ev[slot][0], ps));
+  HIP_CHECK(h, enqueue_pyr_part(h, ls, slot, timed, ps, st));
+  if (ps == h->pstream) h->staged_uploads = false;
   if (h->learned && !h->P.learned_fused) {
     // the learned stage's inputs are the previous frame's (ordered before it
     // on this stream) and the pinned frame table: it starts at once
     if (graphed) HIP_CHECK(h, hipGraphLaunch(gr[slot].learn, st));
     else HIP_CHECK(h, enqueue_stage(h, ls, st, 4, timed));
   }
-  HIP_CHECK(h, wait_pyr_part(h, st, slot));
+  HIP_CHECK(h, wait_pyr_part(h, ps, st, slot));
   if (graphed) HIP_CHECK(h, hipGraphLaunch(gr[slot].trk, st));
   else HIP_CHECK(h, enqueue_track_part(h, ls, st, timed));
   HIP_CHECK(h, hipEventRecord(h->ev[slot][1], st));
@@ -958,18 +973,24 @@ static int complete_all(vio_frontend* h) {
   return VIO_OK;
 }
 
-// Runs one frame of a launch set and waits for it (and for anything submitted
-// before it).
-static int run_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStream_t st) {
-  int rc = complete_all(h);
-  if (rc == VIO_OK) rc = submit_set(h, ls, gr, st);
-  if (rc == VIO_OK) rc = complete_all(h);
-  return rc;
+// Whether a frame that is waited for at once, with none in flight, runs on one
+// stream: the pyramid stream's signal and the launch stream's wait for it cost
+// two small kernels and nothing runs beside them (mono 320x240 73 -> 67 us,
+// stereo 752x480 83 -> 78 us a frame). With the learned stage in its own launch
+// that stage does run beside the pyramid; and images queued on the pyramid stream
+// by a staging call are read behind them there.
+static bool one_stream(const vio_frontend* h) {
+  return !(h->learned && !h->P.learned_fused) && !h->staged_uploads;
 }
 
-// Runs one frame of stream s whose level-0 sources are already in h_frame.
-static int run_frame(vio_frontend* h, int s, hipStream_t st) {
-  return run_set(h, stream_set(h, s), h->streams[s].graph, st);
+// Runs one frame of stream s whose level-0 sources are already in h_frame (or
+// queued on st's order) and waits for it; nothing is in flight. Its three
+// launches are made directly: replaying a captured graph costs the host more
+// (mono 320x240 67 -> 56 us a frame).
+static int run_frame(vio_frontend* h, int s, hipStream_t st, bool single) {
+  int rc = submit_set(h, stream_set(h, s), nullptr, st, single);
+  if (rc == VIO_OK) rc = complete_all(h);
+  return rc;
 }
 
 static int check_push(vio_frontend* h, int32_t s, int64_t t_ns) {
@@ -1045,31 +1066,34 @@ static void fill_frame(vio_frontend* h, int s) {
   fill_stream(h, s);
 }
 
-static size_t stage_offset(const vio_frontend* h, int s) {
-  size_t so = 0;
-  for (int k = 0; k < h->streams[s].first_cam; ++k) so += (size_t)h->cams[k].w * h->cams[k].h;
-  return so;
-}
-
 // Copies host images of stream s into pinned staging and queues their upload
-// into the current pyramid slot's level 0.
-static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* images, const int32_t* strides) {
+// on `st` into the current pyramid slot's level 0: rows at the level's pitch, so
+// that the upload is a linear copy (a two-dimensional one of 641-byte rows took
+// 3.4 ms, row by row, against 14 us), one for all cameras of small frames, one per
+// camera beside the next one's staging for larger ones.
+constexpr size_t kUploadSplit = 1 << 20;  // bytes of a frame from which its cameras go up one by one
+static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* images, const int32_t* strides,
+                              hipStream_t st) {
   const StreamInfo& si = h->streams[s];
   const int ps = (int)(si.frames % kPyrSlots);
-  size_t so = stage_offset(h, s);
+  uint8_t* stg = h->h_stage + (h->sub % kInFlight) * h->stage_bytes + si.stage_off;
+  uint8_t* dst = h->cams[si.first_cam].lvl[ps][0];
+  const size_t pitch = (size_t)h->cams[si.first_cam].pitch[0], bytes = pitch * si.h;
+  const bool split = si.l0_stride * si.n_cams >= kUploadSplit;
   for (int k = 0; k < si.n_cams; ++k) {
-    const int c = si.first_cam + k;
-    const CamDesc& cd = h->cams[c];
-    uint8_t* stg = h->h_stage + (h->sub % kInFlight) * h->stage_bytes + so;
-    for (int y = 0; y < si.h; ++y) std::memcpy(stg + (size_t)y * si.w, images[k] + (size_t)y * strides[k], si.w);
-    HIP_CHECK(h, hipMemcpy2DAsync(cd.lvl[ps][0], cd.pitch[0], stg, si.w, si.w, si.h, hipMemcpyHostToDevice,
-                                  h->pstream));
-    FrameCam& f = h->h_frame->cam[c];
+    const CamDesc& cd = h->cams[si.first_cam + k];
+    uint8_t* to = stg + k * si.l0_stride;
+    if ((size_t)strides[k] == pitch && (size_t)si.w == pitch) std::memcpy(to, images[k], bytes);
+    else
+      for (int y = 0; y < si.h; ++y) std::memcpy(to + (size_t)y * pitch, images[k] + (size_t)y * strides[k], si.w);
+    if (split) HIP_CHECK(h, hipMemcpyAsync(dst + k * si.l0_stride, to, bytes, hipMemcpyHostToDevice, st));
+    FrameCam& f = h->h_frame->cam[si.first_cam + k];
     f.src = cd.lvl[ps][0];
     f.src_pitch = cd.pitch[0];
     f.copy_l0 = 0;
-    so += (size_t)si.w * si.h;
   }
+  if (!split)
+    HIP_CHECK(h, hipMemcpyAsync(dst, stg, si.l0_stride * (si.n_cams - 1) + bytes, hipMemcpyHostToDevice, st));
   return VIO_OK;
 }
 
@@ -1112,9 +1136,11 @@ int vio_frontend_push_stereo_frame(vio_frontend* h, int32_t s, int64_t t_ns, con
   if (rc != VIO_OK) return rc;
   rc = stage_motion(h, s, h->stream);
   if (rc != VIO_OK) return rc;
-  rc = upload_host_images(h, s, images, strides);
+  const bool single = one_stream(h);
+  rc = upload_host_images(h, s, images, strides, single ? h->stream : h->pstream);
+  if (rc == VIO_OK) rc = complete_all(h);
   if (rc != VIO_OK) return rc;
-  rc = run_frame(h, s, h->stream);
+  rc = run_frame(h, s, h->stream, single);
   if (rc != VIO_OK) return rc;
   si.last_t = t_ns;
   return VIO_OK;
@@ -1136,9 +1162,11 @@ int vio_frontend_push_stereo_frame_device(vio_frontend* h, int32_t s, int64_t t_
     f.copy_l0 = 1;
   }
   hipStream_t st = hip_stream ? static_cast<hipStream_t>(hip_stream) : h->stream;
-  rc = stage_motion(h, s, st);
+  // (first: the frames in flight read the depths that stage_motion replaces)
+  rc = complete_all(h);
+  if (rc == VIO_OK) rc = stage_motion(h, s, st);
   if (rc != VIO_OK) return rc;
-  rc = run_frame(h, s, st);
+  rc = run_frame(h, s, st, one_stream(h));
   if (rc != VIO_OK) return rc;
   si.last_t = t_ns;
   return VIO_OK;
@@ -1153,8 +1181,9 @@ int vio_frontend_stage_frame(vio_frontend* h, int32_t s, int64_t t_ns, const uin
   for (int k = 0; k < si.n_cams; ++k)
     if (!images[k] || strides[k] < si.w) return fail(h, VIO_EINVAL, "camera %d: null image or stride < width", k);
   fill_stream(h, s);
-  rc = upload_host_images(h, s, images, strides);
+  rc = upload_host_images(h, s, images, strides, h->pstream);
   if (rc != VIO_OK) return rc;
+  h->staged_uploads = true;
   rc = stage_motion(h, s, h->stream);
   if (rc != VIO_OK) return rc;
   si.staged = true;
@@ -1197,8 +1226,9 @@ int vio_frontend_stage_frames_device(vio_frontend* h, int32_t n, const int32_t* 
   return VIO_OK;
 }
 
-// Submits every staged stream's frame as one batched launch set.
-static int submit_staged(vio_frontend* h) {
+// Submits every staged stream's frame as one batched launch set (waited: the
+// caller waits for it at once).
+static int submit_staged(vio_frontend* h, bool waited) {
   if (!h) return VIO_EINVAL;
   if (h->poisoned) return VIO_EDEVICE;
   if (h->learned && !h->mlp_ready) return fail(h, VIO_ESTATE, "learned init: call vio_frontend_set_mlp first");
@@ -1208,7 +1238,7 @@ static int submit_staged(vio_frontend* h) {
     for (int k = 0; k < si.n_cams; ++k) h->h_frame->cam[si.first_cam + k].active = si.staged ? 1 : 0;
   }
   if (!any) return fail(h, VIO_ESTATE, "no frame staged");
-  const int rc = submit_set(h, all_set(h), h->graph_all, h->stream);
+  const int rc = submit_set(h, all_set(h), h->graph_all, h->stream, waited && h->n_pend == 0 && one_stream(h));
   if (rc != VIO_OK) return rc;
   for (auto& si : h->streams)
     if (si.staged) {
@@ -1219,12 +1249,12 @@ static int submit_staged(vio_frontend* h) {
 }
 
 int vio_frontend_step(vio_frontend* h) {
-  int rc = submit_staged(h);
+  int rc = submit_staged(h, true);
   if (rc == VIO_OK) rc = complete_all(h);
   return rc;
 }
 
-int vio_frontend_step_async(vio_frontend* h) { return submit_staged(h); }
+int vio_frontend_step_async(vio_frontend* h) { return submit_staged(h, false); }
 
 int vio_frontend_wait(vio_frontend* h) {
   if (!h) return VIO_EINVAL;
@@ -1569,8 +1599,6 @@ int vio_frontend_set_mlp(vio_frontend* h, const float* params, int32_t n, float 
   HIP_CHECK(h, hipStreamSynchronize(h->stream));
   if (rho >= 0.f) h->P.learned_rho = rho;
   // the captured graphs hold the old threshold as a kernel argument
-  for (auto& si : h->streams)
-    for (Graphs& g : si.graph) g.destroy();
   for (Graphs& g : h->graph_all) g.destroy();
   h->mlp_ready = true;
   return VIO_OK;
