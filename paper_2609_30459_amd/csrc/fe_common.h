@@ -229,6 +229,9 @@ hipError_t launch_pyr_detect_range(const CamDesc* d_cams, const FrameTable* h_fr
                                    int copy_bytes, int cam_begin, int cam_end, int tile_base, int n_tiles, int levels,
                                    int tile, int tmin, int margin, hipStream_t s);
 size_t pyr_detect_lds_bytes(int levels, int tile);
+// Copies bytes (a multiple of 4, at most a few tens of MB) from mapped pinned
+// host memory at device address d_src to d_dst.
+hipError_t launch_upload(const void* d_src, void* d_dst, size_t bytes, hipStream_t s);
 // Tracking work items [item_base, item_base + n_items) over the segments
 // d_segs[0..n_segs) (segment begins are global item indices). waves_per_cu = 0
 // launches one wave per item; > 0 launches a persistent grid of that many

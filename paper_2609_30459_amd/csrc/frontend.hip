@@ -154,6 +154,7 @@ struct vio_frontend {
   int32_t* h_rec_count = nullptr; // [record slot][cameras]
   vio_track* h_rec = nullptr;     // [record slot][rec_total]
   uint8_t* h_stage = nullptr;     // [slot][stage_bytes]
+  uint8_t* hm_stage = nullptr;    // its device mapping
   size_t stage_bytes = 0;
   Prediction* h_pred = nullptr;  // [slot][pred_cap]
   KpDepth* h_depth = nullptr;    // [slot][pred_cap]
@@ -606,6 +607,7 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
   h->hm_frame = h->hm_frames[0];
   std::memset(h->h_rec_count, 0, sizeof(int32_t) * kRecSlots * n_cams);
   std::memset(h->h_camstats, 0, sizeof(int32_t) * kCamStats * kRecSlots * n_cams);
+  HIP_CHECK(h, hipHostGetDevicePointer((void**)&h->hm_stage, h->h_stage, 0));
   vio_track* rec_dev = nullptr;
   int32_t *cnt_dev = nullptr, *stats_dev = nullptr;
   HIP_CHECK(h, hipHostGetDevicePointer((void**)&rec_dev, h->h_rec, 0));
@@ -1069,14 +1071,16 @@ static void fill_frame(vio_frontend* h, int s) {
 // Copies host images of stream s into pinned staging and queues their upload
 // on `st` into the current pyramid slot's level 0: rows at the level's pitch, so
 // that the upload is a linear copy (a two-dimensional one of 641-byte rows took
-// 3.4 ms, row by row, against 14 us), one for all cameras of small frames, one per
-// camera beside the next one's staging for larger ones.
+// 3.4 ms, row by row, against 14 us): one kernel for all cameras of small frames,
+// one per camera beside the next one's staging for larger ones.
 constexpr size_t kUploadSplit = 1 << 20;  // bytes of a frame from which its cameras go up one by one
 static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* images, const int32_t* strides,
                               hipStream_t st) {
   const StreamInfo& si = h->streams[s];
   const int ps = (int)(si.frames % kPyrSlots);
-  uint8_t* stg = h->h_stage + (h->sub % kInFlight) * h->stage_bytes + si.stage_off;
+  const size_t at = (h->sub % kInFlight) * h->stage_bytes + si.stage_off;
+  uint8_t* stg = h->h_stage + at;
+  const uint8_t* from = h->hm_stage + at;
   uint8_t* dst = h->cams[si.first_cam].lvl[ps][0];
   const size_t pitch = (size_t)h->cams[si.first_cam].pitch[0], bytes = pitch * si.h;
   const bool split = si.l0_stride * si.n_cams >= kUploadSplit;
@@ -1086,14 +1090,14 @@ static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* imag
     if ((size_t)strides[k] == pitch && (size_t)si.w == pitch) std::memcpy(to, images[k], bytes);
     else
       for (int y = 0; y < si.h; ++y) std::memcpy(to + (size_t)y * pitch, images[k] + (size_t)y * strides[k], si.w);
-    if (split) HIP_CHECK(h, hipMemcpyAsync(dst + k * si.l0_stride, to, bytes, hipMemcpyHostToDevice, st));
+    if (split) HIP_CHECK(h, launch_upload(from + k * si.l0_stride, dst + k * si.l0_stride, bytes, st));
     FrameCam& f = h->h_frame->cam[si.first_cam + k];
     f.src = cd.lvl[ps][0];
     f.src_pitch = cd.pitch[0];
     f.copy_l0 = 0;
   }
   if (!split)
-    HIP_CHECK(h, hipMemcpyAsync(dst, stg, si.l0_stride * (si.n_cams - 1) + bytes, hipMemcpyHostToDevice, st));
+    HIP_CHECK(h, launch_upload(from, dst, si.l0_stride * (si.n_cams - 1) + bytes, st));
   return VIO_OK;
 }
 
