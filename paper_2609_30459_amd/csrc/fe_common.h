@@ -148,6 +148,30 @@ struct FrameTable {
   FrameCam cam[kMaxCams];
 };
 
+// The part of a frame's table that the pyramid and learned-stage kernels read, by
+// value in their arguments: the table itself is in pinned host memory until the
+// pyramid launch has copied it, and every workgroup that read it there waited some
+// microseconds for the host link (the pyramid of sixteen streams, 21,000
+// workgroups: 147 us against 99; of one 1280x720 pair 17.4 against 14.3). Entry i: camera `cam` of the i-th active camera
+// of the launch, whose workgroups begin at begin[i] (ascending).
+struct CamArg {
+  const uint8_t* src;
+  int32_t src_pitch;
+  uint8_t cam, pyr, pyr_prev, flags;
+};
+enum : uint8_t { kArgCopyL0 = 1, kArgHasPrev = 2, kArgParity = 4 };
+static_assert(kMaxCams <= 64, "a wave finds its entry with one load and a vote");
+struct LaunchCams {
+  int32_t n, blocks;  // entries, workgroups in all
+  int32_t begin[kMaxCams];
+  CamArg cam[kMaxCams];
+};
+// The entry of workgroup b (every lane of the wave active).
+__device__ __forceinline__ int launch_entry(const LaunchCams& a, int b) {
+  const int lane = (int)(threadIdx.x & 63);
+  return __popcll(__ballot(lane < a.n && a.begin[lane] <= b)) - 1;
+}
+
 // Per-camera counters, indexed [parity][camera]; rec_count[camera].
 struct Counters {
   int32_t n_live[2][kMaxCams];
@@ -219,15 +243,13 @@ struct Prediction {
 };
 
 // ---- launchers (defined in the kernel translation units) ----
-// Pyramid + detector over tiles [tile_base, tile_base + n_tiles) (at least
-// one) of cameras [cam_begin, cam_end); tile: the level-0 tile edge the
-// cameras' tile grids use (32 or 64). h_frame: the frame's table, mapped
-// pinned host memory, which the kernel reads and whose first copy_bytes (a
-// multiple of 4) its first workgroup copies to d_frame for the frame's later
-// kernels.
-hipError_t launch_pyr_detect_range(const CamDesc* d_cams, const FrameTable* h_frame, FrameTable* d_frame,
-                                   int copy_bytes, int cam_begin, int cam_end, int tile_base, int n_tiles, int levels,
-                                   int tile, int tmin, int margin, hipStream_t s);
+// Pyramid + detector over the tiles of args' cameras (tile: the level-0 tile edge
+// the cameras' tile grids use, 32 or 64). One more workgroup copies the first
+// copy_bytes (a multiple of 4) of h_frame, the frame's table in mapped pinned host
+// memory, to d_frame for the frame's later kernels.
+hipError_t launch_pyr_detect(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame,
+                             FrameTable* d_frame, int copy_bytes, int levels, int tile, int tmin, int margin,
+                             hipStream_t s);
 size_t pyr_detect_lds_bytes(int levels, int tile);
 // Copies bytes (a multiple of 4, at most a few tens of MB) from mapped pinned
 // host memory at device address d_src to d_dst.
@@ -249,11 +271,11 @@ hipError_t launch_track(const CamDesc* d_cams, FrameTable* d_frame, Counters* d_
                         int n_segs, int item_base, int n_items, const Prediction* d_pred, Tuning tune,
                         TrackShape shape, hipStream_t s);
 // Features (into d_feat) and network outputs (into d_guess) of the previous
-// keypoints of cameras [cam_begin, cam_end); h_cams: host copy of the
-// descriptors (caps).
-hipError_t launch_learn(const CamDesc* d_cams, const FrameTable* d_frame, const Counters* d_cnt, const CamDesc* h_cams,
-                        int cam_begin, int cam_end, const MlpDev& M, float* d_feat, float* d_guess, int waves,
-                        hipStream_t s);
+// keypoints of args' cameras, whose workgroups take `waves` keypoints each
+// (learn_blocks of them per camera).
+hipError_t launch_learn(const CamDesc* d_cams, const LaunchCams& args, const Counters* d_cnt, const MlpDev& M,
+                        float* d_feat, float* d_guess, int waves, hipStream_t s);
+constexpr int learn_blocks(int cap, int waves) { return (cap + waves - 1) / waves; }
 hipError_t mlp_forward_launch(const MlpDev& M, const float* X, int K, float* Y, hipStream_t s);
 hipError_t mlp_pack_launch(const MlpDev& M, hipStream_t s);
 // Selection phases: kSelectAll (speculative stereo: everything in one

@@ -41,20 +41,15 @@ static_assert(kMaxCellsAbi * kMaxPerCell <= 65536, "the selection kernel keeps k
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Captured launches of one submission slot of the batched step: the learned
-// stage (features and network) and the tracking part (tracker and selection).
-// The pyramid/detector runs as a plain launch on the pyramid stream (a captured
-// copy-and-kernel graph launched slower).
+// The captured tracking part (tracker and selection) of one submission slot of
+// the batched step. The pyramid/detector and the learned stage are plain launches:
+// their arguments hold the frame's inputs.
 struct Graphs {
-  hipGraphExec_t learn = nullptr, trk = nullptr;
-  bool captured = false;
-  bool any() const { return captured; }
+  hipGraphExec_t trk = nullptr;
+  bool any() const { return trk != nullptr; }
   void destroy() {
-    for (hipGraphExec_t* g : {&learn, &trk}) {
-      if (*g) (void)hipGraphExecDestroy(*g);
-      *g = nullptr;
-    }
-    captured = false;
+    if (trk) (void)hipGraphExecDestroy(trk);
+    trk = nullptr;
   }
 };
 
@@ -303,6 +298,23 @@ int check_params(const vio_frontend_params* p, std::string& why) {
   if (p->pyramid_stream < VIO_PYRAMID_SIGNAL || p->pyramid_stream > VIO_PYRAMID_SAME_STREAM)
     return why = "pyramid_stream must be VIO_PYRAMID_SIGNAL, _EVENT or _SAME_STREAM", VIO_EINVAL;
   return VIO_OK;
+}
+
+// The launch set's active cameras with their inputs from the frame's table and
+// blocks_of(camera) workgroups each.
+template <class BlocksOf>
+LaunchCams launch_cams(const vio_frontend* h, const LaunchSet& ls, const BlocksOf& blocks_of) {
+  LaunchCams a{};
+  for (int c = ls.cam_begin; c < ls.cam_end; ++c) {
+    const FrameCam& f = h->h_frame->cam[c];
+    if (!f.active) continue;
+    a.begin[a.n] = a.blocks;
+    a.blocks += blocks_of(h->cams[c]);
+    a.cam[a.n++] = CamArg{f.src, f.src_pitch, (uint8_t)c, (uint8_t)f.pyr, (uint8_t)f.pyr_prev,
+                          (uint8_t)((f.copy_l0 ? kArgCopyL0 : 0) | (f.has_prev ? kArgHasPrev : 0) |
+                                    (f.parity ? kArgParity : 0))};
+  }
+  return a;
 }
 
 }  // namespace
@@ -739,11 +751,11 @@ static hipError_t track_range(vio_frontend* h, const LaunchSet& ls, int seg_begi
                       st);
 }
 
-// Enqueues one step of a frame of the launch set on `st`: 0 = frame table
-// copy, 1 = pyramid+detector, 2 = tracker, 3 = selection (deferred stereo:
-// selection, stereo tracker, selection), 4 = learned mode's features and
-// network. Nothing enqueued changes between frames (per-frame inputs live in
-// the frame table), so the sequence can be captured once.
+// Enqueues one step of a frame of the launch set on `st`: 1 = pyramid+detector,
+// 2 = tracker, 3 = selection (deferred stereo: selection, stereo tracker,
+// selection), 4 = learned mode's features and network. What 2 and 3 enqueue does
+// not change between frames (per-frame inputs live in the frame table), so they
+// can be captured once.
 // `timed` attaches each kernel's start/stop events to its dispatch.
 static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_t st, int stage, bool timed) {
   const Tuning tune = tuning(h);
@@ -756,23 +768,19 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
   } reset;
   hipError_t e;
   if (stage == 1) {
-    // the pyramid kernel reads the frame's table from its pinned host slot and
-    // copies it to the device table the later kernels read
     timing(kKernPyr);
-    return launch_pyr_detect_range(h->d_cams, h->hm_frame, h->d_frame,
-                                   (int)(offsetof(FrameTable, cam) + sizeof(FrameCam) * h->cams.size()), ls.cam_begin,
-                                   ls.cam_end, ls.tile_begin, ls.n_tiles, tune.levels, h->tile, tune.tmin, tune.margin,
-                                   st);
+    return launch_pyr_detect(h->d_cams, launch_cams(h, ls, [&](const CamDesc& c) { return c.tiles_x * c.tiles_y; }),
+                             h->hm_frame, h->d_frame,
+                             (int)(offsetof(FrameTable, cam) + sizeof(FrameCam) * h->cams.size()), tune.levels,
+                             h->tile, tune.tmin, tune.margin, st);
   }
   if (stage == 4) {
     // the features of the previous keypoints and the network's guesses in one
     // launch; the tracker reads the guesses
     timing(kKernFeatures);
-    // (it runs beside the pyramid kernel, which copies the frame's table to
-    // the device: it reads the pinned host table)
-    return launch_learn(h->d_cams, h->hm_frame, h->d_cnt, h->cams.data(), ls.cam_begin, ls.cam_end, h->mlp,
-                        h->d_feat, h->d_guess, h->P.learned_block_waves ? h->P.learned_block_waves : kLearnWavesDefault,
-                        st);
+    const int waves = h->P.learned_block_waves ? h->P.learned_block_waves : kLearnWavesDefault;
+    return launch_learn(h->d_cams, launch_cams(h, ls, [&](const CamDesc& c) { return learn_blocks(c.cap, waves); }),
+                        h->d_cnt, h->mlp, h->d_feat, h->d_guess, waves, st);
   }
   if (stage == 2) {
     // speculative: every item; deferred: the temporal items only (they follow the stereo ones)
@@ -794,7 +802,7 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
 }
 
 // A frame runs on two streams. The pyramid stream builds the pyramid and
-// detections (its kernel copies the slot's frame table to the device) and
+// detections (its launch copies the slot's frame table to the device) and
 // then raises its signal; the launch stream runs the learned stage (its
 // inputs are the previous frame's keypoints and level 0, so it runs beside
 // the pyramid) and, once the signal reaches the frame's count, the tracker
@@ -826,28 +834,21 @@ static hipError_t enqueue_track_part(vio_frontend* h, const LaunchSet& ls, hipSt
   return enqueue_stage(h, ls, st, 3, timed);
 }
 
-// Captures a slot's learned stage and tracking part on first use; a capture
-// failure switches the handle to eager launches for good.
+// Captures a slot's tracking part on first use; a capture failure switches the
+// handle to eager launches for good.
 static void ensure_graph(vio_frontend* h, const LaunchSet& ls, Graphs* gr) {
   if (h->eager || h->plain || gr->any()) return;
-  // part 1: learned stage, 2: tracking part
-  auto capture = [&](hipGraphExec_t* out, int part) {
-    hipStream_t cs = h->stream;
-    hipGraph_t g = nullptr;
-    bool ok = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) == hipSuccess;
-    if (ok) {
-      const hipError_t e = part == 1 ? enqueue_stage(h, ls, cs, 4, false) : enqueue_track_part(h, ls, cs, false);
-      ok = hipStreamEndCapture(cs, &g) == hipSuccess && e == hipSuccess && g;
-    }
-    if (ok) ok = hipGraphInstantiate(out, g, nullptr, nullptr, 0) == hipSuccess;
-    if (g) (void)hipGraphDestroy(g);
-    return ok;
-  };
-  bool ok = capture(&gr->trk, 2);
-  if (ok && h->learned && !h->P.learned_fused) ok = capture(&gr->learn, 1);
-  gr->captured = ok;
+  hipStream_t cs = h->stream;
+  hipGraph_t g = nullptr;
+  bool ok = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) == hipSuccess;
+  if (ok) {
+    const hipError_t e = enqueue_track_part(h, ls, cs, false);
+    ok = hipStreamEndCapture(cs, &g) == hipSuccess && e == hipSuccess && g;
+  }
+  if (ok) ok = hipGraphInstantiate(&gr->trk, g, nullptr, nullptr, 0) == hipSuccess;
+  if (g) (void)hipGraphDestroy(g);
   if (!ok) {
-    gr->destroy();
+    gr->trk = nullptr;
     h->eager = true;
     (void)hipGetLastError();
   }
@@ -895,10 +896,9 @@ static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStrea
   HIP_CHECK(h, enqueue_pyr_part(h, ls, slot, timed, ps, st));
   if (ps == h->pstream) h->staged_uploads = false;
   if (h->learned && !h->P.learned_fused) {
-    // the learned stage's inputs are the previous frame's (ordered before it
-    // on this stream) and the pinned frame table: it starts at once
-    if (graphed) HIP_CHECK(h, hipGraphLaunch(gr[slot].learn, st));
-    else HIP_CHECK(h, enqueue_stage(h, ls, st, 4, timed));
+    // the learned stage's inputs are the previous frame's (ordered before it on
+    // this stream): it starts at once
+    HIP_CHECK(h, enqueue_stage(h, ls, st, 4, timed));
   }
   HIP_CHECK(h, wait_pyr_part(h, ps, st, slot));
   if (graphed) HIP_CHECK(h, hipGraphLaunch(gr[slot].trk, st));

@@ -43,9 +43,9 @@ constexpr int kCandChunk = 2048;  // tracks staged in LDS at a time (16 KB)
 // workgroup spread a camera over more compute units, each wave with a larger
 // share of its SIMD.
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_learn(const CamDesc* __restrict__ cams, const FrameTable* __restrict__ frame,
-                                                  const Counters* __restrict__ cnt, int cam_begin, int cam_end,
-                                                  MlpDev M, float* __restrict__ feat, float* __restrict__ guess) {
+__global__ __launch_bounds__(64 * W) void k_learn(const CamDesc* __restrict__ cams, const LaunchCams args,
+                                                  const Counters* __restrict__ cnt, MlpDev M,
+                                                  float* __restrict__ feat, float* __restrict__ guess) {
   static_assert(W >= 1 && W <= kTileRows, "one tile of keypoints per workgroup");
   constexpr int kTPW = (kHidTiles + W - 1) / W;  // hidden tiles per wave
   __shared__ float2 sCand[kCandChunk];                   // a chunk of the camera's tracks
@@ -54,18 +54,13 @@ __global__ __launch_bounds__(64 * W) void k_learn(const CamDesc* __restrict__ ca
   // start 4 banks apart instead of in the same bank
   __shared__ __align__(16) uint16_t sX[kTileRows][MI + 8];
   __shared__ __align__(16) uint16_t sH[kTileRows][MH + 8];
-  // the workgroup's camera and keypoints: ceil(cap / W) workgroups per camera
-  int c = cam_begin, b = (int)blockIdx.x;
-  for (; c < cam_end; ++c) {
-    const int nb = (cams[c].cap + W - 1) / W;
-    if (b < nb) break;
-    b -= nb;
-  }
-  if (c >= cam_end) return;  // the conditions below are uniform over the workgroup: no barrier is skipped
+  // the workgroup's camera and keypoints: learn_blocks(cap, W) workgroups per camera
+  const int entry = __builtin_amdgcn_readfirstlane(launch_entry(args, (int)blockIdx.x));
+  const CamArg fc = args.cam[entry];
+  if (!(fc.flags & kArgHasPrev)) return;  // (uniform over the workgroup, as below: no barrier is skipped)
+  const int c = fc.cam, b = (int)blockIdx.x - args.begin[entry];
   const CamDesc& cd = cams[c];
-  const FrameCam& fc = frame->cam[c];
-  if (!fc.active || !fc.has_prev) return;
-  const int Q = fc.parity ^ 1;
+  const int Q = (fc.flags & kArgParity ? 1 : 0) ^ 1;
   const int n = cnt->n_live[Q][c];
   const int j0 = b * W;
   if (j0 >= n) return;
@@ -225,25 +220,17 @@ __global__ __launch_bounds__(64 * W) void k_learn(const CamDesc* __restrict__ ca
 
 }  // namespace
 
-template <int W>
-static hipError_t launch_learn_w(const CamDesc* d_cams, const FrameTable* d_frame, const Counters* d_cnt,
-                                 const CamDesc* h_cams, int cam_begin, int cam_end, const MlpDev& M, float* d_feat,
-                                 float* d_guess, hipStream_t s) {
-  int blocks = 0;
-  for (int c = cam_begin; c < cam_end; ++c) blocks += (h_cams[c].cap + W - 1) / W;
-  launch_kernel(k_learn<W>, dim3(blocks), dim3(64 * W), 0, s, d_cams, d_frame, d_cnt, cam_begin, cam_end, M, d_feat,
-                d_guess);
-  return hipGetLastError();
-}
-
-hipError_t launch_learn(const CamDesc* d_cams, const FrameTable* d_frame, const Counters* d_cnt, const CamDesc* h_cams,
-                        int cam_begin, int cam_end, const MlpDev& M, float* d_feat, float* d_guess, int waves,
-                        hipStream_t s) {
-  if (cam_end <= cam_begin) return hipSuccess;
+hipError_t launch_learn(const CamDesc* d_cams, const LaunchCams& args, const Counters* d_cnt, const MlpDev& M,
+                        float* d_feat, float* d_guess, int waves, hipStream_t s) {
+  if (args.n < 1 || args.blocks < 1) return hipSuccess;
+  const auto launch = [&](auto kernel) {
+    launch_kernel(kernel, dim3(args.blocks), dim3(64 * waves), 0, s, d_cams, args, d_cnt, M, d_feat, d_guess);
+    return hipGetLastError();
+  };
   switch (waves) {
-    case 4: return launch_learn_w<4>(d_cams, d_frame, d_cnt, h_cams, cam_begin, cam_end, M, d_feat, d_guess, s);
-    case 8: return launch_learn_w<8>(d_cams, d_frame, d_cnt, h_cams, cam_begin, cam_end, M, d_feat, d_guess, s);
-    case 16: return launch_learn_w<16>(d_cams, d_frame, d_cnt, h_cams, cam_begin, cam_end, M, d_feat, d_guess, s);
+    case 4: return launch(k_learn<4>);
+    case 8: return launch(k_learn<8>);
+    case 16: return launch(k_learn<16>);
     default: return hipErrorInvalidValue;
   }
 }

@@ -7,14 +7,15 @@
 //  * computes the FAST-9 score (Sec. III-D) of the tile and a one-pixel ring
 //    (the paper's early rejection on ring pairs (0,8)/(4,12) over every pixel,
 //    the survivors compacted into an LDS list, then the score over the list,
-//    both polarities at once in 16-bit halves), keeps strict 3x3 maxima with
+//    both polarities at once in FP16 halves), keeps strict 3x3 maxima with
 //    score >= the last threshold and folds each into its cell's packed
 //    winner keys with atomicMax, and
 //  * builds every coarser pyramid level of the tile (Sec. III-C, eqs. 2-3)
 //    from LDS, recomputing the apron instead of reading it back from HBM, so
 //    level 0 is read from HBM once per frame and the L-1 level-serial
 //    dispatches of the paper become one launch.
-// All arithmetic is integer, so the result is bit-identical to a level-serial
+// All values are small integers (exact in FP16 too), so the result is bit-identical
+// to a level-serial
 // build.
 //
 // Threshold walk (Sec. III-D): walking the decreasing thresholds 40, 20, 10, 5
@@ -87,27 +88,25 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
   return ((j / R) * kXcds + x) * R + j % R;
 }
 
-// Signed differences of the 16 circle pixels to the centre (Bresenham circle
-// of radius 3 from (0,-3) clockwise), read from the LDS tile at offset `o`
-// with row pitch `sp`.
-__device__ __forceinline__ void ring_diffs(const uint8_t* img, int o, int sp, int d[16]) {
-  const int c = img[o];
-  d[0] = img[o - 3 * sp] - c;
-  d[1] = img[o - 3 * sp + 1] - c;
-  d[2] = img[o - 2 * sp + 2] - c;
-  d[3] = img[o - sp + 3] - c;
-  d[4] = img[o + 3] - c;
-  d[5] = img[o + sp + 3] - c;
-  d[6] = img[o + 2 * sp + 2] - c;
-  d[7] = img[o + 3 * sp + 1] - c;
-  d[8] = img[o + 3 * sp] - c;
-  d[9] = img[o + 3 * sp - 1] - c;
-  d[10] = img[o + 2 * sp - 2] - c;
-  d[11] = img[o + sp - 3] - c;
-  d[12] = img[o - 3] - c;
-  d[13] = img[o - sp - 3] - c;
-  d[14] = img[o - 2 * sp - 2] - c;
-  d[15] = img[o - 3 * sp - 1] - c;
+// The 16 circle pixels (Bresenham circle of radius 3 from (0,-3) clockwise) of
+// the pixel at offset `o` of the LDS tile with row pitch `sp`.
+__device__ __forceinline__ void ring_pixels(const uint8_t* img, int o, int sp, uint32_t p[16]) {
+  p[0] = img[o - 3 * sp];
+  p[1] = img[o - 3 * sp + 1];
+  p[2] = img[o - 2 * sp + 2];
+  p[3] = img[o - sp + 3];
+  p[4] = img[o + 3];
+  p[5] = img[o + sp + 3];
+  p[6] = img[o + 2 * sp + 2];
+  p[7] = img[o + 3 * sp + 1];
+  p[8] = img[o + 3 * sp];
+  p[9] = img[o + 3 * sp - 1];
+  p[10] = img[o + 2 * sp - 2];
+  p[11] = img[o + sp - 3];
+  p[12] = img[o - 3];
+  p[13] = img[o - sp - 3];
+  p[14] = img[o - 2 * sp - 2];
+  p[15] = img[o - 3 * sp - 1];
 }
 
 typedef short short2v __attribute__((ext_vector_type(2)));
@@ -118,66 +117,76 @@ typedef short short2v __attribute__((ext_vector_type(2)));
 //   min(max(p0, p8), max(p4, p12)) - I(p) > tmin   (bright) or
 //   I(p) - max(min(p0, p8), min(p4, p12)) > tmin   (dark).
 // Four horizontally adjacent pixels at once: byte k of c is pixel k, of p0,
-// p4, p8, p12 its ring pixels 0 (above), 4 (right), 8 (below), 12 (left);
-// bytes 0, 2 and then 1, 3 ride in 16-bit halves. Bit k of the result is set
-// when pixel k passes.
+// p4, p8, p12 its ring pixels 0 (above), 4 (right), 8 (below), 12 (left). Two
+// pixels ride in the high bytes of a word's 16-bit halves: unsigned minima and
+// maxima of the halves order by the high byte first, so what is in the low
+// bytes does not matter, and pixels 1 and 3 need no unpacking, 0 and 2 a shift.
+// Bit k of the result is set when pixel k passes.
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t fast_may_pass4(uint32_t p0, uint32_t p4, uint32_t p8, uint32_t p12, uint32_t c,
                                                    int tmin) {
   const short2v tm = {(short)tmin, (short)tmin};
   uint32_t res = 0;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    auto pair = [h](uint32_t w) { return __builtin_bit_cast(short2v, (w >> (8 * h)) & 0x00FF00FFu); };
-    const short2v a = pair(p0), b = pair(p8), r = pair(p4), l = pair(p12), cc = pair(c);
-    const short2v hi = __builtin_elementwise_min(__builtin_elementwise_max(a, b), __builtin_elementwise_max(r, l));
-    const short2v lo = __builtin_elementwise_max(__builtin_elementwise_min(a, b), __builtin_elementwise_min(r, l));
+    const auto halves = [h](uint32_t w) { return __builtin_bit_cast(ushort2v, h == 0 ? w << 8 : w); };
+    const auto byte = [](ushort2v w) { return __builtin_bit_cast(short2v, (ushort2v)(w >> 8)); };
+    const ushort2v a = halves(p0), b = halves(p8), r = halves(p4), l = halves(p12);
+    const short2v hi =
+        byte(__builtin_elementwise_min(__builtin_elementwise_max(a, b), __builtin_elementwise_max(r, l)));
+    const short2v lo =
+        byte(__builtin_elementwise_max(__builtin_elementwise_min(a, b), __builtin_elementwise_min(r, l)));
+    const short2v cc = byte(halves(c));
     // sign bit set where tmin - margin < 0, i.e. the margin exceeds tmin
-    const uint32_t e = __builtin_bit_cast(uint32_t, (short2v)(tm - (hi - cc))) |
-                       __builtin_bit_cast(uint32_t, (short2v)(tm - (cc - lo)));
-    res |= ((e >> 15) & 1u) << h;        // byte h
-    res |= ((e >> 31) & 1u) << (2 + h);  // byte h + 2
+    const uint32_t e = __builtin_bit_cast(uint32_t, (short2v)((cc + tm) - hi)) |
+                       __builtin_bit_cast(uint32_t, (short2v)((lo + tm) - cc));
+    res |= ((e >> 15) & 1u) << h;        // pixel h
+    res |= ((e >> 31) & 1u) << (2 + h);  // pixel h + 2
   }
   return res;
 }
 
 // FAST-9 score (Sec. III-D): the largest tau with a 9-arc all brighter than
 // I(p)+tau or all darker than I(p)-tau, i.e. (max over polarity and arc of the
-// arc's minimum signed difference) - 1. Both polarities ride in the two
-// 16-bit halves of one register (differences lie in -255..255): sliding
-// minima of width 2, 4, then 9 over the circle, one maximum.
-__device__ __forceinline__ int fast_score(const int d[16]) {
-  short2v e[16], m2[16], m4[16];
+// arc's minimum signed difference to the centre c) - 1. Both polarities ride in
+// the two halves of one register, the ring pixel p and 255 - p, as the FP16
+// values 1024 + p and 1279 - p (whose bits are 0x6400 plus the byte, so their
+// order is the bytes'): sliding minima of width 3 and then 9 over the circle and
+// one maximum, three operands an instruction.
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int fast_score(const uint32_t p[16], int c) {
+  half2v e[16], m3[16];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) e[k] = short2v{(short)d[k], (short)-d[k]};
+  for (int k = 0; k < 16; ++k)  // p + 0x6400 in the low half, 255 - p + 0x6400 in the high one
+    e[k] = __builtin_bit_cast(half2v, (uint32_t)(__mul24((int)p[k], 1 - 65536) + 0x64FF6400));
+  const auto min3 = [](half2v a, half2v b, half2v c) {
+    return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
+  };
 #pragma unroll
-  for (int k = 0; k < 16; ++k) m2[k] = __builtin_elementwise_min(e[k], e[(k + 1) & 15]);
+  for (int k = 0; k < 16; ++k) m3[k] = min3(e[k], e[(k + 1) & 15], e[(k + 2) & 15]);
+  half2v best = min3(m3[0], m3[3], m3[6]);
 #pragma unroll
-  for (int k = 0; k < 16; ++k) m4[k] = __builtin_elementwise_min(m2[k], m2[(k + 2) & 15]);
-  short2v best = __builtin_elementwise_min(__builtin_elementwise_min(m4[0], m4[4]), e[8]);
-#pragma unroll
-  for (int k = 1; k < 16; ++k)
-    best = __builtin_elementwise_max(
-        best, __builtin_elementwise_min(__builtin_elementwise_min(m4[k], m4[(k + 4) & 15]), e[(k + 8) & 15]));
-  return max(max((int)best.x, (int)best.y) - 1, -1);
+  for (int k = 1; k < 15; k += 2)
+    best = __builtin_elementwise_maximum(
+        __builtin_elementwise_maximum(best, min3(m3[k], m3[(k + 3) & 15], m3[(k + 6) & 15])),
+        min3(m3[k + 1], m3[(k + 4) & 15], m3[(k + 7) & 15]));
+  best = __builtin_elementwise_maximum(best, min3(m3[15], m3[2], m3[5]));
+  const uint32_t w = __builtin_bit_cast(uint32_t, best);
+  const int bright = (int)(w & 0xFFu) - c, dark = (int)((w >> 16) & 0xFFu) - 255 + c;
+  return max(max(bright, dark) - 1, -1);
 }
 
-typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t* s_v32(uint16_t* p) { return reinterpret_cast<uint32_t*>(p); }
 
 // eq. (2) for two adjacent outputs: with input bytes x0..x6 (x_k = byte k of
 // a, then b), out = (x0 + 4 x1 + 6 x2 + 4 x3 + x4, x2 + 4 x3 + 6 x4 + 4 x5 + x6)
-// in the low and high 16-bit halves (each at most 16 * 255).
+// in the low and high 16-bit halves (each at most 16 * 255), as two four-byte dot
+// products each.
 __device__ __forceinline__ uint32_t pyr_h_pair(uint32_t a, uint32_t b) {
-  // v_perm_b32 selectors over (b:a): bytes 0..3 of a are 0..3, of b 4..7; 0x0C gives zero
-  const ushort2v p0 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(b, a, 0x0C020C00u));  // x0, x2
-  const ushort2v p1 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(b, a, 0x0C030C01u));  // x1, x3
-  const ushort2v p2 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(b, a, 0x0C040C02u));  // x2, x4
-  const ushort2v p3 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(b, a, 0x0C050C03u));  // x3, x5
-  const ushort2v p4 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(b, a, 0x0C060C04u));  // x4, x6
-  const ushort2v four = {4, 4}, six = {6, 6};
-  const ushort2v s = (p0 + p4) + four * (p1 + p3) + six * p2;
-  return __builtin_bit_cast(uint32_t, s);
+  const uint32_t lo = __builtin_amdgcn_udot4(b, 0x00000001u, __builtin_amdgcn_udot4(a, 0x04060401u, 0u, false), false);
+  const uint32_t hi = __builtin_amdgcn_udot4(b, 0x00010406u, __builtin_amdgcn_udot4(a, 0x04010000u, 0u, false), false);
+  return lo | (hi << 16);
 }
 
 // eq. (3) for two adjacent columns: five rows of packed horizontal sums,
@@ -195,10 +204,10 @@ __device__ __forceinline__ uint32_t pyr_v_pair(uint32_t r0, uint32_t r1, uint32_
 
 template <int L, int T>
 __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDesc* __restrict__ cams,
+                                                                      const LaunchCams args,
                                                                       const FrameTable* __restrict__ frame,
                                                                       FrameTable* __restrict__ dframe,
-                                                                      int copy_words, int cam_begin, int cam_end,
-                                                                      int tile_base, int tmin, int margin) {
+                                                                      int copy_words, int tmin, int margin) {
   using G = PyrGeom<L, T>;
   static_assert(G::threads == (T == 64 ? 1024 : 256), "launch bounds");
   constexpr int kTile = T;
@@ -211,21 +220,19 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
   __shared__ __align__(16) uint16_t s_v[G::vbytes];
   __shared__ __align__(16) uint8_t s_lv[2][G::lvl_bytes];
 
-  // `frame` is the frame's table in mapped pinned host memory; the first
-  // workgroup copies it to the device table that the later kernels of the
-  // frame read (no separate copy call on the host)
-  if (blockIdx.x == 0) {
+  // the last workgroup copies the frame's table from mapped pinned host memory to
+  // the device table that the later kernels of the frame read
+  if ((int)blockIdx.x == args.blocks) {
     const uint32_t* fs = reinterpret_cast<const uint32_t*>(frame);
     uint32_t* fd = reinterpret_cast<uint32_t*>(dframe);
     for (int i = (int)threadIdx.x; i < copy_words; i += kPyrThreads) fd[i] = fs[i];
+    return;
   }
-  const int gtile = tile_base + xcd_tile<G::xcd_run>((int)blockIdx.x, (int)gridDim.x);
-  int c = cam_begin;
-  while (c + 1 < cam_end && cams[c + 1].tile_begin <= gtile) ++c;
-  const CamDesc& cd = cams[c];
-  const FrameCam& fc = frame->cam[c];
-  if (!fc.active) return;
-  const int t = gtile - cd.tile_begin;
+  const int gtile = xcd_tile<G::xcd_run>((int)blockIdx.x, args.blocks);
+  const int entry = __builtin_amdgcn_readfirstlane(launch_entry(args, gtile));
+  const CamArg fc = args.cam[entry];
+  const CamDesc& cd = cams[fc.cam];
+  const int t = gtile - args.begin[entry];
   const int x0 = (t % cd.tiles_x) * kTile, y0 = (t / cd.tiles_x) * kTile;
   const int W = cd.w, H = cd.h, par = fc.pyr;
   const int tid = threadIdx.x;
@@ -264,7 +271,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
   __syncthreads();
 
   // ---- copy level 0 into the own pyramid when it came from outside --------
-  if (fc.copy_l0) {
+  if (fc.flags & kArgCopyL0) {
     uint8_t* dst = cd.lvl[par][0];
     const int dp = cd.pitch[0];
     for (int i = tid; i < kTile * (kTile / 4); i += kPyrThreads) {
@@ -335,9 +342,10 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
     for (int j = tid; j < ncand; j += kPyrThreads) {
       const int i = s_cand[j];
       const int sy = y0 - 1 + i / kScoreEdge, sx = x0 - 1 + i % kScoreEdge;
-      int d[16];
-      ring_diffs(s_l0, (sy - oy0) * G::sw0 + (sx - ox0), G::sw0, d);
-      const int score = fast_score(d);
+      const int o = (sy - oy0) * G::sw0 + (sx - ox0);
+      uint32_t ring[16];
+      ring_pixels(s_l0, o, G::sw0, ring);
+      const int score = fast_score(ring, s_l0[o]);
       s_score[i] = (uint8_t)(score >= tmin ? score + 1 : 0);
     }
     __syncthreads();
@@ -484,10 +492,10 @@ __global__ __launch_bounds__(256) void k_upload(const uint32_t* __restrict__ src
 }
 
 template <int L, int T>
-hipError_t launch_LT(const CamDesc* cams, const FrameTable* frame, FrameTable* dframe, int copy_words, int cam_begin,
-                     int cam_end, int tile_base, int n_tiles, int tmin, int margin, hipStream_t s) {
-  launch_kernel(k_pyr_detect<L, T>, dim3(n_tiles), dim3(PyrGeom<L, T>::threads), 0, s, cams, frame, dframe, copy_words,
-                cam_begin, cam_end, tile_base, tmin, margin);
+hipError_t launch_LT(const CamDesc* cams, const LaunchCams& args, const FrameTable* frame, FrameTable* dframe,
+                     int copy_words, int tmin, int margin, hipStream_t s) {
+  launch_kernel(k_pyr_detect<L, T>, dim3(args.blocks + 1), dim3(PyrGeom<L, T>::threads), 0, s, cams, args, frame,
+                dframe, copy_words, tmin, margin);
   return hipGetLastError();
 }
 
@@ -508,21 +516,15 @@ size_t lds_bytes_T(int levels) {
 }
 
 template <int T>
-hipError_t launch_T(const CamDesc* d_cams, const FrameTable* h_frame, FrameTable* d_frame, int copy_words, int cam_begin,
-                    int cam_end, int tile_base, int n_tiles, int levels, int tmin, int margin, hipStream_t s) {
+hipError_t launch_T(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame, FrameTable* d_frame,
+                    int copy_words, int levels, int tmin, int margin, hipStream_t s) {
   switch (levels) {
-    case 1: return launch_LT<1, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
-    case 2: return launch_LT<2, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
-    case 3: return launch_LT<3, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
-    case 4: return launch_LT<4, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
-    case 5: return launch_LT<5, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
-    case 6: return launch_LT<6, T>(d_cams, h_frame, d_frame, copy_words, cam_begin, cam_end, tile_base, n_tiles, tmin,
-                                       margin, s);
+    case 1: return launch_LT<1, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 2: return launch_LT<2, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 3: return launch_LT<3, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 4: return launch_LT<4, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 5: return launch_LT<5, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 6: return launch_LT<6, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -542,15 +544,13 @@ hipError_t launch_upload(const void* d_src, void* d_dst, size_t bytes, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_pyr_detect_range(const CamDesc* d_cams, const FrameTable* h_frame, FrameTable* d_frame,
-                                   int copy_bytes, int cam_begin, int cam_end, int tile_base, int n_tiles, int levels,
-                                   int tile, int tmin, int margin, hipStream_t s) {
-  if (n_tiles <= 0 || copy_bytes % 4) return hipErrorInvalidValue;
+hipError_t launch_pyr_detect(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame,
+                             FrameTable* d_frame, int copy_bytes, int levels, int tile, int tmin, int margin,
+                             hipStream_t s) {
+  if (args.n < 1 || args.blocks < 1 || copy_bytes % 4) return hipErrorInvalidValue;
   const int w = copy_bytes / 4;
-  if (tile == 32)
-    return launch_T<32>(d_cams, h_frame, d_frame, w, cam_begin, cam_end, tile_base, n_tiles, levels, tmin, margin, s);
-  if (tile == 64)
-    return launch_T<64>(d_cams, h_frame, d_frame, w, cam_begin, cam_end, tile_base, n_tiles, levels, tmin, margin, s);
+  if (tile == 32) return launch_T<32>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, s);
+  if (tile == 64) return launch_T<64>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, s);
   return hipErrorInvalidValue;
 }
 

@@ -90,3 +90,31 @@ def test_push_among_frames_in_flight_and_staged_host_images():
                 a.step()
             for s in (0, 1):
                 assert a.get_tracks(s).tobytes() == b.get_tracks(s).tobytes(), (t, s)
+
+
+@pytest.mark.parametrize("learned", [False, True])
+def test_sixty_four_cameras_partly_staged(learned):
+    """The most cameras a handle can have, of two sizes, with every third stream
+    left out of each step: the records are those of pushing each stream alone."""
+    import paper_2609_30459_amd as vf
+    seqs = [synthgen.render(seed=s, width=64 + 16 * s, height=48 + 9 * s, n_frames=4, density=4.0) for s in (0, 1, 2)]
+    streams = [(1,) + seqs[s % 3].size + (20 + s % 7, 16) for s in range(64)]
+    kw = dict(init_mode=1, learned_levels=2, learned_iters=3, learned_rho=0.05) if learned else {}
+    p = vf.make_params(levels=3, **kw)
+    with vf.Frontend(streams, p) as a, vf.Frontend(streams, p) as b:
+        if learned:
+            rng = np.random.default_rng(3)
+            params = rng.normal(0, 0.02, vf.MLP_NPARAM).astype(np.float32)
+            a.set_mlp(params)
+            b.set_mlp(params)
+        at = [0] * 64
+        for t in range(4):
+            now = [s for s in range(64) if (s + t) % 3]
+            for s in now:
+                im = [seqs[s % 3].frames[at[s], 0]]
+                at[s] += 1
+                a.stage_frame(s, t + 1, im)
+                b.push_stereo_frame(s, t + 1, im)
+            a.step()
+            for s in now:
+                assert a.get_tracks(s).tobytes() == b.get_tracks(s).tobytes(), (t, s)
