@@ -14,6 +14,10 @@ constexpr int kMaxLevels = VIO_MAX_LEVELS;
 constexpr int kMaxCams = VIO_MAX_CAMERAS;
 constexpr int kPatch = 52;      // pattern points (Sec. III-E)
 constexpr int kTileDefault = 64;  // level-0 tile edge of the pyramid/detector kernel unless chosen
+// Handles of at most so many 64-px tiles (half the compute units) take 32-px ones unless chosen:
+// mono 320x240 (20) 7.4 us with 64-px tiles, 6.3 with 32-px ones; 641x479 (88) 13.2 and 12.6;
+// two 752x480 (192) 10.5 and 11.3.
+constexpr int kFewTiles = 128;
 // Row pitch of a pyramid level `width` pixels wide.
 __host__ __device__ constexpr int level_pitch(int width) { return (width + 63) & ~63; }
 // Kernel timing: while set, the frontend's kernel launches on this thread
@@ -159,7 +163,8 @@ struct CamArg {
   int32_t src_pitch;
   uint8_t cam, pyr, pyr_prev, flags;
 };
-enum : uint8_t { kArgCopyL0 = 1, kArgHasPrev = 2, kArgParity = 4 };
+// (kArgDetect, kArgLevels: what the entry's pyramid workgroups do)
+enum : uint8_t { kArgCopyL0 = 1, kArgHasPrev = 2, kArgParity = 4, kArgDetect = 8, kArgLevels = 16 };
 static_assert(kMaxCams <= 64, "a wave finds its entry with one load and a vote");
 struct LaunchCams {
   int32_t n, blocks;  // entries, workgroups in all

@@ -301,18 +301,42 @@ int check_params(const vio_frontend_params* p, std::string& why) {
 }
 
 // The launch set's active cameras with their inputs from the frame's table and
-// blocks_of(camera) workgroups each.
+// blocks_of(camera) workgroups each; `flags` is set in every entry, and cameras
+// for which blocks_of is 0 are left out. Entries are added to `a`.
 template <class BlocksOf>
-LaunchCams launch_cams(const vio_frontend* h, const LaunchSet& ls, const BlocksOf& blocks_of) {
-  LaunchCams a{};
+void add_launch_cams(const vio_frontend* h, const LaunchSet& ls, int flags, const BlocksOf& blocks_of, LaunchCams& a) {
   for (int c = ls.cam_begin; c < ls.cam_end; ++c) {
     const FrameCam& f = h->h_frame->cam[c];
-    if (!f.active) continue;
+    const int blocks = f.active ? blocks_of(h->cams[c]) : 0;
+    if (blocks == 0) continue;
     a.begin[a.n] = a.blocks;
-    a.blocks += blocks_of(h->cams[c]);
+    a.blocks += blocks;
     a.cam[a.n++] = CamArg{f.src, f.src_pitch, (uint8_t)c, (uint8_t)f.pyr, (uint8_t)f.pyr_prev,
-                          (uint8_t)((f.copy_l0 ? kArgCopyL0 : 0) | (f.has_prev ? kArgHasPrev : 0) |
-                                    (f.parity ? kArgParity : 0))};
+                          (uint8_t)(flags | (f.copy_l0 && (flags & kArgLevels) ? kArgCopyL0 : 0) |
+                                    (f.has_prev ? kArgHasPrev : 0) | (f.parity ? kArgParity : 0))};
+  }
+}
+
+// The pyramid launch: a tile's detection and levels in one workgroup, one after
+// the other, or in two. Two stage the tile twice and so take longer when the chip
+// is full, but halve the chain while all of them fit at once: two 1,024-thread
+// workgroups to a compute unit; of the 256-thread ones, whose chains are short,
+// four by measurement. With 64-px tiles: mono 320x240 (40 workgroups) 9.2 -> 7.8
+// us, stereo 752x480 (384) 13.1 -> 10.7, star 752x480 (480) 14.1 -> 11.9, but
+// stereo 1280x720 (960) 13.8 -> 20.9; with 32-px ones mono 320x240 (160) 8.6 ->
+// 6.8, mono 641x479 (630) 16.3 -> 14.4, star 752x480 (1,800) 12.3 -> 12.8.
+LaunchCams pyramid_args(const vio_frontend* h, const LaunchSet& ls) {
+  LaunchCams a{};
+  const auto tiles = [](const CamDesc& c) { return c.tiles_x * c.tiles_y; };
+  int split = 0;  // workgroups of a split launch
+  for (int c = ls.cam_begin; c < ls.cam_end; ++c)
+    if (h->h_frame->cam[c].active) split += tiles(h->cams[c]) * (h->cams[c].detect ? 2 : 1);
+  if (split <= h->n_cus * (h->tile == 32 ? 4 : 2) && 2 * (ls.cam_end - ls.cam_begin) <= kMaxCams) {
+    add_launch_cams(h, ls, kArgDetect, [&](const CamDesc& c) { return c.detect ? tiles(c) : 0; }, a);
+    add_launch_cams(h, ls, kArgLevels, tiles, a);
+  } else {
+    add_launch_cams(h, ls, kArgLevels | kArgDetect, [&](const CamDesc& c) { return c.detect ? tiles(c) : 0; }, a);
+    add_launch_cams(h, ls, kArgLevels, [&](const CamDesc& c) { return c.detect ? 0 : tiles(c); }, a);
   }
   return a;
 }
@@ -678,7 +702,10 @@ int vio_frontend_create(const vio_stream_desc* streams, int32_t n_streams, const
   h->eager = (params->flags & VIO_FLAG_EAGER) != 0;
   h->plain = (params->flags & VIO_FLAG_PLAIN) != 0;
   h->learned = params->init_mode == VIO_INIT_LEARNED;
-  h->tile = params->pyr_tile ? params->pyr_tile : kTileDefault;
+  int tiles = 0;
+  for (int s = 0; s < n_streams; ++s)
+    tiles += streams[s].n_cameras * ((streams[s].width + 63) / 64) * ((streams[s].height + 63) / 64);
+  h->tile = params->pyr_tile ? params->pyr_tile : tiles <= kFewTiles ? 32 : kTileDefault;
   const int rc = create_impl(h, streams, n_streams);
   if (rc != VIO_OK) {
     vio_frontend_destroy(h);
@@ -769,7 +796,7 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
   hipError_t e;
   if (stage == 1) {
     timing(kKernPyr);
-    return launch_pyr_detect(h->d_cams, launch_cams(h, ls, [&](const CamDesc& c) { return c.tiles_x * c.tiles_y; }),
+    return launch_pyr_detect(h->d_cams, pyramid_args(h, ls),
                              h->hm_frame, h->d_frame,
                              (int)(offsetof(FrameTable, cam) + sizeof(FrameCam) * h->cams.size()), tune.levels,
                              h->tile, tune.tmin, tune.margin, st);
@@ -779,8 +806,9 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
     // launch; the tracker reads the guesses
     timing(kKernFeatures);
     const int waves = h->P.learned_block_waves ? h->P.learned_block_waves : kLearnWavesDefault;
-    return launch_learn(h->d_cams, launch_cams(h, ls, [&](const CamDesc& c) { return learn_blocks(c.cap, waves); }),
-                        h->d_cnt, h->mlp, h->d_feat, h->d_guess, waves, st);
+    LaunchCams args{};
+    add_launch_cams(h, ls, 0, [&](const CamDesc& c) { return learn_blocks(c.cap, waves); }, args);
+    return launch_learn(h->d_cams, args, h->d_cnt, h->mlp, h->d_feat, h->d_guess, waves, st);
   }
   if (stage == 2) {
     // speculative: every item; deferred: the temporal items only (they follow the stereo ones)

@@ -68,6 +68,22 @@ struct PyrGeom {
   static constexpr int xcd_run = 512 / T;
 };
 
+// Global memory by name, so that pointers read from a descriptor are not taken for
+// possible LDS addresses; dwords at any byte offset.
+typedef const __attribute__((address_space(1))) uint8_t* gbytes;
+typedef __attribute__((address_space(1))) uint8_t* gbytes_out;
+typedef __attribute__((address_space(1))) uint32_t* gwords;
+struct __attribute__((packed)) U32 {
+  uint32_t v;
+};
+__device__ __forceinline__ uint32_t ld32(gbytes p, ptrdiff_t off) {
+  return ((const __attribute__((address_space(1))) U32*)(p + off))->v;
+}
+// *p <- max(*p, v); the old value
+__device__ __forceinline__ uint32_t max_exchange(gwords p, uint32_t v) {
+  return __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // Tile of workgroup b among n. Workgroups go to the 8 XCDs in turn (b mod 8),
@@ -229,7 +245,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
     return;
   }
   const int gtile = xcd_tile<G::xcd_run>((int)blockIdx.x, args.blocks);
-  const int entry = __builtin_amdgcn_readfirstlane(launch_entry(args, gtile));
+  const int entry = args.n == 1 ? 0 : __builtin_amdgcn_readfirstlane(launch_entry(args, gtile));
   const CamArg fc = args.cam[entry];
   const CamDesc& cd = cams[fc.cam];
   const int t = gtile - args.begin[entry];
@@ -239,26 +255,27 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
 
   // ---- stage level 0 (tile + apron) -------------------------------------
   const int ox0 = x0 - G::a0x, oy0 = y0 - G::a0;
-  const uint8_t* src = fc.src;
+  // a workgroup that only detects stages only the rows that takes
+  const int row0 = fc.flags & kArgLevels ? 0 : G::a0 - 4, row1 = fc.flags & kArgLevels ? G::sh0 : G::a0 + kTile + 4;
+  const gbytes src = (gbytes)fc.src;
   const int sp = fc.src_pitch;
-  const bool aligned = ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)sp) & 3) == 0;
   constexpr int qrow = G::sw0 / 4;
-  if (aligned && ox0 >= 0 && oy0 >= 0 && ox0 + G::sw0 <= W && oy0 + G::sh0 <= H) {
+  if (ox0 >= 0 && oy0 >= 0 && ox0 + G::sw0 <= W && oy0 + G::sh0 <= H) {
     // the whole staged region inside the image (the workgroup's choice): plain dword copies
-    for (int i = tid; i < G::sh0 * qrow; i += kPyrThreads) {
+    const gbytes from = src + ((ptrdiff_t)oy0 * sp + ox0);
+    for (int i = row0 * qrow + tid; i < row1 * qrow; i += kPyrThreads) {
       const int r = i / qrow, q = i - r * qrow;
-      *reinterpret_cast<uint32_t*>(&s_l0[r * G::sw0 + 4 * q]) =
-          *reinterpret_cast<const uint32_t*>(src + (size_t)(oy0 + r) * sp + ox0 + 4 * q);
+      *reinterpret_cast<uint32_t*>(&s_l0[r * G::sw0 + 4 * q]) = ld32(from, (ptrdiff_t)r * sp + 4 * q);
     }
   } else
-  for (int i = tid; i < G::sh0 * qrow; i += kPyrThreads) {
+  for (int i = row0 * qrow + tid; i < row1 * qrow; i += kPyrThreads) {
     const int r = i / qrow, q = i - r * qrow;
     const int y = oy0 + r, x = ox0 + 4 * q;
     uint32_t v = 0;
     if (y >= 0 && y < H) {
-      const uint8_t* row = src + (size_t)y * sp;
-      if (aligned && x >= 0 && x + 3 < W) {
-        v = *reinterpret_cast<const uint32_t*>(row + x);
+      const gbytes row = src + (ptrdiff_t)y * sp;
+      if (x >= 0 && x + 3 < W) {
+        v = ld32(row, x);
       } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -272,7 +289,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
 
   // ---- copy level 0 into the own pyramid when it came from outside --------
   if (fc.flags & kArgCopyL0) {
-    uint8_t* dst = cd.lvl[par][0];
+    const gbytes_out dst = (gbytes_out)cd.lvl[par][0];
     const int dp = cd.pitch[0];
     for (int i = tid; i < kTile * (kTile / 4); i += kPyrThreads) {
       const int r = i / (kTile / 4), q = i - r * (kTile / 4);
@@ -280,7 +297,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
       if (y >= H || x >= W) continue;
       const uint8_t* s = &s_l0[(y - oy0) * G::sw0 + (x - ox0)];
       if (x + 3 < W) {
-        *reinterpret_cast<uint32_t*>(dst + (size_t)y * dp + x) = *reinterpret_cast<const uint32_t*>(s);
+        *(__attribute__((address_space(1))) uint32_t*)(dst + (size_t)y * dp + x) = *reinterpret_cast<const uint32_t*>(s);
       } else {
         for (int k = 0; x + k < W; ++k) dst[(size_t)y * dp + x + k] = s[k];
       }
@@ -293,7 +310,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
   // a quarter of a textured image) to a list; the full score then runs over
   // the list, so a wave scores 64 survivors at a time instead of running the
   // score for every wave that holds one.
-  if (cd.detect) {
+  if (fc.flags & kArgDetect) {
     const int lane = tid & 63;
     for (int i = tid; i < G::score_bytes / 4; i += kPyrThreads) reinterpret_cast<uint32_t*>(s_score)[i] = 0u;
     // four pixels per thread: the score-region row cy, columns 4g-3 .. 4g
@@ -350,7 +367,12 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
     }
     __syncthreads();
     // strict 3x3 maxima: only listed pixels can hold a nonzero score
-    uint32_t* keys = cd.keys[par];
+    const gwords keys = (gwords)cd.keys[par];
+    const gbytes mask = (gbytes)cd.mask;
+    // v / cell for v < 2^20: (v + 1/2) / cell stays 1 / (2 cell) away from every whole
+    // number, and its product with the rounded inverse errs by less than (v + 1/2) / (2^22 cell)
+    const float icell = 1.f / (float)cd.cell;
+    const auto cells = [icell](int v) { return (int)(((float)v + 0.5f) * icell); };
     for (int j = tid; j < ncand; j += kPyrThreads) {
       const int i = s_cand[j];
       const int ly = i / kScoreEdge - 1, lx = i % kScoreEdge - 1;
@@ -366,26 +388,27 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
                         (s > sc[kScoreEdge]) & (s > sc[kScoreEdge + 1]);
       // the caller's detection mask drops a corner after the maximum test, so
       // a masked maximum still suppresses its neighbours
-      if (peak && (!cd.has_mask || cd.mask[y * W + x] == 0)) {
+      if (peak && (!cd.has_mask || mask[y * W + x] == 0)) {
         const uint32_t key = ((uint32_t)(s - 1) << 24) | (0xFFFFFFu - (uint32_t)(y * W + x));
-        const int cell = (y / cd.cell) * cd.ncx + x / cd.cell;
+        const int cell = cells(y) * cd.ncx + cells(x);
         if (cd.kcell == 1) {
-          atomicMax(&keys[cell], key);
+          (void)max_exchange(keys + cell, key);
         } else {
           // k > 1: the cell's k slots keep its best keys in descending order.
           // Each slot keeps the larger of its value and the incoming key and
           // passes the smaller one on, so slot values plus keys in flight
           // always form the same multiset; once every insert has finished,
           // slot r holds the (r+1)-th largest key (0 = none).
-          uint32_t* slot = keys + cell * cd.kcell;
+          const gwords slot = keys + cell * cd.kcell;
           uint32_t v = key;
-          for (int r = 0; r < cd.kcell && v != 0u; ++r) v = min(v, atomicMax(&slot[r], v));
+          for (int r = 0; r < cd.kcell && v != 0u; ++r) v = min(v, max_exchange(slot + r, v));
         }
       }
     }
   }
 
   // ---- coarser levels from LDS (eqs. 2-3) ---------------------------------
+  if (!(fc.flags & kArgLevels)) return;
   if constexpr (L > 1) {
     const uint8_t* cur = s_l0;
     int cur_ox = ox0, cur_oy = oy0, cur_p = G::sw0;
@@ -422,7 +445,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
         __syncthreads();
         // eq. (3): +128 then >> 8, two columns per thread
         uint8_t* nxt = s_lv[l & 1];
-        uint8_t* gdst = cd.lvl[par][l + 1];
+        const gbytes_out gdst = (gbytes_out)cd.lvl[par][l + 1];
         const int gp = cd.pitch[l + 1];
         const int tx0 = x0 >> (l + 1), ty0 = y0 >> (l + 1), te = kTile >> (l + 1);
         const int nn = (Y1 - Y0 + 1) * npair;
@@ -433,7 +456,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
           const int X = o_x + 2 * q;
           *reinterpret_cast<uint16_t*>(&nxt[(Y - o_y) * S + 2 * q]) = (uint16_t)v2;
           if (X >= tx0 && X < tx0 + te && Y >= ty0 && Y < ty0 + te)
-            *reinterpret_cast<uint16_t*>(&gdst[(size_t)Y * gp + X]) = (uint16_t)v2;
+            *(__attribute__((address_space(1))) uint16_t*)(gdst + (size_t)Y * gp + X) = (uint16_t)v2;
         }
         __syncthreads();
         cur = nxt;
@@ -455,7 +478,7 @@ __global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDe
         __syncthreads();
         // eq. (3): vertical pass, +128 then >> 8
         uint8_t* nxt = s_lv[l & 1];
-        uint8_t* gdst = cd.lvl[par][l + 1];
+        const gbytes_out gdst = (gbytes_out)cd.lvl[par][l + 1];
         const int gp = cd.pitch[l + 1];
         const int tx0 = x0 >> (l + 1), ty0 = y0 >> (l + 1), te = kTile >> (l + 1);
         const int nn = (Y1 - Y0 + 1) * S;
