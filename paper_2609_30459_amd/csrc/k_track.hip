@@ -56,6 +56,7 @@
 // current pyramids, so they run beside the temporal tracks instead of after the
 // selection, and the selection kernel picks the ones it keeps.
 #include <algorithm>
+#include <type_traits>
 
 #include "fe_common.h"
 #include "learn_ops.h"
@@ -158,10 +159,10 @@ constexpr int kWinW = 24, kWinH = 21, kWinLead = 9;
 constexpr int kWinWords = 128;
 constexpr int kWinBytes = 4 * kWinWords;
 static_assert(kWinW % 4 == 0 && kWinW / 4 * kWinH <= kWinWords, "a window is two loads of 64 dwords");
-// a block's windows, [wave][image][level], aligned to a window; a template's
+// a block's windows, [wave][image][keypoint][level], aligned to a window; a template's
 // reads run up to three rows and one dword past its first
-template <int L>
-constexpr int kWinBlock = kTrackWaves * 2 * L * kWinWords + 3 * (kWinW / 4) + 2;
+template <int L, int KP = 1>
+constexpr int kWinBlock = kTrackWaves * KP * 2 * L * kWinWords + 3 * (kWinW / 4) + 2;
 typedef __attribute__((address_space(3))) uint32_t* lds_words;
 
 // The windows of one image's levels: lane l holds level l's position (a wave's
@@ -242,6 +243,22 @@ __device__ __forceinline__ float bilinear_win(uint32_t base, int first, float x,
   return (1.f - fy) * ((1.f - fx) * a + fx * b) + fy * ((1.f - fx) * c + fx * d);
 }
 
+// The same from a window whose pixel (0, 0) would be at LDS byte address
+// `origin` (its LDS address less y kWinW + x of its first pixel), for a sample
+// known to lie in the window. (Aligned dwords and a byte shift: unaligned LDS
+// loads are two instructions less, and one kernel of 21,432 items of 4 levels
+// took 277 us with them instead of 187.)
+__device__ __forceinline__ float bilinear_in_win(uint32_t origin, float x, float y) {
+  const float fx = fract(x), fy = fract(y);
+  const uint32_t o = window_offset(trunc_i(x), trunc_i(y)) + origin;
+  const lds_words p = (lds_words)(uintptr_t)(o & ~3u);
+  const uint32_t r0 = __builtin_amdgcn_alignbyte(p[1], p[0], o);
+  const uint32_t r1 = __builtin_amdgcn_alignbyte(p[kWinW / 4 + 1], p[kWinW / 4], o);
+  const float a = (float)(r0 & 0xFFu), b = (float)((r0 >> 8) & 0xFFu), c = (float)(r1 & 0xFFu),
+              d = (float)((r1 >> 8) & 0xFFu);
+  return (1.f - fy) * ((1.f - fx) * a + fx * b) + fy * ((1.f - fx) * c + fx * d);
+}
+
 // Template samples at (x, y): I(x, y) and the central differences
 // (I(x+1, y) - I(x-1, y)) / 2, (I(x, y+1) - I(x, y-1)) / 2, all bilinear as
 // above. They share the 4x4 pixels from (floor(x) - 1, floor(y) - 1) and the
@@ -272,7 +289,8 @@ __device__ __forceinline__ Window4 template_load(const Level& I, float x, float 
   const uint32_t pt = (uint32_t)I.pitch;
   return {{ld32(I.p, o), ld32(I.p, o + pt), ld32(I.p, o + 2u * pt), ld32(I.p, o + 3u * pt)}};
 }
-// the 4x4 pixels from the window at `base` (see bilinear_win)
+// the 4x4 pixels from the window at `base` whose first pixel is byte -`first`
+// (y kWinW + x); the address stays in the window for any (x, y)
 __device__ __forceinline__ Window4 template_win(uint32_t base, int first, float x, float y) {
   const uint32_t o = window_offset(trunc_i(x), trunc_i(y)) - (uint32_t)(first + kWinW + 1);
   const lds_words p = (lds_words)(uintptr_t)((o & (uint32_t)(kWinBytes - 4)) | base);
@@ -1150,207 +1168,419 @@ __device__ __forceinline__ void process_item(const CamDesc* __restrict__ cams, c
 // Half h = lane / 32 of the wave tracks one keypoint; lane g = lane mod 32 of a
 // half holds pattern points g (index 0 of the per-lane arrays) and g + 32
 // (index 1; weight 0 from g = 20 on, where the index passes the 52 points).
+// With the chip full the tracker is bound by instruction issue, and everything
+// but the samples and their first sums is issued once for the two keypoints.
 // Per keypoint the steps, decisions and arithmetic are those of klt_pass, and
 // the sums over the pattern run through the same tree (half_sums), so a half
 // computes what one wave computes for the same keypoint, bit for bit. Levels,
 // iterations and descriptors are the wave's; `act` (uniform across each half)
 // says which halves run the pass. A half that leaves the procedure keeps its
-// status and idles (its loads masked off) while the other half goes on.
-// level_sums for two keypoints per wave: out[K l + k] <- the half's total of
-// value k of level l, gen(K l + k, point) giving each lane's two values.
-template <int L, int K, int l = 0, class Gen>
-__device__ __forceinline__ void level_pair_sums2(float* out, const Gen& gen, int nl, int lane) {
-  if constexpr (l < L) {
-    if (l < nl) half_sums_of<(l + 1 < L ? 2 : 1) * K, K * l>(out, gen, lane);
-    level_pair_sums2<L, K, l + 2>(out, gen, nl, lane);
+// status and computes on, unused (its addresses stay in its windows, whatever
+// its numbers), while the other half goes on.
+// The levels run one after the other, template and all: four waves to a SIMD
+// overlap their loads and chains without the registers of all levels at once
+// (L = 4: 225 -> 127, two waves to a SIMD -> four). 21,432 items of 4 levels
+// x 5 iterations: 197 us with samples gathered from global memory, 203 with
+// windows and the templates of all levels at once, 159 so, of which 143 are
+// vector issue; k_track 187, all of it issue (5,387 vector instructions an item,
+// 3,990 here).
+
+// One Gauss-Newton step. Its half-uniform math runs in the lanes of each quad, so
+// that one instruction does for both coordinates: x in the even lanes, y in the
+// odd ones (klt_pass with it: 91 -> 73 vector instructions in an iteration, 187
+// -> 178 us for 21,432 items of 4 levels, but 22.0 -> 22.5 us for 950, whose one
+// wave per SIMD waits for the lane exchanges; so it keeps scalars).
+struct Pose {
+  float t;       // translation: x in even lanes, y in odd ones
+  float th, cs, sn;  // rotation and its cosine and sine, in every lane
+};
+// Lane constants: of the series of the SE(2) exponential (even lanes: that of
+// a = sin(phi)/phi, odd ones: of b/phi, b = (1 - cos(phi))/phi), and a sign.
+struct StepLanes {
+  float c0, c1, c2, c3, sign, i52;
+  bool odd;
+};
+__device__ __forceinline__ StepLanes step_lanes(int lane) {
+  const bool odd = lane & 1;
+  StepLanes c{odd ? 0.5f : 1.f, odd ? 1.f / 24.f : 1.f / 6.f, odd ? 1.f / 720.f : 1.f / 120.f,
+              odd ? 1.f / 40320.f : 1.f / 5040.f, odd ? 1.f : -1.f, 1.f / 52.f, odd};
+  asm("" : "+v"(c.sign), "+v"(c.i52));  // (factors in registers, so that a lane exchange is part of the product)
+  return c;
+}
+// (k0, k1, k2) in lanes 1, 2, 3 of every quad
+__device__ __forceinline__ float step_target(float k0, float k1, float k2, int lane) {
+  const int j = lane & 3;
+  return j == 1 ? k0 : j == 2 ? k1 : k2;
+}
+// An unusable rotation (an infinite or undefined angle) leaves an undefined
+// position, which no window and no image contains.
+__device__ __forceinline__ void pose_check(Pose& p) {
+  if (!(fabsf(p.cs) < 2.f)) p.t = __builtin_nanf("");
+}
+// The step delta = k - S / mean': S4 holds (sum I', sums G_i I') in lanes 0..3
+// of every quad, k its target in lanes 1..3. The pose is composed with the SE(2)
+// exponential of delta = (d0, d1, phi), whose translation is V(phi) (d0, d1) with
+// V = [[a, -b], [b, a]]. `live` lanes' results count. Returns 1 / mean' and, in
+// mw_min, the smallest mean's bits so far (a mean of pixels is never negative).
+__device__ __forceinline__ float gn_step(Pose& p, float S4, float k, const StepLanes& c, uint32_t& mw_min,
+                                         bool live) {
+  const float mw = quad<0>(S4) * c.i52;
+  mw_min = min(mw_min, __float_as_uint(mw));
+  const float imw = rcp(mw);
+  const float d = k - S4 * imw;
+  const float phi = quad<3>(d);
+  // the next iteration's sine and cosine need only phi: they run beside the
+  // exponential below
+  float R2 = c.odd ? p.sn : p.cs, Q2 = c.odd ? p.cs : -p.sn;
+  p.th = p.th + phi;
+  asm("" : "+v"(p.th), "+v"(R2), "+v"(Q2));  // (the old sine and cosine have been read: no copies of the new)
+  p.cs = __cosf(p.th);
+  p.sn = __sinf(p.th);
+  asm("" : "+v"(p.cs), "+v"(p.sn));  // (keeps them ahead of the branch below)
+  const float p2 = phi * phi;
+  // series, error below 2e-9 for |phi| < 0.25; R: a in even lanes, b in odd ones
+  float R = (c.c0 - p2 * (c.c1 - p2 * (c.c2 - p2 * c.c3))) * (c.odd ? phi : 1.f);
+  const bool small = fabsf(phi) < 0.25f;
+  if (__builtin_expect(wave_any(!small & live), 0)) {
+    const float ip = rcp(phi);
+    const float a = __sinf(phi) * ip, b = (1.f - __cosf(phi)) * ip;
+    R = small ? R : c.odd ? b : a;
+    pose_check(p);
+  }
+  // (a d0 - b d1, b d0 + a d1), then (cs vx - sn vy, sn vx + cs vy)
+  const float d1 = quad<1, 0, 3, 2>(R) * c.sign * quad<2>(d);
+  const float v = R * quad<1>(d) + d1;
+  const float v1 = Q2 * quad<1, 1, 3, 3>(v);
+  const float w = R2 * quad<0, 0, 2, 2>(v) + v1;
+  p.t = p.t + w;
+  return imw;
+}
+// a patch's samples around a position lie within this distance of it in each
+// coordinate (the pattern's radius is 3.81)
+constexpr float kPatchReach = 3.875f;
+
+// Lane l of every row holds level l's value of its half: l's value to all lanes.
+template <int l>
+__device__ __forceinline__ int row_lane(int v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + l, 0xF, 0xF, false);
+}
+template <int l>
+__device__ __forceinline__ float row_lane(float v) {
+  return __builtin_bit_cast(float, row_lane<l>(__builtin_bit_cast(int, v)));
+}
+// Sum i of M that klt_pass takes together: the quad parity of the lane it is
+// read from (wave_sums of M), which decides the order of the quads' sums.
+constexpr int sum_parity(int M, int i) {
+  for (;;) {
+    const int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
+    if (i < C) return C >= 8 ? (i >> 2) & 1 : 0;
+    i -= C;
+    M -= C;
   }
 }
-template <int L, int K, class Gen>
-__device__ __forceinline__ void level_sums2(float* out, const Gen& gen, int nl, int lane) {
-  if (nl >= L) half_sums_of<K * L, 0>(out, gen, lane);
-  else level_pair_sums2<L, K>(out, gen, nl, lane);
+// out[m0 + i] <- sum i of x's C from a quad of the right parity
+template <int MF, int MP, int OF, int OP, int m0, int C, int i>
+__device__ __forceinline__ void level_sum_pick(float* out, float x, bool full) {
+  if constexpr (i < C) {
+    constexpr int lf = 4 * sum_parity(MF, OF + m0 + i) + i, lp = 4 * sum_parity(MP, OP + m0 + i) + i;
+    const float f = dpp_mov<0x150 + lf>(x);
+    out[m0 + i] = f;
+    if constexpr (lp != lf) {
+      const float p = dpp_mov<0x150 + lp>(x);
+      out[m0 + i] = full ? f : p;
+    }
+    level_sum_pick<MF, MP, OF, OP, m0, C, i + 1>(out, x, full);
+  }
+}
+// level_sums of klt_pass for level l alone and two keypoints per wave, bit for
+// bit: out[m] <- the half's total of value m of K, gen(m, q) giving each lane's
+// two values. In chunks of four, two and one, whose sums every quad holds;
+// `full`: all L levels' sums are one call there, else those of level pairs.
+template <int K, int L, int l, int m0 = 0, class Gen>
+__device__ __forceinline__ void level_sums2(float* out, const Gen& gen, bool full, int lane) {
+  if constexpr (m0 < K) {
+    constexpr int C = K - m0 >= 4 ? 4 : K - m0 >= 2 ? 2 : 1;
+    float w[2][C];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < C; ++i) w[q][i] = gen(m0 + i, q);
+    const float x = rowswap_sum16(row_sums_pow2<C>(w[0], lane) + row_sums_pow2<C>(w[1], lane));
+    constexpr int pair = (l & ~1) + 1 < L ? 2 : 1;
+    level_sum_pick<K * L, K * pair, K * l, K * (l & 1), m0, C, 0>(out, x, full);
+    level_sums2<K, L, l, m0 + C>(out, gen, full, lane);
+  }
+}
+// f(level) for levels L-1 .. 0 as compile-time constants
+template <int l>
+using LevelNo = std::integral_constant<int, l>;
+template <int L, class F>
+__device__ __forceinline__ void each_level_down(const F& f) {
+  if constexpr (L > 0) {
+    f(LevelNo<L - 1>{});
+    each_level_down<L - 1>(f);
+  }
 }
 
+// The windows of half h, image i, level l: window (2 i + h) L + l of the wave's.
 template <int L>
 __device__ __forceinline__ PassOut klt_pass2(const CamDesc& csrc_in, int ssrc_in, const CamDesc& cdst_in, int sdst_in,
                                              float px, float py, float ix, float iy, float ith, int nl_in, int N_in,
-                                             const float* u, const float* v, float wb, bool act, int lane) {
+                                             const float* u, const float* v, float wb, bool act, int lane,
+                                             bool fresh, lds_words sw, Windows& ws, lds_words dw, Windows& wd) {
   // point g < 32 is always one of the 52: its weight is 1
   const float wgt[2] = {1.f, wb};
   const cdesc_k csrc = (cdesc_k)uniform_ptr(&csrc_in);
   const cdesc_k cdst = (cdesc_k)uniform_ptr(&cdst_in);
-  const int ssrc = __builtin_amdgcn_readfirstlane(ssrc_in), sdst = __builtin_amdgcn_readfirstlane(sdst_in);
-  const int nl = __builtin_amdgcn_readfirstlane(nl_in), N = __builtin_amdgcn_readfirstlane(N_in);
+  const int ssrc = uniform(ssrc_in), sdst = uniform(sdst_in);
+  const int nl = uniform(nl_in), N = uniform(N_in);
+  const int lv = lane & 7;
   PassOut o{VIO_TRACKED, 0.f, 0.f, 0.f, 0.f};
   bool live = act;  // the half is still in the procedure
-  // ---- templates of all levels (Sec. III-E) ------------------------------
-  bool fits[L], valid[L];
-  float T[L][2], G0[L][2], G1[L][2], G2[L][2], k[3 * L];
-  float I0[L][2], gxr[L][2], gyr[L][2];
+  // ---- the windows (as in klt_pass, lane l of a half on level l) -----------
+  const int src_w = csrc->w, src_h = csrc->h, dst_w = cdst->w, dst_h = cdst->h;
+  uint64_t fit;  // bit 32 h + l
+  {
+    gbytes sp[L], dp[L];
 #pragma unroll
-  for (int l = 0; l < L; ++l) {
-    fits[l] = false;
+    for (int l = 0; l < L; ++l) {
+      sp[l] = (gbytes)csrc->lvl[ssrc][l];
+      dp[l] = (gbytes)cdst->lvl[sdst][l];
+    }
+    const float sc = ldexpf(1.f, -lv);
+    const int sw_l = src_w >> lv, sh_l = src_h >> lv;
+    const float cx = px * sc, cy = py * sc;
+    const float x0 = cx - 3.5f, x1 = cx + 3.5f, y0 = cy - 3.5f, y1 = cy + 3.5f;
+    fit = __builtin_amdgcn_ballot_w64((x0 - 1.f >= 0.f) & (x1 + 1.f <= (float)(sw_l - 1)) & (y0 - 1.f >= 0.f) &
+                                      (y1 + 1.f <= (float)(sh_l - 1)));
+    const bool have = (!fresh) & (x0 - 1.f >= (float)ws.x) & (x1 + 3.f <= (float)(ws.x + kWinW)) &
+                      (y0 - 1.f >= (float)ws.y) & (y1 + 3.f <= (float)(ws.y + kWinH));
+    const uint64_t need = __builtin_amdgcn_ballot_w64(act & !have);
+    const Windows at = window_around(sw_l, sh_l, cx, cy);
+    ws.x = have ? ws.x : at.x;
+    ws.y = have ? ws.y : at.y;
+    if (fresh) wd = window_around(dst_w >> lv, dst_h >> lv, ix * sc, iy * sc);
+    const uint64_t levels = ((1ull << nl) - 1ull) * 0x100000001ull;
+    if ((need & levels) != 0) {
+      const WinTask wt = window_task(lane);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) I0[l][q] = gxr[l][q] = gyr[l][q] = 0.f;
-    if (l < nl) {
-      const Level S = level_of(csrc, ssrc, l);
-      const float sc = 1.f / (float)(1 << l);
-      float sx[2], sy[2];
-      bool in = true;
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t nh = (uint32_t)((need & levels) >> (32 * h));
+        if (nh == 0) continue;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        sx[q] = px * sc + u[q];
-        sy[q] = py * sc + v[q];
-        in = in & in_dom(S, sx[q] - 1.f, sy[q]) & in_dom(S, sx[q] + 1.f, sy[q]) & in_dom(S, sx[q], sy[q] - 1.f) &
-             in_dom(S, sx[q], sy[q] + 1.f);
+        for (int l = 0; l < L; ++l)
+          if ((nh >> l) & 1)
+            window_load(sp[l], src_w >> l, src_h >> l, lane_of(ws.x, 32 * h + l), lane_of(ws.y, 32 * h + l),
+                        sw + kWinWords * (h * L + l), wt);
+        if (fresh) {
+#pragma unroll
+          for (int l = 0; l < L; ++l)
+            if (l < nl)
+              window_load(dp[l], dst_w >> l, dst_h >> l, lane_of(wd.x, 32 * h + l), lane_of(wd.y, 32 * h + l),
+                          dw + kWinWords * (h * L + l), wt);
+        }
       }
-      fits[l] = half_all(in, lane) && live;
-      if (fits[l]) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          template_samples(template_load(S, sx[q], sy[q]), fract(sx[q]), fract(sy[q]), I0[l][q], gxr[l][q], gyr[l][q]);
-      }
+      window_wait();
     }
   }
-  float mean[L];
-  level_sums2<L, 1>(mean, [&](int l, int q) { return wgt[q] * I0[l][q]; }, nl, lane);
-  float J0[L][2], J1[L][2], J2[L][2];
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    mean[l] *= 1.f / 52.f;
-    const float im = rcp(mean[l]);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      T[l][q] = I0[l][q] * im;
-      J0[l][q] = gxr[l][q] * im;
-      J1[l][q] = gyr[l][q] * im;
-      J2[l][q] = J1[l][q] * u[q] - J0[l][q] * v[q];
-    }
-  }
-  // H_l = sum w J^T J: (00, 01, 02, 11, 12, 22) of level l at 6 l .. 6 l + 5
-  float hs[6 * L];
-  level_sums2<L, 6>(
-      hs,
-      [&](int i, int q) {
-        const int l = i / 6, m = i % 6;
-        const float a = m < 3 ? J0[l][q] : m < 5 ? J1[l][q] : J2[l][q];
-        const float b = m == 0 ? J0[l][q] : m == 1 || m == 3 ? J1[l][q] : J2[l][q];
-        return wgt[q] * a * b;
-      },
-      nl, lane);
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    valid[l] = false;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) G0[l][q] = G1[l][q] = G2[l][q] = 0.f;
-    if (l >= nl) continue;  // a level the pass does not visit
-    const float h00 = hs[6 * l + 0], h01 = hs[6 * l + 1], h02 = hs[6 * l + 2];
-    const float h11 = hs[6 * l + 3], h12 = hs[6 * l + 4], h22 = hs[6 * l + 5];
-    // 3x3 inverse by cofactors (H symmetric); degenerate when det <= 1e-6 (tr/3)^3
-    const float c00 = h11 * h22 - h12 * h12;
-    const float c01 = h12 * h02 - h01 * h22;
-    const float c02 = h01 * h12 - h11 * h02;
-    const float det = h00 * c00 + h01 * c01 + h02 * c02;
-    const float tr3 = (h00 + h11 + h22) * (1.f / 3.f);
-    const float id = rcp(det);
-    const float i00 = c00 * id, i01 = c01 * id, i02 = c02 * id;
-    const float i11 = (h00 * h22 - h02 * h02) * id;
-    const float i12 = (h02 * h01 - h00 * h12) * id;
-    const float i22 = (h00 * h11 - h01 * h01) * id;
-    bool fin = true;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      G0[l][q] = wgt[q] * (i00 * J0[l][q] + i01 * J1[l][q] + i02 * J2[l][q]);
-      G1[l][q] = wgt[q] * (i01 * J0[l][q] + i11 * J1[l][q] + i12 * J2[l][q]);
-      G2[l][q] = wgt[q] * (i02 * J0[l][q] + i12 * J1[l][q] + i22 * J2[l][q]);
-      fin = fin & isfinite(G0[l][q]) & isfinite(G1[l][q]) & isfinite(G2[l][q]);
-    }
-    valid[l] = mean[l] > 0.f && det > 1e-6f * tr3 * tr3 * tr3 && half_all(fin, lane);
-  }
-  // c_l = sum G_i T_i
-  level_sums2<L, 3>(
-      k,
-      [&](int i, int q) {
-        const int l = i / 3, m = i % 3;
-        return (m == 0 ? G0[l][q] : m == 1 ? G1[l][q] : G2[l][q]) * T[l][q];
-      },
-      nl, lane);
+  const uint32_t half_off = (uint32_t)((lane >> 5) * (kWinBytes * L));
+  const uint32_t sbase = (uint32_t)uniform((int)(uint32_t)(uintptr_t)sw) + half_off;
+  const uint32_t dbase = (uint32_t)uniform((int)(uint32_t)(uintptr_t)dw) + half_off;
   // ---- coarse-to-fine Gauss-Newton (eqs. 4-5) ------------------------------
-  float tx = ldexpf(ix, 1 - nl), ty = ldexpf(iy, 1 - nl), th = ith;
-#pragma unroll
-  for (int l = L - 1; l >= 0; --l) {
-    if (l >= nl) continue;
-    if (l < nl - 1) {
-      tx = tx * 2.f;
-      ty = ty * 2.f;
-    }
+  const StepLanes sl = step_lanes(lane);
+  const bool odd = sl.odd;
+  Pose p{ldexpf(odd ? iy : ix, 1 - nl), ith, __cosf(ith), __sinf(ith)};
+  pose_check(p);
+  // lane l of a half: positions all of whose samples lie in level l's window (and so in the image)
+  float vlox, vhix, vloy, vhiy;
+  const auto bounds = [&] {
+    vlox = (float)max(wd.x, 0) + kPatchReach;
+    vhix = (float)min(wd.x + kWinW - 2, (dst_w >> lv) - 1) - kPatchReach;
+    vloy = (float)max(wd.y, 0) + kPatchReach;
+    vhiy = (float)min(wd.y + kWinH - 2, (dst_h >> lv) - 1) - kPatchReach;
+  };
+  bounds();
+  bool ended = false;  // no half is left in the procedure
+  each_level_down<L>([&](auto level) {
+    constexpr int l = decltype(level)::value;
+    if (ended || l >= nl) return;
+    if (l < nl - 1) p.t = p.t * 2.f;
+    const bool fits = __builtin_amdgcn_inverse_ballot_w64(half_mask((fit >> l) & 1, (fit >> (32 + l)) & 1));
     // a level whose template does not fit is skipped, and at level 0 the track is lost
-    if (live && !fits[l] && l == 0) {
+    if (l == 0 && live && !fits) {
       o.status = VIO_LOST_OOB;
       live = false;
     }
-    if (live && fits[l] && !valid[l]) {
-      o.status = VIO_LOST_DEGENERATE;
-      live = false;
-    }
-    bool run = live && fits[l];
+    bool run = live && fits;
     if (!wave_any(run)) {
-      if (!wave_any(live)) break;
-      continue;
+      ended = !wave_any(live);
+      return;
     }
-    const Level D = level_of(cdst, sdst, l);
-    for (int it = 0; it < N; ++it) {
-      const float cs = __cosf(th), sn = __sinf(th);
-      float wx[2], wy[2];
-      bool in = true;
+    // ---- the level's template (Sec. III-E), the arithmetic of klt_pass -------
+    const bool full = nl >= L;
+    float T[2], G0[2], G1[2], G2[2], k[3];
+    {
+      float I0[2], gxr[2], gyr[2], mean[1], hs[6];
+      const float sc = 1.f / (float)(1 << l);
+      const int sfirst = row_lane<l>(ws.y * kWinW + ws.x);
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        wx[q] = (cs * u[q] - sn * v[q]) + tx;
-        wy[q] = (sn * u[q] + cs * v[q]) + ty;
-        in = in & in_dom(D, wx[q], wy[q]);
+        const float sx = px * sc + u[q], sy = py * sc + v[q];
+        template_samples(template_win(sbase + kWinBytes * l, sfirst, sx, sy), fract(sx), fract(sy), I0[q], gxr[q],
+                         gyr[q]);
       }
-      if (half_any(!in, lane) && run) {
-        o.status = VIO_LOST_OOB;
-        live = run = false;
-      }
-      if (!wave_any(run)) break;
-      float Iw[2] = {0.f, 0.f};
-      if (run) {
+      level_sums2<1, L, l>(mean, [&](int, int q) { return wgt[q] * I0[q]; }, full, lane);
+      mean[0] *= 1.f / 52.f;
+      const float im = rcp(mean[0]);
+      float J0[2], J1[2], J2[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) Iw[q] = bilinear(D, wx[q], wy[q]);
+      for (int q = 0; q < 2; ++q) {
+        T[q] = I0[q] * im;
+        J0[q] = gxr[q] * im;
+        J1[q] = gyr[q] * im;
+        J2[q] = J1[q] * u[q] - J0[q] * v[q];
       }
-      float S[4] = {wgt[0] * Iw[0], G0[l][0] * Iw[0], G1[l][0] * Iw[0], G2[l][0] * Iw[0]};
-      const float Sb[4] = {wgt[1] * Iw[1], G0[l][1] * Iw[1], G1[l][1] * Iw[1], G2[l][1] * Iw[1]};
-      half_sums<4>(S, Sb, lane);
-      const float mw = S[0] * (1.f / 52.f);
-      if (run && !(mw > 0.f)) {
-        o.status = VIO_LOST_OOB;
-        live = run = false;
+      level_sums2<6, L, l>(
+          hs,
+          [&](int m, int q) {
+            const float a = m < 3 ? J0[q] : m < 5 ? J1[q] : J2[q];
+            const float b = m == 0 ? J0[q] : m == 1 || m == 3 ? J1[q] : J2[q];
+            return wgt[q] * a * b;
+          },
+          full, lane);
+      const float h00 = hs[0], h01 = hs[1], h02 = hs[2], h11 = hs[3], h12 = hs[4], h22 = hs[5];
+      const float c00 = h11 * h22 - h12 * h12;
+      const float c01 = h12 * h02 - h01 * h22;
+      const float c02 = h01 * h12 - h11 * h02;
+      const float det = h00 * c00 + h01 * c01 + h02 * c02;
+      const float tr3 = (h00 + h11 + h22) * (1.f / 3.f);
+      const float id = rcp(det);
+      const float i00 = c00 * id, i01 = c01 * id, i02 = c02 * id;
+      const float i11 = (h00 * h22 - h02 * h02) * id;
+      const float i12 = (h02 * h01 - h00 * h12) * id;
+      const float i22 = (h00 * h11 - h01 * h01) * id;
+      bool fin = true;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        G0[q] = wgt[q] * (i00 * J0[q] + i01 * J1[q] + i02 * J2[q]);
+        G1[q] = wgt[q] * (i01 * J0[q] + i11 * J1[q] + i12 * J2[q]);
+        G2[q] = wgt[q] * (i02 * J0[q] + i12 * J1[q] + i22 * J2[q]);
+        fin = fin & isfinite(G0[q]) & isfinite(G1[q]) & isfinite(G2[q]);
       }
-      const float imw = rcp(mw);
-      if (l == 0 && it == N - 1) {
-        const float e0 = Iw[0] * imw - T[l][0], e1 = Iw[1] * imw - T[l][1];
-        const float rs = sqrtf(half_sum(wgt[0] * e0 * e0, wgt[1] * e1 * e1, lane) * (1.f / 52.f));
-        if (run) o.resid = rs;
+      const bool valid = half_all((mean[0] > 0.f) & (det > 1e-6f * tr3 * tr3 * tr3) & fin, lane);
+      level_sums2<3, L, l>(
+          k, [&](int m, int q) { return (m == 0 ? G0[q] : m == 1 ? G1[q] : G2[q]) * T[q]; }, full, lane);
+      if (run && !valid) {
+        o.status = VIO_LOST_DEGENERATE;
+        run = live = false;
       }
-      const float d0 = k[3 * l + 0] - S[1] * imw, d1 = k[3 * l + 1] - S[2] * imw, d2 = k[3 * l + 2] - S[3] * imw;
-      float a, b;
-      se2_v(d2, fabsf(d2) < 0.25f, a, b);
-      const float vx = a * d0 - b * d1, vy = b * d0 + a * d1;
-      const float ntx = tx + (cs * vx - sn * vy);
-      const float nty = ty + (sn * vx + cs * vy);
-      const float nth = th + d2;
-      if (run) {
-        tx = ntx;
-        ty = nty;
-        th = nth;
+      if (!wave_any(run)) {
+        ended = !wave_any(live);
+        return;
       }
     }
-    if (!wave_any(live)) break;
-  }
-  o.tx = tx;
-  o.ty = ty;
-  o.th = th;
+    // positions that have moved away from their window's middle take a new one
+    {
+      // (exchanges between lanes stay out of lane-dependent branches)
+      const int wxl = row_lane<l>(wd.x), wyl = row_lane<l>(wd.y);
+      const float wf = (float)(odd ? wyl : wxl);
+      const uint64_t off = __builtin_amdgcn_ballot_w64(
+          run & !((p.t - 6.f >= wf) & (p.t - (odd ? kWinH - 8.f : kWinW - 8.f) <= wf)));
+      if (off != 0) {
+        const Level D = level_of(cdst, sdst, l);
+        bool loaded = false;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if ((uint32_t)(off >> (32 * h)) == 0) continue;
+          const Windows q = window_around(D.w, D.h, lane_of(p.t, 32 * h), lane_of(p.t, 32 * h + 1));
+          const int x = uniform(q.x), y = uniform(q.y);
+          if ((x != lane_of(wd.x, 32 * h + l)) | (y != lane_of(wd.y, 32 * h + l))) {
+            wd.x = (lv == l) & ((lane >> 5) == h) ? x : wd.x;
+            wd.y = (lv == l) & ((lane >> 5) == h) ? y : wd.y;
+            window_load(D.p, D.w, D.h, x, y, dw + kWinWords * (h * L + l), window_task(lane));
+            loaded = true;
+          }
+        }
+        if (loaded) {
+          bounds();
+          window_wait();
+        }
+      }
+    }
+    const float lox = row_lane<l>(vlox), hix = row_lane<l>(vhix), loy = row_lane<l>(vloy), hiy = row_lane<l>(vhiy);
+    const float lo = odd ? loy : lox, hi = odd ? hiy : hix;
+    const uint32_t origin = dbase + kWinBytes * l - (uint32_t)row_lane<l>(wd.y * kWinW + wd.x);
+    // the gains, selected for the sums' first exchange stage (see klt_pass)
+    float keep0[2], send0[2], keep1[2], send1[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      keep0[q] = odd ? G0[q] : wgt[q];
+      send0[q] = odd ? wgt[q] : G0[q];
+      keep1[q] = odd ? G2[q] : G1[q];
+      send1[q] = odd ? G1[q] : G2[q];
+    }
+    const float target = step_target(k[0], k[1], k[2], lane);
+    const Pose before = p;
+    uint32_t mw_min = 0xFFFFFFFFu;
+    float Iw[2] = {0.f, 0.f}, imw = 0.f;
+#pragma unroll 1
+    for (int it = 0; it < N; ++it) {
+      const float tx = quad<0, 0, 2, 2>(p.t), ty = quad<1, 1, 3, 3>(p.t);
+      float wx[2], wy[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        wx[q] = (p.cs * u[q] - p.sn * v[q]) + tx;
+        wy[q] = (p.sn * u[q] + p.cs * v[q]) + ty;
+      }
+      // (even and odd lanes hold a half's x and y)
+      const uint64_t in = __builtin_amdgcn_ballot_w64(p.t >= lo) & __builtin_amdgcn_ballot_w64(p.t <= hi);
+      if (__builtin_expect(in == ~0ull, 1)) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) Iw[q] = bilinear_in_win(origin, wx[q], wy[q]);
+      } else {
+        const Level far = level_of(cdst, sdst, l);
+        const bool win = __builtin_amdgcn_inverse_ballot_w64(half_mask((uint32_t)in == ~0u, (uint32_t)(in >> 32) == ~0u));
+        const bool dom = half_all(in_dom(far, wx[0], wy[0]) & in_dom(far, wx[1], wy[1]), lane);
+        Iw[0] = Iw[1] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if (win) Iw[q] = bilinear_in_win(origin, wx[q], wy[q]);
+          if (run & !win & dom) Iw[q] = bilinear(far, wx[q], wy[q]);
+        }
+        if (run & !win & !dom) {
+          mw_min = 0u;
+          run = false;
+        }
+      }
+      float a0[2], b0[2], a1[2], b1[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        a0[q] = keep0[q] * Iw[q];
+        b0[q] = send0[q] * Iw[q];
+        a1[q] = keep1[q] * Iw[q];
+        b1[q] = send1[q] * Iw[q];
+      }
+      imw = gn_step(p, half_sums4_paired(a0, b0, a1, b1, lane), target, sl, mw_min, run);
+    }
+    // a sample outside the image, or a mean that was not positive, ends the track
+    if (live && fits && mw_min == 0u) {
+      o.status = VIO_LOST_OOB;
+      live = false;
+    }
+    if (l == 0) {
+      const float e0 = Iw[0] * imw - T[0], e1 = Iw[1] * imw - T[1];
+      o.resid = sqrtf(half_sum(wgt[0] * e0 * e0, wgt[1] * e1 * e1, lane) * (1.f / 52.f));
+    }
+    // a half whose template did not fit has not moved
+    p.t = fits ? p.t : before.t;
+    p.th = fits ? p.th : before.th;
+    p.cs = fits ? p.cs : before.cs;
+    p.sn = fits ? p.sn : before.sn;
+    ended = !wave_any(live);
+  });
+  o.tx = quad<0>(p.t);
+  o.ty = quad<1>(p.t);
+  o.th = p.th;
   return o;
 }
 
@@ -1359,7 +1589,8 @@ __device__ __forceinline__ PassOut klt_pass2(const CamDesc& csrc_in, int ssrc_in
 template <int L>
 __device__ __forceinline__ TrackRes track_fb2(const CamDesc& csrc, int ssrc, const CamDesc& cdst, int sdst, float px,
                                               float py, float ix, float iy, float ith, int nl, int N, float fb_thr,
-                                              const float* u, const float* v, float wb, bool act, int lane) {
+                                              const float* u, const float* v, float wb, bool act, int lane,
+                                              lds_words win) {
   TrackRes r;
   r.x = ix;
   r.y = iy;
@@ -1373,10 +1604,15 @@ __device__ __forceinline__ TrackRes track_fb2(const CamDesc& csrc, int ssrc, con
   int sa = ssrc, sb = sdst;
   float qx = px, qy = py, gx = ix, gy = iy, gth = ith;
   bool run = act;
+  Windows wa{}, wz{};
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {
     if (!wave_any(run)) break;
-    const PassOut o = klt_pass2<L>(*A, sa, *B, sb, qx, qy, gx, gy, gth, nl, N, u, v, wb, run, lane);
+    const PassOut o = klt_pass2<L>(*A, sa, *B, sb, qx, qy, gx, gy, gth, nl, N, u, v, wb, run, lane, pass == 0,
+                                   win + pass * (2 * L * kWinWords), wa, win + (1 - pass) * (2 * L * kWinWords), wz);
+    const Windows wt = wa;
+    wa = wz;
+    wz = wt;
     const bool ok = run && o.status == VIO_TRACKED;
     if (run && !ok) r.status = o.status;
     if (pass == 0) {
@@ -1452,7 +1688,7 @@ __device__ __forceinline__ void process_pair(const CamDesc* __restrict__ cams, c
                                              const Counters* __restrict__ cnt, const TrackSeg* __restrict__ segs,
                                              int n_segs, const Prediction* __restrict__ pred, const Tuning& tune,
                                              int item, bool item_in_range, int lane, const float* u, const float* v,
-                                             float wb, Plan* sp) {
+                                             float wb, lds_words win, Plan* sp) {
   {
     const Plan pl =
         plan_item<false, kW / 2>(cams, frame, cnt, segs, n_segs, pred, tune, item, item_in_range, lane, nullptr);
@@ -1483,7 +1719,7 @@ __device__ __forceinline__ void process_pair(const CamDesc* __restrict__ cams, c
       const TrackRes t = track_fb2<L>(*ph.src, ph.ssrc, *ph.dst, ph.sdst, me.px, me.py, short_run ? me.gx : me.ix,
                                       short_run ? me.gy : me.iy, short_run ? me.gth : me.ith,
                                       short_run ? ph.sl : ph.fl, short_run ? ph.si : ph.fi, tune.fb_threshold, u, v,
-                                      wb, act, lane);
+                                      wb, act, lane, win);
       if (act) r = t;
     }
     if (short_run && want) {
@@ -1560,7 +1796,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamD
 // Two work items per wave (the throughput shape for many items): wave k runs
 // items 2k (half 0) and 2k + 1 (half 1).
 template <int L>
-__global__ __launch_bounds__(kW* kTrackWaves) void k_track2(const CamDesc* __restrict__ cams,
+__global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_track2(const CamDesc* __restrict__ cams,
                                                            const FrameTable* __restrict__ frame,
                                                            const Counters* __restrict__ cnt,
                                                            const TrackSeg* __restrict__ segs, int n_segs,
@@ -1569,13 +1805,14 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2(const CamDesc* __res
   const int lane = threadIdx.x & (kW - 1);
   const int k = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (int)(blockDim.x / kW) + (int)(threadIdx.x / kW));
   if (2 * k >= n_items) return;
+  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L, 2>];
   __shared__ Plan sPlan[kTrackWaves][2];
   float u[2], v[2], w0, wb;
   pattern_of(lane & 31, u[0], v[0], w0);
   pattern_of((lane & 31) + 32, u[1], v[1], wb);
   const int it = 2 * k + (lane >> 5);
   process_pair<L>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + it, it < n_items, lane, u, v, wb,
-                  sPlan[threadIdx.x / kW]);
+                  (lds_words)sWin + uniform((int)threadIdx.x / kW) * (4 * L * kWinWords), sPlan[threadIdx.x / kW]);
 }
 
 // The persistent grid with two items per wave: each pop takes two items.
@@ -1588,6 +1825,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const Cam
                                                                       const Prediction* __restrict__ pred,
                                                                       Tuning tune, int queue) {
   const int lane = threadIdx.x & (kW - 1);
+  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L, 2>];
   __shared__ Plan sPlan[kTrackWaves][2];
   float u[2], v[2], w0, wb;
   pattern_of(lane & 31, u[0], v[0], w0);
@@ -1597,7 +1835,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const Cam
     if (k >= n_items) break;
     const int it = k + (lane >> 5);
     process_pair<L>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + it, it < n_items, lane, u, v, wb,
-                    sPlan[threadIdx.x / kW]);
+                    (lds_words)sWin + uniform((int)threadIdx.x / kW) * (4 * L * kWinWords), sPlan[threadIdx.x / kW]);
     wave_sync_lds();  // the next item's plan overwrites this one's
   }
 }

@@ -91,6 +91,17 @@ __device__ __forceinline__ void wave_sums4_paired(float keep0, float send0, floa
     out[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
 }
 
+// The four values of a quad rearranged: lane i of every quad <- its lane qi.
+template <int q0, int q1, int q2, int q3>
+__device__ __forceinline__ float quad(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), q0 | q1 << 2 | q2 << 4 | q3 << 6,
+                                                            0xF, 0xF, true));
+}
+template <int q>
+__device__ __forceinline__ float quad(float v) {
+  return quad<q, q, q, q>(v);
+}
+
 // v[i] <- wave sum of v[i] for i < M, in chunks of 16, 8, 4, 2, 1
 template <int M>
 __device__ __forceinline__ void wave_sums(float* v, int lane) {
@@ -148,6 +159,29 @@ __device__ __forceinline__ void half_sums_pow2(float* a, const float* b, int lan
   row_broadcasts<N>(a, rowswap_sum16(row_sums_pow2<N>(a, lane) + row_sums_pow2<N>(b, lane)));
 }
 
+// A row's odd quads hold sums added in another order than the first one's; they
+// take their even neighbour's.
+__device__ __forceinline__ float even_quads(float x) {
+  const int i = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x114, 0xF, 0xA, false));  // row_shr:4
+}
+
+// wave_sums4_paired for two items per wave: index 0 of the arguments at position
+// g, index 1 at position g + 32. Returns, in lane j of every quad, sum j.
+__device__ __forceinline__ float half_sums4_paired(const float* keep0, const float* send0, const float* keep1,
+                                                   const float* send1, int lane) {
+  float row[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float w[2] = {keep0[q] + dpp<0xB1>(send0[q]), keep1[q] + dpp<0xB1>(send1[q])};
+    xstage<0x4E, 1, 2>(w, lane);
+    xstage<0x124, 2, 1>(w, lane);
+    xstage<0x128, 3, 1>(w, lane);
+    row[q] = w[0];
+  }
+  return even_quads(rowswap_sum16(row[0] + row[1]));
+}
+
 // a[i] <- half-wave totals of (a[i], b[i]) for i < M, chunked as wave_sums<M>
 template <int M>
 __device__ __forceinline__ void half_sums(float* a, const float* b, int lane) {
@@ -155,25 +189,6 @@ __device__ __forceinline__ void half_sums(float* a, const float* b, int lane) {
     constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
     half_sums_pow2<C>(a, b, lane);
     half_sums<M - C>(a + C, b + C, lane);
-  }
-}
-
-// out[i] <- half-wave totals of gen(i, 0) + gen(i, 1) for i in [OFF, OFF + M),
-// chunked and summed as half_sums (and so as wave_sums<M> on out + OFF), each
-// chunk's values made just before its stages (a's, then b's), so only one
-// chunk of one position is held at a time.
-template <int M, int OFF, class Gen>
-__device__ __forceinline__ void half_sums_of(float* out, const Gen& gen, int lane) {
-  if constexpr (M > 0) {
-    constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
-    float w[C];
-#pragma unroll
-    for (int i = 0; i < C; ++i) w[i] = gen(OFF + i, 0);
-    const float xa = row_sums_pow2<C>(w, lane);
-#pragma unroll
-    for (int i = 0; i < C; ++i) w[i] = gen(OFF + i, 1);
-    row_broadcasts<C>(out + OFF, rowswap_sum16(xa + row_sums_pow2<C>(w, lane)));
-    half_sums_of<M - C, OFF + C>(out, gen, lane);
   }
 }
 

@@ -1,7 +1,8 @@
 """The tracker's LDS windows: keypoints at and past the borders, starts far from
 the truth (windows that move, samples outside them) and small or odd levels.
-The one-keypoint kernels read windows, the two-keypoint kernels global memory:
-their records have to be the same, bit for bit."""
+The kernels of one and of two keypoints per wave leave their windows at
+different positions (each sample's, or any the patch could reach) and then read
+global memory: their records have to be the same, bit for bit."""
 import numpy as np
 import pytest
 
