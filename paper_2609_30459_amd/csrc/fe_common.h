@@ -188,6 +188,20 @@ struct Counters {
   int32_t sel_base[kMaxCams];
   int32_t n_sel[kMaxCams];
   int32_t n_pairs[2][kMaxCams];  // entries of CamDesc::pairs, [parity][target camera]
+  // selection: from a stream's camera group (by its detecting camera) to the next
+  // one, twice the next free identifier plus one; zero: not there yet
+  int64_t id_chain[kMaxCams];
+};
+
+// The selection's workgroups, one per camera group: a detecting camera (mono,
+// a pair's left, a star's first) and the cameras that receive its matches.
+struct SelectGroups {
+  int32_t n;
+  struct {
+    uint8_t cam;          // the detecting camera
+    uint8_t first, last;  // of its stream
+    uint8_t prev;         // the detecting camera of the stream's group before (unless first)
+  } g[kMaxCams];
 };
 
 // Per-keypoint inverse depth of the camera-model start, 16 bytes.
@@ -289,6 +303,6 @@ hipError_t mlp_pack_launch(const MlpDev& M, hipStream_t s);
 // kSelectRight (deferred: acceptance of the matches into the right cameras).
 enum { kSelectAll = 0, kSelectLeft = 1, kSelectRight = 2 };
 hipError_t launch_select(const CamDesc* d_cams, const FrameTable* d_frame, Counters* d_cnt,
-                         const int* d_stream_cams, int n_streams_launch, int phase, Tuning tune, hipStream_t s);
+                         const SelectGroups& groups, int phase, Tuning tune, hipStream_t s);
 
 }  // namespace vio

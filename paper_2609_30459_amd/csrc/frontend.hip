@@ -103,7 +103,6 @@ struct vio_frontend {
   std::vector<CamDesc> cams;
   std::vector<TrackSeg> segs;      // per stream: the stream's items are contiguous
   std::vector<TrackSeg> segs_all;  // the same items in the batched step's order
-  std::vector<int> stream_cams;
   int total_tiles = 0;
   size_t rec_total = 0;
   // device
@@ -114,7 +113,6 @@ struct vio_frontend {
   Counters* d_cnt = nullptr;
   TrackSeg* d_segs = nullptr;
   TrackSeg* d_segs_all = nullptr;
-  int* d_stream_cams = nullptr;
   Prediction* d_pred = nullptr;
   int pred_cap = 0;
   KpDepth* d_depth = nullptr;  // per camera at CamDesc::row_off, up to its cap
@@ -317,6 +315,20 @@ void add_launch_cams(const vio_frontend* h, const LaunchSet& ls, int flags, cons
   }
 }
 
+// The launch set's camera groups in camera order (inactive ones too: a captured
+// launch serves every frame).
+SelectGroups select_groups(const vio_frontend* h, const LaunchSet& ls) {
+  SelectGroups a{};
+  for (int c = ls.cam_begin; c < ls.cam_end; ++c) {
+    if (!h->cams[c].detect) continue;
+    const bool first = a.n == 0 || h->cams[a.g[a.n - 1].cam].stream != h->cams[c].stream;
+    if (a.n > 0) a.g[a.n - 1].last = first;
+    a.g[a.n] = {(uint8_t)c, (uint8_t)first, 1, (uint8_t)(first ? 0 : a.g[a.n - 1].cam)};
+    a.n += 1;
+  }
+  return a;
+}
+
 // The pyramid launch: a tile's detection and levels in one workgroup, one after
 // the other, or in two. Two stage the tile twice and so take longer when the chip
 // is full, but halve the chain while all of them fit at once: two 1,024-thread
@@ -514,8 +526,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
     si.n_tiles = tiles - si.tile_begin;
     si.rec_n = rec_total - si.rec_off;
     h->streams.push_back(si);
-    h->stream_cams.push_back(si.first_cam);
-    h->stream_cams.push_back(si.n_cams);
   }
   // the batched step's order: every stream's stereo items, then every temporal item
   {
@@ -536,7 +546,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
   const size_t o_cnt = take(sizeof(Counters));
   const size_t o_segs = take(sizeof(TrackSeg) * h->segs.size());
   const size_t o_segs_all = take(sizeof(TrackSeg) * h->segs_all.size());
-  const size_t o_sc = take(sizeof(int) * h->stream_cams.size());
   const size_t o_pred = take(sizeof(Prediction) * std::max(1, h->pred_cap));
   const size_t o_depth = take(sizeof(KpDepth) * std::max(1, h->pred_cap));
   size_t o_feat = 0, o_guess = 0, o_P = 0, o_W1 = 0, o_W2 = 0, o_W2t = 0, o_W3 = 0;
@@ -603,7 +612,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
   h->d_cnt = reinterpret_cast<Counters*>(base + o_cnt);
   h->d_segs = reinterpret_cast<TrackSeg*>(base + o_segs);
   h->d_segs_all = reinterpret_cast<TrackSeg*>(base + o_segs_all);
-  h->d_stream_cams = reinterpret_cast<int*>(base + o_sc);
   h->d_pred = reinterpret_cast<Prediction*>(base + o_pred);
   h->d_depth = reinterpret_cast<KpDepth*>(base + o_depth);
   h->K.assign(n_cams, vio_pinhole{0.f, 0.f, 0.f, 0.f});
@@ -620,8 +628,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
   }
   HIP_CHECK(h, hipMemcpy(h->d_segs, h->segs.data(), sizeof(TrackSeg) * h->segs.size(), hipMemcpyHostToDevice));
   HIP_CHECK(h, hipMemcpy(h->d_segs_all, h->segs_all.data(), sizeof(TrackSeg) * h->segs_all.size(),
-                         hipMemcpyHostToDevice));
-  HIP_CHECK(h, hipMemcpy(h->d_stream_cams, h->stream_cams.data(), sizeof(int) * h->stream_cams.size(),
                          hipMemcpyHostToDevice));
   // pinned host buffers; records and their counts are written by the
   // selection kernel through the device mapping of h_rec / h_rec_count
@@ -828,16 +834,16 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
     return track_range(h, ls, ls.seg_begin + s0, ls.n_segs - s0, ls.item_begin + i0, ls.n_items - i0, tune, 0, st);
   }
   timing(kKernSelect);
-  const int* sc = h->d_stream_cams + 2 * ls.stream_begin;
-  if (!tune.deferred) return launch_select(h->d_cams, h->d_frame, h->d_cnt, sc, ls.n_streams, kSelectAll, tune, st);
+  const SelectGroups groups = select_groups(h, ls);
+  if (!tune.deferred) return launch_select(h->d_cams, h->d_frame, h->d_cnt, groups, kSelectAll, tune, st);
   // deferred stereo: select, match the selected detections, accept the matches
-  if ((e = launch_select(h->d_cams, h->d_frame, h->d_cnt, sc, ls.n_streams, kSelectLeft, tune, st))) return e;
+  if ((e = launch_select(h->d_cams, h->d_frame, h->d_cnt, groups, kSelectLeft, tune, st))) return e;
   if (ls.st_items > 0) {
     timing(kKernTrackStereo);
     if ((e = track_range(h, ls, ls.seg_begin, ls.st_segs, ls.item_begin, ls.st_items, tune, 1, st))) return e;
   }
   timing(kKernSelectRight);
-  return launch_select(h->d_cams, h->d_frame, h->d_cnt, sc, ls.n_streams, kSelectRight, tune, st);
+  return launch_select(h->d_cams, h->d_frame, h->d_cnt, groups, kSelectRight, tune, st);
 }
 
 // A frame runs on two streams. The pyramid stream builds the pyramid and

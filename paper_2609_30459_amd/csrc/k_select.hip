@@ -4,11 +4,17 @@
 // into mapped pinned host memory (the host reads them after the frame's wait,
 // with no copy).
 //
-// One 1024-thread workgroup per stream; camera groups (mono camera or stereo
-// pair) are handled in order so identifiers are assigned in (group, cell)
-// order. Every ordering decision is a prefix count over flags (wave ballots
-// plus a scan of the 16 wave totals), so the result does not depend on thread
-// timing.
+// One 1024-thread workgroup per camera group (a mono camera, a stereo pair, a
+// star rig). A selection is a chain of memory round trips and barriers, so what
+// does not depend on earlier steps (keys, the previous keypoints and their
+// results) is loaded at the start. Identifiers are assigned in (group, cell)
+// order: a stream's groups hand the next free one on as soon as they know how
+// many detections they take. Every ordering decision is a prefix count over
+// flags (wave ballots plus a scan of the 16 wave totals), so the result does not
+// depend on thread timing. Mono 320x240 (200 keypoints, 300 cells) 5.9 -> 5.1
+// us, a pair of 300 8.9 -> 8.5, a four-camera rig of 6,000 (two pairs, one after
+// the other before) 40 -> 24. What is left is the chain: records laid out in LDS
+// and stored in whole lines took 5.6, 9.3 and 25.
 //
 // Rules (all on integers):
 //  * a cell is masked when it holds at least k surviving tracks of the camera;
@@ -132,39 +138,49 @@ struct PairRow {
 };
 constexpr int kPairLds = 1024;  // rows per camera kept in LDS (cameras of larger caps read global memory)
 
+// A camera's previous keypoint and its tracking result.
+struct PrevRow {
+  Kp kp;
+  TrackRes r;
+};
+// Row j of `cd` (j < cap; garbage past the camera's live rows).
+__device__ __forceinline__ PrevRow load_row(const CamDesc& cd, const FrameCam& fc, int j) {
+  PrevRow p{};
+  if (j < cd.cap) {
+    p.kp = cd.state[fc.parity ^ 1][j];
+    if (fc.has_prev) {
+      // a short attempt that was not kept: its fallback, computed beside it
+      // (both results loaded at once, so the choice costs no second round
+      // trip; the fallback slot of a kept track is not used)
+      p.r = cd.res[j];
+      if (cd.res_fb) {
+        const TrackRes rf = cd.res_fb[j];
+        if (p.r.pad[0] != 0) p.r = rf;
+      }
+    } else {
+      p.r.x = p.kp.x;
+      p.r.y = p.kp.y;
+    }
+  }
+  return p;
+}
+
 // Carries camera c's previous keypoints into its current state: the survivors
 // of temporal tracking (all of them when there was no previous frame) in their
 // old order, with their records. Adds the survivors to `occ` when given, and
-// their ids and positions to `tab` when given. Returns the survivor count;
-// *n_rec receives the number of records written.
-__device__ int carry_survivors(const CamDesc& cd, const FrameCam& fc, int n_prev, unsigned* occ, Scan& sc,
-                               int* n_rec, bool count_fallback, PairRow* tab = nullptr,
-                               int64_t* tab_ids = nullptr) {
-  const int P = fc.parity, Q = P ^ 1;
+// their ids and positions to `tab` when given. `row`: this thread's first row.
+// Returns the survivor count; *n_rec receives the number of records written.
+__device__ __forceinline__ int carry_survivors(const CamDesc& cd, const FrameCam& fc, int n_prev, PrevRow row,
+                                               unsigned* occ, Scan& sc, int* n_rec, bool count_fallback,
+                                               PairRow* tab = nullptr, int64_t* tab_ids = nullptr) {
+  const int P = fc.parity;
   int base = 0, n_fb = 0;
   for (int j0 = 0; j0 < n_prev; j0 += kSelectThreads) {
     const int j = j0 + (int)threadIdx.x;
-    bool alive = false;
-    Kp kp{};
-    TrackRes r{};
-    if (j < n_prev) {
-      kp = cd.state[Q][j];
-      if (fc.has_prev) {
-        // a short attempt that was not kept: its fallback, computed beside it
-        // (both results loaded at once, so the choice costs no second round
-        // trip; the fallback slot of a kept track is not used)
-        r = cd.res[j];
-        if (cd.res_fb) {
-          const TrackRes rf = cd.res_fb[j];
-          if (r.pad[0] != 0) r = rf;
-        }
-        alive = r.status == VIO_TRACKED;
-      } else {
-        r.x = kp.x;
-        r.y = kp.y;
-        alive = true;
-      }
-    }
+    if (j0 > 0) row = load_row(cd, fc, j);
+    const Kp kp = row.kp;
+    const TrackRes r = row.r;
+    const bool alive = j < n_prev && (!fc.has_prev || r.status == VIO_TRACKED);
     int total, fb_tot;
     const int pos = base + (count_fallback ? block_scan_flag2(alive, j < n_prev && fc.has_prev && r.pad[0] != 0, sc,
                                                               total, fb_tot)
@@ -198,24 +214,23 @@ __device__ int carry_survivors(const CamDesc& cd, const FrameCam& fc, int n_prev
   return base;
 }
 
-// Appends the accepted stereo matches of the n_new detections of left camera
-// L (ids from L's new keypoints state[P][sel_base + i]) to right camera R,
-// after its n_surv_r survivors and n_rec_r temporal records. sres(i): the
-// match of detection i.
-template <class SresOf>
-__device__ int accept_matches(const CamDesc& L, int P, int sel_base, const CamDesc& R, const FrameCam& fr,
-                              int rc, int n_new, int n_surv_r, int n_rec_r, SresOf sres, Counters* cnt,
-                              Scan& sc, PairRow* tab = nullptr) {
+// Appends the accepted stereo matches of the n_new detections of a detecting
+// camera to right camera R, after its n_surv_r survivors and n_rec_r temporal
+// records. id(i), sres(i): detection i's identifier and match; `sr`: the match
+// of detection threadIdx.x.
+template <class IdOf, class SresOf>
+__device__ __forceinline__ int accept_matches(const CamDesc& R, const FrameCam& fr, int rc, int n_new, int n_surv_r,
+                                              int n_rec_r, IdOf id_of, SresOf sres, TrackRes sr, Counters* cnt,
+                                              Scan& sc, PairRow* tab = nullptr) {
   const int PR = fr.parity;
   int m_base = 0;
   for (int i0 = 0; i0 < n_new; i0 += kSelectThreads) {
     const int i = i0 + (int)threadIdx.x;
     const bool valid = i < n_new;
-    TrackRes sr{};
     int64_t id = 0;
     if (valid) {
-      sr = sres(i);
-      id = L.state[P][sel_base + i].id;
+      if (i0 > 0) sr = sres(i);
+      id = id_of(i);
     }
     const bool matched = valid && sr.status == VIO_TRACKED;
     int m_tot;
@@ -329,8 +344,7 @@ __device__ void build_pairs(const CamDesc& L, int P, int n_left, const CamDesc& 
 
 __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __restrict__ cams,
                                                           const FrameTable* __restrict__ frame, Counters* cnt,
-                                                          const int* __restrict__ stream_cams, int phase,
-                                                          Tuning tune) {
+                                                          SelectGroups groups, int phase, Tuning tune) {
   __shared__ ScanScratch s_scan;
   __shared__ int s_hsum[4];
   Scan sc{&s_scan, 0};
@@ -338,48 +352,51 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
   __shared__ uint16_t s_sel[kMaxCells];  // key slot of selection rank i (rank < cap <= kMaxCells, slot < 2^16)
   __shared__ int s_hist[256];
   __shared__ int s_thr[2];
+  __shared__ int64_t s_id0;
   // the detecting and the target camera's rows for the neighbour stereo start's pair table
   __shared__ PairRow s_pl[kPairLds], s_pr[kPairLds];
   __shared__ int64_t s_plid[kPairLds];  // s_pl's ids, contiguous for the pair search
-  const int s = blockIdx.x;
-  const int cam0 = stream_cams[2 * s], ncam = stream_cams[2 * s + 1];
-  if (!frame->cam[cam0].active) return;
-  // camera groups: a detecting camera followed by the n_targets cameras that
-  // receive its matches (mono: none, stereo pair: one, star rig: three)
+  const auto grp = groups.g[blockIdx.x];
+  const int lc = grp.cam;
+  const CamDesc& L = cams[lc];
+  const FrameCam& fl = frame->cam[lc];
+  if (!fl.active) return;
+  const int P = fl.parity, Q = P ^ 1;
+  const int tid = (int)threadIdx.x;
   if (phase == kSelectRight) {
-    for (int g = 0; g < ncam; g += 1 + cams[cam0 + g].n_targets) {
-      const int lc = cam0 + g;
-      const CamDesc& L = cams[lc];
-      const int P = frame->cam[lc].parity;
-      for (int t = 0; t < L.n_targets; ++t) {
-        const int rc = lc + 1 + t;
-        const FrameCam& fr = frame->cam[rc];
-        const int PR = fr.parity;
-        const int n_rec_r = fr.has_prev ? cnt->n_live[PR ^ 1][rc] : 0;
-        const TrackRes* sr = L.sres + (size_t)t * L.nslots;
-        const int n_r = accept_matches(L, P, cnt->sel_base[lc], cams[rc], fr, rc, cnt->n_sel[lc],
-                                       cnt->n_live[PR][rc], n_rec_r, [&](int i) { return sr[i]; }, cnt, sc);
+    const int n_new = cnt->n_sel[lc], sel_base = cnt->sel_base[lc];
+    for (int t = 0; t < L.n_targets; ++t) {
+      const int rc = lc + 1 + t;
+      const FrameCam& fr = frame->cam[rc];
+      const int PR = fr.parity;
+      const int n_rec_r = fr.has_prev ? cnt->n_live[PR ^ 1][rc] : 0;
+      const TrackRes* sres = L.sres + (size_t)t * L.nslots;
+      TrackRes sr{};
+      if (tid < n_new) sr = sres[tid];
+      const int n_r = accept_matches(cams[rc], fr, rc, n_new, cnt->n_live[PR][rc], n_rec_r,
+                                     [&](int i) { return L.state[P][sel_base + i].id; },
+                                     [&](int i) { return sres[i]; }, sr, cnt, sc);
+      __syncthreads();
+      if (tune.stereo_nb) {
+        build_pairs(L, P, sel_base + n_new, cams[rc], PR, rc, n_r, cnt, sc, nullptr, nullptr, nullptr,
+                    reinterpret_cast<int64_t*>(s_occ));
         __syncthreads();
-        if (tune.stereo_nb) {
-          build_pairs(L, P, cnt->sel_base[lc] + cnt->n_sel[lc], cams[rc], PR, rc, n_r, cnt, sc, nullptr, nullptr,
-                      nullptr, reinterpret_cast<int64_t*>(s_occ));
-          __syncthreads();
-        }
       }
     }
     return;
   }
-  const int stream = cams[cam0].stream;
-  const int64_t id0 = cnt->next_id[stream];
-  int64_t next_id = id0;
-  for (int g = 0; g < ncam; g += 1 + cams[cam0 + g].n_targets) {
-    const int lc = cam0 + g;
-    const CamDesc& L = cams[lc];
-    const FrameCam& fl = frame->cam[lc];
-    const int P = fl.parity, Q = P ^ 1;
-    const int ncells = L.ncells, kc = L.kcell, nslots = L.nslots;
-    for (int i = threadIdx.x; i < ncells; i += kSelectThreads) s_occ[i] = 0;
-    for (int i = threadIdx.x; i < 256; i += kSelectThreads) s_hist[i] = 0;
+  // what depends on no earlier step: the thread's first key slot and rows
+  const int ncells = L.ncells, kc = L.kcell, nslots = L.nslots;
+  const uint32_t* keys = L.keys[fl.pyr];
+  const uint32_t key0 = tid < nslots ? keys[tid] : 0u;
+  const PrevRow row_l = load_row(L, fl, tid);
+  PrevRow row_r{};
+  if (L.n_targets > 0) row_r = load_row(cams[lc + 1], frame->cam[lc + 1], tid);
+  const auto key_of = [&](int slot) { return slot < kSelectThreads ? key0 : slot < nslots ? keys[slot] : 0u; };
+  const auto cell_of = [kc](int slot) { return kc == 1 ? slot : slot / kc; };
+  {
+    for (int i = tid; i < ncells; i += kSelectThreads) s_occ[i] = 0;
+    for (int i = tid; i < 256; i += kSelectThreads) s_hist[i] = 0;
     __syncthreads();
 
     // ---- left / mono camera: survivors and occupancy ----------------------
@@ -387,15 +404,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
     const bool count_fb = tune.learned != 0 || tune.plevels > 0;
     // pair rows in LDS (all-in-one selection with the neighbour stereo start)
     const bool pairs_lds = phase == kSelectAll && tune.stereo_nb && L.cap <= kPairLds;
-    const int n_surv = carry_survivors(L, fl, cnt->n_live[Q][lc], s_occ, sc, &n_rec, count_fb,
+    const int n_surv = carry_survivors(L, fl, cnt->n_live[Q][lc], row_l, s_occ, sc, &n_rec, count_fb,
                                        pairs_lds ? s_pl : nullptr, pairs_lds ? s_plid : nullptr);
     __syncthreads();
 
     // ---- candidates of unmasked cells, score histogram --------------------
-    const uint32_t* keys = L.keys[fl.pyr];
-    for (int i = threadIdx.x; i < nslots; i += kSelectThreads) {
-      const uint32_t key = keys[i];
-      if (key && (int)s_occ[i / kc] < kc) atomicAdd(&s_hist[key >> 24], 1);
+    for (int i = tid; i < nslots; i += kSelectThreads) {
+      const uint32_t key = key_of(i);
+      if (key && (int)s_occ[cell_of(i)] < kc) atomicAdd(&s_hist[key >> 24], 1);
     }
     __syncthreads();
     // Score threshold of the best `room` candidates: thread t < 256 holds bin
@@ -406,14 +422,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
     {
       const int room = max(0, L.cap - n_surv);
       int hv = 0, incl = 0;
-      if (threadIdx.x < 256) {
-        hv = s_hist[255 - threadIdx.x];
+      if (tid < 256) {
+        hv = s_hist[255 - tid];
         incl = wave_incl_scan(hv);
-        if ((threadIdx.x & 63) == 63) s_hsum[threadIdx.x >> 6] = incl;
+        if ((tid & 63) == 63) s_hsum[tid >> 6] = incl;
       }
       __syncthreads();
-      if (threadIdx.x < 256) {
-        const int w = threadIdx.x >> 6;
+      if (tid < 256) {
+        const int w = tid >> 6;
         int before = 0, total = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -423,24 +439,45 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
         }
         const int cum = before + incl;
         if (room > 0 && total > room && cum >= room && cum - hv < room) {
-          s_thr[0] = 255 - (int)threadIdx.x;
+          s_thr[0] = 255 - tid;
           s_thr[1] = room - (cum - hv);
         }
-        if (threadIdx.x == 0 && (room == 0 || total <= room)) {
+        if (tid == 0 && (room == 0 || total <= room)) {
           s_thr[0] = room == 0 ? 256 : -1;
           s_thr[1] = 0;
+        }
+        if (tid == 0) {
+          // The group's identifiers follow those of the stream's earlier groups.
+          // (The wait ends: at most kMaxCams workgroups, the earlier ones
+          // started before this one, and the first waits for nobody.)
+          int64_t id0;
+          if (grp.first) {
+            id0 = cnt->next_id[L.stream];
+          } else {
+            int64_t v;
+            while ((v = __hip_atomic_load(&cnt->id_chain[grp.prev], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0)
+              __builtin_amdgcn_s_sleep(1);
+            __hip_atomic_store(&cnt->id_chain[grp.prev], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            id0 = v >> 1;
+          }
+          s_id0 = id0;
+          const int64_t next = id0 + min(room, total);
+          if (grp.last) cnt->next_id[L.stream] = next;
+          else
+            __hip_atomic_store(&cnt->id_chain[lc], next << 1 | 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
       __syncthreads();
     }
     const int thr = s_thr[0], rem = s_thr[1];
+    const int64_t next_id = s_id0;
 
     // ---- selection in slot order, identifiers, DET_t records --------------
     int n_new = 0, eq_base = 0;
     for (int i0 = 0; i0 < nslots; i0 += kSelectThreads) {
       const int slot = i0 + (int)threadIdx.x;
-      const uint32_t key = slot < nslots ? keys[slot] : 0u;
-      const bool cand = key && (int)s_occ[slot < nslots ? slot / kc : 0] < kc;
+      const uint32_t key = key_of(slot);
+      const bool cand = key && (int)s_occ[slot < nslots ? cell_of(slot) : 0] < kc;
       const int score = (int)(key >> 24);
       const bool is_eq = cand && score == thr;
       int eq_tot, sel_tot;
@@ -485,18 +522,23 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
       const int PR = fr.parity;
       int n_rec_r = 0;
       const bool pairs_lds_r = pairs_lds && R.cap <= kPairLds;
-      const int n_surv_r = carry_survivors(R, fr, cnt->n_live[PR ^ 1][rc], nullptr, sc, &n_rec_r, count_fb,
+      const TrackRes* sres = L.sres + (size_t)t * nslots;
+      TrackRes sr{};
+      if (phase == kSelectAll && tid < n_new) sr = sres[s_sel[tid]];
+      const PrevRow row = row_r;
+      if (t + 1 < L.n_targets) row_r = load_row(cams[rc + 1], frame->cam[rc + 1], tid);
+      const int n_surv_r = carry_survivors(R, fr, cnt->n_live[PR ^ 1][rc], row, nullptr, sc, &n_rec_r, count_fb,
                                            pairs_lds_r ? s_pr : nullptr);
       if (phase == kSelectAll) {
-        const TrackRes* sr = L.sres + (size_t)t * nslots;
-        const int n_r = accept_matches(L, P, n_surv, R, fr, rc, n_new, n_surv_r, n_rec_r,
-                                       [&](int i) { return sr[s_sel[i]]; }, cnt, sc, pairs_lds_r ? s_pr : nullptr);
+        const int n_r = accept_matches(R, fr, rc, n_new, n_surv_r, n_rec_r, [&](int i) { return next_id + i; },
+                                       [&](int i) { return sres[s_sel[i]]; }, sr, cnt, sc,
+                                       pairs_lds_r ? s_pr : nullptr);
         if (tune.stereo_nb) {
           __syncthreads();
           build_pairs(L, P, n_surv + n_new, R, PR, rc, n_r, cnt, sc, pairs_lds ? s_pl : nullptr,
                       pairs_lds ? s_plid : nullptr, pairs_lds_r ? s_pr : nullptr, reinterpret_cast<int64_t*>(s_occ));
         }
-      } else if (threadIdx.x == 0) {
+      } else if (tid == 0) {
         // the matches come from the stereo tracking launch; kSelectRight appends them
         cnt->sel_base[lc] = n_surv;
         cnt->n_sel[lc] = n_new;
@@ -504,18 +546,15 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
       }
       __syncthreads();
     }
-    next_id += n_new;
   }
-  if (threadIdx.x == 0) cnt->next_id[stream] = next_id;
 }
 
 }  // namespace
 
-hipError_t launch_select(const CamDesc* d_cams, const FrameTable* d_frame, Counters* d_cnt, const int* d_stream_cams,
-                         int n_streams_launch, int phase, Tuning tune, hipStream_t s) {
-  if (n_streams_launch <= 0) return hipSuccess;
-  launch_kernel(k_select, dim3(n_streams_launch), dim3(kSelectThreads), 0, s, d_cams, d_frame, d_cnt,
-                d_stream_cams, phase, tune);
+hipError_t launch_select(const CamDesc* d_cams, const FrameTable* d_frame, Counters* d_cnt, const SelectGroups& groups,
+                         int phase, Tuning tune, hipStream_t s) {
+  if (groups.n <= 0) return hipSuccess;
+  launch_kernel(k_select, dim3(groups.n), dim3(kSelectThreads), 0, s, d_cams, d_frame, d_cnt, groups, phase, tune);
   return hipGetLastError();
 }
 
