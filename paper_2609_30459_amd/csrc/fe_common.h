@@ -268,7 +268,7 @@ struct Prediction {
 // memory, to d_frame for the frame's later kernels.
 hipError_t launch_pyr_detect(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame,
                              FrameTable* d_frame, int copy_bytes, int levels, int tile, int tmin, int margin,
-                             hipStream_t s);
+                             int n_cus, hipStream_t s);
 size_t pyr_detect_lds_bytes(int levels, int tile);
 // Copies bytes (a multiple of 4, at most a few tens of MB) from mapped pinned
 // host memory at device address d_src to d_dst.

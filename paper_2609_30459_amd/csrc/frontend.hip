@@ -816,7 +816,7 @@ static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_
     return launch_pyr_detect(h->d_cams, pyramid_args(h, ls),
                              h->hm_frame, h->d_frame,
                              (int)(offsetof(FrameTable, cam) + sizeof(FrameCam) * h->cams.size()), tune.levels,
-                             h->tile, tune.tmin, tune.margin, st);
+                             h->tile, tune.tmin, tune.margin, h->n_cus, st);
   }
   if (stage == 4) {
     // the features of the previous keypoints and the network's guesses in one

@@ -1,6 +1,6 @@
 // Fused pyramid + corner detector for gfx950.
 //
-// One workgroup owns a TxT level-0 tile of one camera (T = 64 with 1024
+// One workgroup owns a TxT level-0 tile of one camera (T = 64 with 1024 or 512
 // threads, or T = 32 with 256 threads: more, smaller workgroups for small
 // images, chosen per workload at create). It stages
 // the tile plus an apron in LDS with coalesced dword loads, then
@@ -36,7 +36,8 @@ namespace {
 
 template <int L, int T>
 struct PyrGeom {
-  static constexpr int threads = T == 64 ? 1024 : 256;
+  static constexpr int threads = T == 64 ? 1024 : 256;  // of a workgroup, and where they come in rounds
+  static constexpr int threads_many = T == 64 && L <= 5 ? 512 : threads;
   static constexpr int score_edge = T + 2;
   // apron of level l so that the tile of level L-1 can be computed: A[L-1] = 0,
   // A[l] = 2 A[l+1] + 2, i.e. A[l] = 2^(L-l) - 2
@@ -218,16 +219,15 @@ __device__ __forceinline__ uint32_t pyr_v_pair(uint32_t r0, uint32_t r1, uint32_
   return (w & 0xFFu) | ((w >> 8) & 0xFF00u);
 }
 
-template <int L, int T>
-__global__ __launch_bounds__(T == 64 ? 1024 : 256) void k_pyr_detect(const CamDesc* __restrict__ cams,
+template <int L, int T, int NT>
+__global__ __launch_bounds__(NT) void k_pyr_detect(const CamDesc* __restrict__ cams,
                                                                       const LaunchCams args,
                                                                       const FrameTable* __restrict__ frame,
                                                                       FrameTable* __restrict__ dframe,
                                                                       int copy_words, int tmin, int margin) {
   using G = PyrGeom<L, T>;
-  static_assert(G::threads == (T == 64 ? 1024 : 256), "launch bounds");
   constexpr int kTile = T;
-  constexpr int kPyrThreads = G::threads;
+  constexpr int kPyrThreads = NT;
   constexpr int kScoreEdge = G::score_edge;
   __shared__ __align__(16) uint8_t s_l0[G::sh0 * G::sw0];
   __shared__ __align__(4) uint8_t s_score[G::score_bytes];
@@ -514,11 +514,23 @@ __global__ __launch_bounds__(256) void k_upload(const uint32_t* __restrict__ src
   if (i < n) dst[i] = src[i];
 }
 
+// A compute unit holds 32 waves: two 64-px workgroups of 1,024 threads, or four
+// of 512, whose phases and barriers hide each other's once the workgroups come
+// in more than one round; within one round the wider ones' chains are shorter.
+// 1,024 and 512 threads, four levels: 480 workgroups 17.7 and 17.9 us, 720 26.8
+// and 22.6, 1,920 55.8 and 45.9, sixteen uneven streams (5,433) 101 and 74; one
+// level: 384 11.3 and 12.3, 576 15.9 and 14.6; five: 2,280 58.5 and 50.1. Six
+// levels' LDS leaves one workgroup to a compute unit (576: 58.5 and 73.0).
 template <int L, int T>
 hipError_t launch_LT(const CamDesc* cams, const LaunchCams& args, const FrameTable* frame, FrameTable* dframe,
-                     int copy_words, int tmin, int margin, hipStream_t s) {
-  launch_kernel(k_pyr_detect<L, T>, dim3(args.blocks + 1), dim3(PyrGeom<L, T>::threads), 0, s, cams, args, frame,
-                dframe, copy_words, tmin, margin);
+                     int copy_words, int tmin, int margin, int n_cus, hipStream_t s) {
+  using G = PyrGeom<L, T>;
+  if (args.blocks > 2 * n_cus)
+    launch_kernel(k_pyr_detect<L, T, G::threads_many>, dim3(args.blocks + 1), dim3(G::threads_many), 0, s, cams, args,
+                  frame, dframe, copy_words, tmin, margin);
+  else
+    launch_kernel(k_pyr_detect<L, T, G::threads>, dim3(args.blocks + 1), dim3(G::threads), 0, s, cams, args, frame,
+                  dframe, copy_words, tmin, margin);
   return hipGetLastError();
 }
 
@@ -527,12 +539,12 @@ size_t lds_bytes_T(int levels) {
   hipFuncAttributes a{};
   hipError_t e = hipErrorInvalidValue;
   switch (levels) {
-    case 1: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<1, T>)); break;
-    case 2: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<2, T>)); break;
-    case 3: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<3, T>)); break;
-    case 4: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<4, T>)); break;
-    case 5: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<5, T>)); break;
-    case 6: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<6, T>)); break;
+    case 1: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<1, T, PyrGeom<1, T>::threads>)); break;
+    case 2: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<2, T, PyrGeom<2, T>::threads>)); break;
+    case 3: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<3, T, PyrGeom<3, T>::threads>)); break;
+    case 4: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<4, T, PyrGeom<4, T>::threads>)); break;
+    case 5: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<5, T, PyrGeom<5, T>::threads>)); break;
+    case 6: e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_pyr_detect<6, T, PyrGeom<6, T>::threads>)); break;
     default: break;
   }
   return e == hipSuccess ? a.sharedSizeBytes : 0;
@@ -540,14 +552,14 @@ size_t lds_bytes_T(int levels) {
 
 template <int T>
 hipError_t launch_T(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame, FrameTable* d_frame,
-                    int copy_words, int levels, int tmin, int margin, hipStream_t s) {
+                    int copy_words, int levels, int tmin, int margin, int n_cus, hipStream_t s) {
   switch (levels) {
-    case 1: return launch_LT<1, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
-    case 2: return launch_LT<2, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
-    case 3: return launch_LT<3, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
-    case 4: return launch_LT<4, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
-    case 5: return launch_LT<5, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
-    case 6: return launch_LT<6, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, s);
+    case 1: return launch_LT<1, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
+    case 2: return launch_LT<2, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
+    case 3: return launch_LT<3, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
+    case 4: return launch_LT<4, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
+    case 5: return launch_LT<5, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
+    case 6: return launch_LT<6, T>(d_cams, args, h_frame, d_frame, copy_words, tmin, margin, n_cus, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -569,11 +581,11 @@ hipError_t launch_upload(const void* d_src, void* d_dst, size_t bytes, hipStream
 
 hipError_t launch_pyr_detect(const CamDesc* d_cams, const LaunchCams& args, const FrameTable* h_frame,
                              FrameTable* d_frame, int copy_bytes, int levels, int tile, int tmin, int margin,
-                             hipStream_t s) {
+                             int n_cus, hipStream_t s) {
   if (args.n < 1 || args.blocks < 1 || copy_bytes % 4) return hipErrorInvalidValue;
   const int w = copy_bytes / 4;
-  if (tile == 32) return launch_T<32>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, s);
-  if (tile == 64) return launch_T<64>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, s);
+  if (tile == 32) return launch_T<32>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, n_cus, s);
+  if (tile == 64) return launch_T<64>(d_cams, args, h_frame, d_frame, w, levels, tmin, margin, n_cus, s);
   return hipErrorInvalidValue;
 }
 

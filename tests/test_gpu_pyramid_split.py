@@ -1,6 +1,6 @@
 """The pyramid launch in its two forms, and with each tile edge: detection and
 levels of a tile in one workgroup (a step of many streams) or in two (the same
-stream alone), at sizes on both sides of the tile edges, with more than one key
+stream alone), the former with 1,024 or 512 threads to a 64-px tile, at sizes on both sides of the tile edges, with more than one key
 per cell, a detection mask, and 1 to 6 levels. Levels and records are whole
 numbers and float bits that must not change, so they are compared exactly."""
 import numpy as np
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("w,h,levels,kcell", [(64, 64, 2, 1), (65, 63, 1, 1), (97, 130, 3, 2), (320, 240, 6, 1),
-                                              (383, 257, 4, 3), (641, 479, 5, 1)])
+                                              (383, 257, 4, 3), (641, 479, 5, 1), (161, 140, 1, 1),
+                                              (200, 150, 2, 1), (180, 170, 3, 2)])
 def test_split_and_joined_launches_agree(w, h, levels, kcell):
     import torch
     if not torch.cuda.is_available():
