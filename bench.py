@@ -19,9 +19,9 @@ Each leg's sequence is resident in HBM before timing starts. A step stages
 one frame's device images of every stream through the C ABI, submits it and
 reads the records back. The first timed region of a leg is the production
 path: pipelined submission (frame t is submitted before frame t-2's records
-are waited for and read, three frames in flight) with the kernels launched one
-by one (`--launch graph`: captured graphs; `--no-pipeline`: one frame at a
-time). A second region runs the same steps one frame at a time with each
+are waited for and read, three frames in flight) without timestamps
+(`--launch graph`: a frame's start and end are taken; `--no-pipeline`: one frame
+at a time). A second region runs the same steps one frame at a time with each
 kernel's HIP start/stop events attached to its own dispatch: it gives the
 kernel durations behind the roofline figures, with a check that both regions
 give identical records. A host-image leg pushes the frames from host memory
@@ -153,8 +153,8 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-host-leg", action="store_true", help="skip the host-image leg")
     ap.add_argument("--launch", choices=["plain", "graph", "eager"], default="plain",
-                    help="first timed region: kernels launched one by one without timestamps (default), captured "
-                         "graphs, or one by one with HIP events attached to each dispatch")
+                    help="first timed region: without timestamps (default), with each frame's start and end "
+                         "(\"graph\": a captured graph once), or with HIP events attached to each dispatch")
     ap.add_argument("--in-flight", type=int, choices=[2, 3], default=3,
                     help="frames in flight on the pipelined path (the library allows up to three)")
     ap.add_argument("--no-pipeline", action="store_true",

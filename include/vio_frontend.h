@@ -194,11 +194,9 @@ typedef struct vio_frontend_params {
 #define VIO_TOPOLOGY_STAR 1
 
 /* vio_frontend_params.flags */
-#define VIO_FLAG_EAGER 1u /* launch the per-frame kernels one by one, each with dispatch timestamps (without
-                             it the batched step replays a captured hipGraph, and a pushed frame's kernels
-                             are launched one by one) */
-#define VIO_FLAG_PLAIN 2u /* launch the kernels one by one without timestamps (fewer host calls than a
-                             graph launch for small frames); excludes VIO_FLAG_EAGER */
+#define VIO_FLAG_EAGER 1u /* each kernel's dispatch carries timestamps, and a frame is completed before the
+                             next is submitted (without it a frame's start and end are taken) */
+#define VIO_FLAG_PLAIN 2u /* no timestamps (fewer host calls); excludes VIO_FLAG_EAGER */
 
 /* Output record: one per previous keypoint of each camera (tracked or lost) and
  * one per new detection / stereo match, sorted by (camera, id). */
@@ -320,7 +318,7 @@ int vio_frontend_push_stereo_frame_device(vio_frontend* h, int32_t stream, int64
 /* Batched stepping: stage one frame for any number of streams, then run every
  * staged stream in one submit (one pyramid/detector launch over all their
  * cameras, one tracking launch over all their keypoints, one selection
- * launch), replayed as one captured graph. The staging calls copy nothing:
+ * launch). The staging calls copy nothing:
  * d_images must stay valid until vio_frontend_step returns; host images are
  * copied into pinned staging at stage time. A stream staged twice keeps the
  * last frame. vio_frontend_step is synchronous; afterwards each staged

@@ -22,8 +22,7 @@ constexpr int kFewTiles = 128;
 __host__ __device__ constexpr int level_pitch(int width) { return (width + 63) & ~63; }
 // Kernel timing: while set, the frontend's kernel launches on this thread
 // attach these events to the dispatch itself (the kernel's own start and end
-// timestamps, without the gaps between launches); null for plain launches and
-// during graph capture.
+// timestamps, without the gaps between launches); null for plain launches.
 struct KernelTiming {
   hipEvent_t start = nullptr, stop = nullptr;
 };

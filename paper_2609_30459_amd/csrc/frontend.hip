@@ -41,18 +41,6 @@ static_assert(kMaxCellsAbi * kMaxPerCell <= 65536, "the selection kernel keeps k
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// The captured tracking part (tracker and selection) of one submission slot of
-// the batched step. The pyramid/detector and the learned stage are plain launches:
-// their arguments hold the frame's inputs.
-struct Graphs {
-  hipGraphExec_t trk = nullptr;
-  bool any() const { return trk != nullptr; }
-  void destroy() {
-    if (trk) (void)hipGraphExecDestroy(trk);
-    trk = nullptr;
-  }
-};
-
 struct StreamInfo {
   int first_cam, n_cams, w, h, cap, cell;
   int64_t frames = 0;
@@ -98,7 +86,6 @@ struct vio_frontend {
   vio_frontend_params P{};
   int n_cus = 256;
   int tile = kTileDefault;  // pyramid/detector tile edge
-  Graphs graph_all[kInFlight];  // captured batched step by submission slot
   std::vector<StreamInfo> streams;
   std::vector<CamDesc> cams;
   std::vector<TrackSeg> segs;      // per stream: the stream's items are contiguous
@@ -139,7 +126,6 @@ struct vio_frontend {
   int64_t sub = 0;                // submissions so far
   struct Pending {
     LaunchSet ls;
-    bool graphed;
     int slot;
   };
   Pending pend[kInFlight];
@@ -167,8 +153,8 @@ struct vio_frontend {
   int device = 0;
   bool poisoned = false;
   bool fault_device = false;
-  bool eager = false;        // graph capture off (flag) or unavailable
-  bool plain = false;        // plain launches: no graphs, no per-kernel timing
+  bool eager = false;        // per-kernel timing
+  bool plain = false;        // no timing at all
   std::string err;
   vio_stats stats{};
 };
@@ -315,8 +301,7 @@ void add_launch_cams(const vio_frontend* h, const LaunchSet& ls, int flags, cons
   }
 }
 
-// The launch set's camera groups in camera order (inactive ones too: a captured
-// launch serves every frame).
+// The launch set's camera groups in camera order (inactive ones too).
 SelectGroups select_groups(const vio_frontend* h, const LaunchSet& ls) {
   SelectGroups a{};
   for (int c = ls.cam_begin; c < ls.cam_end; ++c) {
@@ -387,7 +372,6 @@ void vio_frontend_destroy(vio_frontend* h) {
   if (!h) return;
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   if (h->pstream) (void)hipStreamSynchronize(h->pstream);
-  for (Graphs& g : h->graph_all) g.destroy();
   if (h->arena) {
     if (h->P.dev_free) h->P.dev_free(h->arena, h->P.alloc_ctx);
     else (void)hipFree(h->arena);
@@ -797,9 +781,7 @@ static hipError_t track_range(vio_frontend* h, const LaunchSet& ls, int seg_begi
 
 // Enqueues one step of a frame of the launch set on `st`: 1 = pyramid+detector,
 // 2 = tracker, 3 = selection (deferred stereo: selection, stereo tracker,
-// selection), 4 = learned mode's features and network. What 2 and 3 enqueue does
-// not change between frames (per-frame inputs live in the frame table), so they
-// can be captured once.
+// selection), 4 = learned mode's features and network.
 // `timed` attaches each kernel's start/stop events to its dispatch.
 static hipError_t enqueue_stage(vio_frontend* h, const LaunchSet& ls, hipStream_t st, int stage, bool timed) {
   const Tuning tune = tuning(h);
@@ -879,35 +861,17 @@ static hipError_t enqueue_track_part(vio_frontend* h, const LaunchSet& ls, hipSt
   return enqueue_stage(h, ls, st, 3, timed);
 }
 
-// Captures a slot's tracking part on first use; a capture failure switches the
-// handle to eager launches for good.
-static void ensure_graph(vio_frontend* h, const LaunchSet& ls, Graphs* gr) {
-  if (h->eager || h->plain || gr->any()) return;
-  hipStream_t cs = h->stream;
-  hipGraph_t g = nullptr;
-  bool ok = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) == hipSuccess;
-  if (ok) {
-    const hipError_t e = enqueue_track_part(h, ls, cs, false);
-    ok = hipStreamEndCapture(cs, &g) == hipSuccess && e == hipSuccess && g;
-  }
-  if (ok) ok = hipGraphInstantiate(&gr->trk, g, nullptr, nullptr, 0) == hipSuccess;
-  if (g) (void)hipGraphDestroy(g);
-  if (!ok) {
-    gr->trk = nullptr;
-    h->eager = true;
-    (void)hipGetLastError();
-  }
-}
-
 static int complete_all(vio_frontend* h);
 
 // Submits one frame of a launch set whose inputs are in the current slot's
-// frame table (h_frame) without waiting: the slot's captured graph, or eager
-// launches with per-kernel timing. The next slot becomes the staging slot.
+// frame table (h_frame) without waiting. The next slot becomes the staging slot.
 // Eager submissions are completed before the next one (their kernel timing
-// events are shared). gr == nullptr: direct launches. one_stream: the frame's
-// pyramid runs on st too.
-static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStream_t st, bool one_stream) {
+// events are shared). one_stream: the frame's pyramid runs on st too. Every
+// launch is made directly: replaying the tracker and the selection as a captured
+// graph cost the host 36 us a submission where this takes 19 (a pair of 1280x720
+// with three frames in flight 57.1 -> 51.3 us a frame, sixteen streams 230.5 ->
+// 225.3).
+static int submit_set(vio_frontend* h, const LaunchSet& ls, hipStream_t st, bool one_stream) {
   if (h->n_pend == kInFlight) return fail(h, VIO_ESTATE, "%d frames in flight: call vio_frontend_wait first", kInFlight);
   if (h->pyr_sig && h->pyr_epoch >= 0x80000000u) {
     // long before the 32-bit count could wrap: drain, then restart it at zero
@@ -920,8 +884,6 @@ static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStrea
   const int slot = (int)(h->sub % kInFlight);
   h->d_frame = h->d_frames[slot];
   h->hm_frame = h->hm_frames[slot];
-  if (gr) ensure_graph(h, ls, &gr[slot]);
-  const bool graphed = gr && gr[slot].any();
   // eager launches time each kernel with shared events: one frame at a time
   const bool timed = h->eager;
   const hipStream_t ps = one_stream ? st : h->pstream;
@@ -946,12 +908,11 @@ static int submit_set(vio_frontend* h, const LaunchSet& ls, Graphs* gr, hipStrea
     HIP_CHECK(h, enqueue_stage(h, ls, st, 4, timed));
   }
   HIP_CHECK(h, wait_pyr_part(h, ps, st, slot));
-  if (graphed) HIP_CHECK(h, hipGraphLaunch(gr[slot].trk, st));
-  else HIP_CHECK(h, enqueue_track_part(h, ls, st, timed));
+  HIP_CHECK(h, enqueue_track_part(h, ls, st, timed));
   HIP_CHECK(h, hipEventRecord(h->ev[slot][1], st));
   for (int s = ls.stream_begin; s < ls.stream_begin + ls.n_streams; ++s)
     if (h->h_frame->cam[h->streams[s].first_cam].active) h->streams[s].frames += 1;
-  h->pend[(h->pend_head + h->n_pend) % kInFlight] = vio_frontend::Pending{ls, graphed, slot};
+  h->pend[(h->pend_head + h->n_pend) % kInFlight] = vio_frontend::Pending{ls, slot};
   h->n_pend += 1;
   h->sub += 1;
   // a stream staged for a later step but not in this submission keeps its
@@ -981,7 +942,7 @@ static int complete_oldest(vio_frontend* h) {
   float km[kKernels];
   for (int k = 0; k < kKernels; ++k) {
     km[k] = -1.f;
-    if (!p.graphed && h->kran[k]) HIP_CHECK(h, hipEventElapsedTime(&km[k], h->kev[k][0], h->kev[k][1]));
+    if (h->kran[k]) HIP_CHECK(h, hipEventElapsedTime(&km[k], h->kev[k][0], h->kev[k][1]));
   }
   // deferred stereo matching: the tracker and selection run twice per frame
   h->stats.last_stage_ms[0] = km[kKernPyr];
@@ -1031,11 +992,9 @@ static bool one_stream(const vio_frontend* h) {
 }
 
 // Runs one frame of stream s whose level-0 sources are already in h_frame (or
-// queued on st's order) and waits for it; nothing is in flight. Its three
-// launches are made directly: replaying a captured graph costs the host more
-// (mono 320x240 67 -> 56 us a frame).
+// queued on st's order) and waits for it; nothing is in flight.
 static int run_frame(vio_frontend* h, int s, hipStream_t st, bool single) {
-  int rc = submit_set(h, stream_set(h, s), nullptr, st, single);
+  int rc = submit_set(h, stream_set(h, s), st, single);
   if (rc == VIO_OK) rc = complete_all(h);
   return rc;
 }
@@ -1287,7 +1246,7 @@ static int submit_staged(vio_frontend* h, bool waited) {
     for (int k = 0; k < si.n_cams; ++k) h->h_frame->cam[si.first_cam + k].active = si.staged ? 1 : 0;
   }
   if (!any) return fail(h, VIO_ESTATE, "no frame staged");
-  const int rc = submit_set(h, all_set(h), h->graph_all, h->stream, waited && h->n_pend == 0 && one_stream(h));
+  const int rc = submit_set(h, all_set(h), h->stream, waited && h->n_pend == 0 && one_stream(h));
   if (rc != VIO_OK) return rc;
   for (auto& si : h->streams)
     if (si.staged) {
@@ -1647,8 +1606,6 @@ int vio_frontend_set_mlp(vio_frontend* h, const float* params, int32_t n, float 
   HIP_CHECK(h, mlp_pack_launch(h->mlp, h->stream));
   HIP_CHECK(h, hipStreamSynchronize(h->stream));
   if (rho >= 0.f) h->P.learned_rho = rho;
-  // the captured graphs hold the old threshold as a kernel argument
-  for (Graphs& g : h->graph_all) g.destroy();
   h->mlp_ready = true;
   return VIO_OK;
 }
