@@ -155,8 +155,9 @@ struct FrameTable {
 // value in their arguments: the table itself is in pinned host memory until the
 // pyramid launch has copied it, and every workgroup that read it there waited some
 // microseconds for the host link (the pyramid of sixteen streams, 21,000
-// workgroups: 147 us against 99; of one 1280x720 pair 17.4 against 14.3). Entry i: camera `cam` of the i-th active camera
-// of the launch, whose workgroups begin at begin[i] (ascending).
+// workgroups: 147 us against 99; of one 1280x720 pair 17.4 against 14.3). Entry i:
+// a camera of the launch (once for its detection and once for its levels in a split
+// pyramid launch), whose workgroups begin at begin[i] (ascending).
 struct CamArg {
   const uint8_t* src;
   int32_t src_pitch;
