@@ -77,16 +77,10 @@ typedef const __attribute__((address_space(1))) uint8_t* gbytes;
 struct __attribute__((packed)) U16 {
   uint16_t v;
 };
-struct __attribute__((packed)) U32 {
-  uint32_t v;
-};
 
-// unaligned 16- and 32-bit global loads at a 32-bit byte offset
+// unaligned 16-bit global loads at a 32-bit byte offset
 __device__ __forceinline__ uint32_t ld16(gbytes p, uint32_t off) {
   return ((const __attribute__((address_space(1))) U16*)(p + off))->v;
-}
-__device__ __forceinline__ uint32_t ld32(gbytes p, uint32_t off) {
-  return ((const __attribute__((address_space(1))) U32*)(p + off))->v;
 }
 
 // votes of the whole wave (all 64 lanes active)
@@ -281,13 +275,6 @@ __device__ __forceinline__ void template_samples(const Window4& q, float fx, flo
   const float iyp = gfy * h21 + fy * h31, iym = gfy * h01 + fy * h11;
   gx = (ixp - ixm) * 0.5f;
   gy = (iyp - iym) * 0.5f;
-}
-// the 4x4 pixels from global memory (each level buffer has a guard row, so row H
-// stays inside it)
-__device__ __forceinline__ Window4 template_load(const Level& I, float x, float y) {
-  const uint32_t o = (uint32_t)(((int)floorf(y) - 1) * I.pitch + ((int)floorf(x) - 1));
-  const uint32_t pt = (uint32_t)I.pitch;
-  return {{ld32(I.p, o), ld32(I.p, o + pt), ld32(I.p, o + 2u * pt), ld32(I.p, o + 3u * pt)}};
 }
 // the 4x4 pixels from the window at `base` whose first pixel is byte -`first`
 // (y kWinW + x); the address stays in the window for any (x, y)
@@ -1171,7 +1158,7 @@ __device__ __forceinline__ void process_item(const CamDesc* __restrict__ cams, c
 // With the chip full the tracker is bound by instruction issue, and everything
 // but the samples and their first sums is issued once for the two keypoints.
 // Per keypoint the steps, decisions and arithmetic are those of klt_pass, and
-// the sums over the pattern run through the same tree (half_sums), so a half
+// the sums over the pattern run through the same tree (half_sums_pow2), so a half
 // computes what one wave computes for the same keypoint, bit for bit. Levels,
 // iterations and descriptors are the wave's; `act` (uniform across each half)
 // says which halves run the pass. A half that leaves the procedure keeps its
@@ -1269,7 +1256,7 @@ __device__ __forceinline__ float row_lane(float v) {
   return __builtin_bit_cast(float, row_lane<l>(__builtin_bit_cast(int, v)));
 }
 // Sum i of M that klt_pass takes together: the quad parity of the lane it is
-// read from (wave_sums of M), which decides the order of the quads' sums.
+// read from (wave_sums_of M values), which decides the order of the quads' sums.
 constexpr int sum_parity(int M, int i) {
   for (;;) {
     const int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
@@ -1652,9 +1639,6 @@ __device__ __forceinline__ T* lane_ptr(T* p, int src) {
   return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
 }
 __device__ __forceinline__ int lane_int(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
-__device__ __forceinline__ float lane_float(float x, int src) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src));
-}
 
 // store_result for two keypoints per wave: lanes 32h .. 32h + 7 write half h's
 // record (dst of lane 32h; nullptr: none), the other lanes' stores fall

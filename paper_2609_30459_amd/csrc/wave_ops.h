@@ -102,18 +102,8 @@ __device__ __forceinline__ float quad(float v) {
   return quad<q, q, q, q>(v);
 }
 
-// v[i] <- wave sum of v[i] for i < M, in chunks of 16, 8, 4, 2, 1
-template <int M>
-__device__ __forceinline__ void wave_sums(float* v, int lane) {
-  if constexpr (M > 0) {
-    constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
-    wave_sums_pow2<C>(v, lane);
-    wave_sums<M - C>(v + C, lane);
-  }
-}
-
-// out[i] <- wave sum of gen(i) for i in [OFF, OFF + M), chunked and summed as
-// wave_sums<M>, each chunk's values made just before its stages.
+// out[i] <- wave sum of gen(i) for i in [OFF, OFF + M), in chunks of 16, 8,
+// 4, 2 and 1, each chunk's values made just before its stages.
 template <int M, int OFF, class Gen>
 __device__ __forceinline__ void wave_sums_of(float* out, const Gen& gen, int lane) {
   if constexpr (M > 0) {
@@ -182,22 +172,12 @@ __device__ __forceinline__ float half_sums4_paired(const float* keep0, const flo
   return even_quads(rowswap_sum16(row[0] + row[1]));
 }
 
-// a[i] <- half-wave totals of (a[i], b[i]) for i < M, chunked as wave_sums<M>
-template <int M>
-__device__ __forceinline__ void half_sums(float* a, const float* b, int lane) {
-  if constexpr (M > 0) {
-    constexpr int C = M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
-    half_sums_pow2<C>(a, b, lane);
-    half_sums<M - C>(a + C, b + C, lane);
-  }
-}
-
 __device__ __forceinline__ float half_sum(float a, float b, int lane) {
   half_sums_pow2<1>(&a, &b, lane);
   return a;
 }
 
-// Votes over each 32-lane half (all 64 lanes active): the half's all / any,
+// Votes over each 32-lane half (all 64 lanes active): whether it holds on all lanes,
 // decided on the scalar unit from the ballot and handed back to the lanes as a
 // lane mask.
 __device__ __forceinline__ uint64_t half_mask(bool h0, bool h1) {
@@ -206,10 +186,6 @@ __device__ __forceinline__ uint64_t half_mask(bool h0, bool h1) {
 __device__ __forceinline__ bool half_all(bool p, int) {
   const uint64_t m = __ballot(p);
   return __builtin_amdgcn_inverse_ballot_w64(half_mask((uint32_t)m == 0xFFFFFFFFu, (uint32_t)(m >> 32) == 0xFFFFFFFFu));
-}
-__device__ __forceinline__ bool half_any(bool p, int) {
-  const uint64_t m = __ballot(p);
-  return __builtin_amdgcn_inverse_ballot_w64(half_mask((uint32_t)m != 0u, (uint32_t)(m >> 32) != 0u));
 }
 
 template <int ctrl>
