@@ -140,7 +140,7 @@ typedef struct vio_frontend_params {
    * position, id) lends its offset (x_target - x_detecting, y_target -
    * y_detecting): the match starts at p plus that offset with stereo_levels
    * levels (1..levels) and stereo_iters iterations (1..32); without such a
-   * keypoint, the disparity prior with the full budget. */
+   * keypoint at a finite distance, the disparity prior with the full budget. */
   int32_t stereo_init;
   int32_t stereo_levels;
   int32_t stereo_iters;

@@ -995,21 +995,23 @@ static void push_frame(Frontend& F, const uint8_t* const* imgs, const int32_t* s
           ix = (float)mx;
           iy = (float)my;
           ith = (float)mth;
-        } else if (!pairs.empty()) {
-          // nearest by (squared distance, id)
-          size_t best = 0;
-          double bd = dist2(pairs[0].x, pairs[0].y, kp.x, kp.y);
-          for (size_t q = 1; q < pairs.size(); ++q) {
-            const double d = dist2(pairs[q].x, pairs[q].y, kp.x, kp.y);
-            if (d < bd || (d == bd && pairs[q].id < pairs[best].id)) {
+        } else {
+          // nearest by (squared distance, id), among the pairs at a finite distance
+          const Pair* best = nullptr;
+          double bd = std::numeric_limits<double>::infinity();
+          for (const Pair& q : pairs) {
+            const double d = dist2(q.x, q.y, kp.x, kp.y);
+            if (d < bd || (best && d == bd && q.id < best->id)) {
               bd = d;
-              best = q;
+              best = &q;
             }
           }
-          ix = kp.x + pairs[best].dx;
-          iy = kp.y + pairs[best].dy;
-          sL = P.stereo_levels;
-          sN = P.stereo_iters;
+          if (best) {
+            ix = kp.x + best->dx;
+            iy = kp.y + best->dy;
+            sL = P.stereo_levels;
+            sN = P.stereo_iters;
+          }
         }
         const TrackOut<float> r = track<float>(cur[g], cur[tc], kp.x, kp.y, ix, iy, sL, sN, P.fb_threshold, ith);
         int st = r.status == TRACKED ? MATCHED : r.status;

@@ -1073,11 +1073,15 @@ __device__ __forceinline__ Plan plan_item(const CamDesc* __restrict__ cams, cons
           }
         }
         if constexpr (G == kW) bi = __builtin_amdgcn_readfirstlane(bi);
-        const float4 e = pt[bi];
-        pl.ix = px + e.z;
-        pl.iy = py + e.w;
-        pl.fl = tune.slevels;
-        pl.fi = tune.siters;
+        // (no pair may be near: the caller's keypoints can hold infinite or
+        // undefined positions, whose distances never compare as smaller)
+        if (bi < np) {
+          const float4 e = pt[bi];
+          pl.ix = px + e.z;
+          pl.iy = py + e.w;
+          pl.fl = tune.slevels;
+          pl.fi = tune.siters;
+        }
       }
     }
     if (dst->has_ext) {
