@@ -188,15 +188,17 @@ struct Counters {
   int32_t sel_base[kMaxCams];
   int32_t n_sel[kMaxCams];
   int32_t n_pairs[2][kMaxCams];  // entries of CamDesc::pairs, [parity][target camera]
-  // selection: from a stream's camera group (by its detecting camera) to the next
-  // one, twice the next free identifier plus one; zero: not there yet
+  // selection (group_order.h): the next free identifier, from a stream's camera
+  // group (by its detecting camera) to the next one; the workgroups' ticket
   int64_t id_chain[kMaxCams];
+  int32_t select_ticket;
 };
 
 // The selection's workgroups, one per camera group: a detecting camera (mono,
 // a pair's left, a star's first) and the cameras that receive its matches.
 struct SelectGroups {
   int32_t n;
+  int32_t chained;  // a stream has several
   struct {
     uint8_t cam;          // the detecting camera
     uint8_t first, last;  // of its stream

@@ -308,6 +308,7 @@ SelectGroups select_groups(const vio_frontend* h, const LaunchSet& ls) {
     if (!h->cams[c].detect) continue;
     const bool first = a.n == 0 || h->cams[a.g[a.n - 1].cam].stream != h->cams[c].stream;
     if (a.n > 0) a.g[a.n - 1].last = first;
+    if (!first) a.chained = 1;
     a.g[a.n] = {(uint8_t)c, (uint8_t)first, 1, (uint8_t)(first ? 0 : a.g[a.n - 1].cam)};
     a.n += 1;
   }

@@ -32,6 +32,7 @@
 // place in the left state in sel_base / n_sel; kSelectRight accepts the
 // matches (indexed by selection rank) into the right cameras.
 #include "fe_common.h"
+#include "group_order.h"
 #include "wave_ops.h"
 
 namespace vio {
@@ -41,6 +42,23 @@ constexpr int kMaxCells = 8192;
 namespace {
 
 constexpr int kWaves = kSelectThreads / 64;
+
+// group_order.h's memory: device-scope atomics (only the values themselves are
+// passed on), and a wave that waits.
+struct AgentMem {
+  static __device__ __forceinline__ int32_t add(int32_t* p, int32_t v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  template <class T>
+  static __device__ __forceinline__ T load(T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  template <class T>
+  static __device__ __forceinline__ void store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(1); }
+};
 
 struct ScanScratch {
   int wave_tot[2][kWaves];
@@ -356,7 +374,15 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
   // the detecting and the target camera's rows for the neighbour stereo start's pair table
   __shared__ PairRow s_pl[kPairLds], s_pr[kPairLds];
   __shared__ int64_t s_plid[kPairLds];  // s_pl's ids, contiguous for the pair search
-  const auto grp = groups.g[blockIdx.x];
+  // the launch's groups in camera order, or in ticket order where some wait for others
+  int gi = (int)blockIdx.x;
+  if (groups.chained && phase != kSelectRight) {
+    __shared__ int s_group;
+    if (threadIdx.x == 0) s_group = take_group<AgentMem>(&cnt->select_ticket, groups.n);
+    __syncthreads();
+    gi = __builtin_amdgcn_readfirstlane(s_group);
+  }
+  const auto grp = groups.g[gi];
   const int lc = grp.cam;
   const CamDesc& L = cams[lc];
   const FrameCam& fl = frame->cam[lc];
@@ -447,24 +473,12 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const CamDesc* __rest
           s_thr[1] = 0;
         }
         if (tid == 0) {
-          // The group's identifiers follow those of the stream's earlier groups.
-          // (The wait ends: at most kMaxCams workgroups, the earlier ones
-          // started before this one, and the first waits for nobody.)
-          int64_t id0;
-          if (grp.first) {
-            id0 = cnt->next_id[L.stream];
-          } else {
-            int64_t v;
-            while ((v = __hip_atomic_load(&cnt->id_chain[grp.prev], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0)
-              __builtin_amdgcn_s_sleep(1);
-            __hip_atomic_store(&cnt->id_chain[grp.prev], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            id0 = v >> 1;
-          }
+          // the group's identifiers follow those of the stream's earlier groups
+          const int64_t id0 = grp.first ? cnt->next_id[L.stream] : take_id<AgentMem>(&cnt->id_chain[grp.prev]);
           s_id0 = id0;
           const int64_t next = id0 + min(room, total);
           if (grp.last) cnt->next_id[L.stream] = next;
-          else
-            __hip_atomic_store(&cnt->id_chain[lc], next << 1 | 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else hand_on_id<AgentMem>(&cnt->id_chain[lc], next);
         }
       }
       __syncthreads();
