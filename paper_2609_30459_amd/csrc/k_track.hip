@@ -153,10 +153,6 @@ constexpr int kWinW = 24, kWinH = 21, kWinLead = 9;
 constexpr int kWinWords = 128;
 constexpr int kWinBytes = 4 * kWinWords;
 static_assert(kWinW % 4 == 0 && kWinW / 4 * kWinH <= kWinWords, "a window is two loads of 64 dwords");
-// a block's windows, [wave][image][keypoint][level], aligned to a window; a template's
-// reads run up to three rows and one dword past its first
-template <int L, int KP = 1>
-constexpr int kWinBlock = kTrackWaves * KP * 2 * L * kWinWords + 3 * (kWinW / 4) + 2;
 typedef __attribute__((address_space(3))) uint32_t* lds_words;
 
 // The windows of one image's levels: lane l holds level l's position (a wave's
@@ -1719,6 +1715,33 @@ __device__ __forceinline__ void process_pair(const CamDesc* __restrict__ cams, c
   store_result2(me.out, r, lane);
 }
 
+// A workgroup's LDS, sized by the waves that it is launched with (at fixed room for
+// four, workgroups of one wave filled the compute units' LDS with one wave to a
+// SIMD): the windows [wave][image][keypoint][level], aligned to a window; with the
+// learned stage fused a row for the network per wave; the plans. (A template's
+// reads run up to three rows and one dword past its window: they stay inside,
+// their values unused.) 7,680 items, two keypoints a wave, workgroups of 1, 2 and 4
+// waves: 4 levels 125, 92 and 65 us with room for four, 68, 67 and 66 so; 5 levels
+// 183, 122 and 89, and 86, 86 and 89.
+extern __shared__ __align__(kWinBytes) uint32_t sTrack[];
+template <int L, int KP, bool F>
+struct TrackLds {
+  static constexpr int kWindows = 2 * KP * L * kWinBytes, kRow = F ? (MI + MH) * (int)sizeof(uint16_t) : 0,
+                       kPlans = KP * (int)sizeof(Plan);
+  static_assert(kPlans >= 3 * kWinW + 8 && kRow % 16 == 0, "the last window's reads, the rows' alignment");
+  static constexpr uint32_t bytes(int waves) { return (uint32_t)(waves * (kWindows + kRow + kPlans)); }
+  lds_words win;
+  uint16_t* row;
+  Plan* plans;
+  __device__ __forceinline__ TrackLds() {
+    const int wave = uniform((int)threadIdx.x / kW), waves = (int)blockDim.x / kW;
+    uint8_t* base = reinterpret_cast<uint8_t*>(sTrack);
+    win = (lds_words)sTrack + wave * (kWindows / 4);
+    row = reinterpret_cast<uint16_t*>(base + waves * kWindows + wave * kRow);
+    plans = reinterpret_cast<Plan*>(base + waves * (kWindows + kRow) + wave * kPlans);
+  }
+};
+
 // One wave per work item. F: the learned stage is fused (each wave has a row
 // of LDS for the network).
 template <int L, bool F>
@@ -1734,18 +1757,11 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track(const CamDesc* __rest
   // registers, loaded through the scalar cache)
   const int k = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (int)(blockDim.x / kW) + (int)(threadIdx.x / kW));
   if (k >= n_items) return;
-  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L>];
-  __shared__ Plan sPlan[kTrackWaves];
-  uint16_t* sx = nullptr;
-  if constexpr (F) {
-    __shared__ __align__(16) uint16_t sLearn[kTrackWaves][MI + MH];
-    sx = sLearn[threadIdx.x / kW];
-  }
+  const TrackLds<L, 1, F> lds;
   float u, v, wgt;
   pattern_of(lane, u, v, wgt);
-  process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx,
-                     (lds_words)sWin + uniform((int)threadIdx.x / kW) * (2 * L * kWinWords),
-                     &sPlan[uniform((int)threadIdx.x / kW)]);
+  process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, lds.row,
+                     lds.win, lds.plans);
 }
 
 // Persistent grid: every wave pops items from the frame's queue counter until
@@ -1762,21 +1778,14 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamD
                                                                      const Prediction* __restrict__ pred,
                                                                      Tuning tune, int queue) {
   const int lane = threadIdx.x & (kW - 1);
-  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L>];
-  __shared__ Plan sPlan[kTrackWaves];
-  uint16_t* sx = nullptr;
-  if constexpr (F) {
-    __shared__ __align__(16) uint16_t sLearn[kTrackWaves][MI + MH];
-    sx = sLearn[threadIdx.x / kW];
-  }
+  const TrackLds<L, 1, F> lds;
   float u, v, wgt;
   pattern_of(lane, u, v, wgt);
   for (;;) {
     const int k = __builtin_amdgcn_readfirstlane(atomicAdd(&frame->queue_head[queue], lane == 0 ? 1 : 0));
     if (k >= n_items) break;
-    process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, sx,
-                       (lds_words)sWin + uniform((int)threadIdx.x / kW) * (2 * L * kWinWords),
-                     &sPlan[uniform((int)threadIdx.x / kW)]);
+    process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, lds.row,
+                       lds.win, lds.plans);
     wave_sync_lds();  // the next item's plan overwrites this one's
   }
 }
@@ -1793,14 +1802,13 @@ __global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu
   const int lane = threadIdx.x & (kW - 1);
   const int k = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (int)(blockDim.x / kW) + (int)(threadIdx.x / kW));
   if (2 * k >= n_items) return;
-  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L, 2>];
-  __shared__ Plan sPlan[kTrackWaves][2];
+  const TrackLds<L, 2, false> lds;
   float u[2], v[2], w0, wb;
   pattern_of(lane & 31, u[0], v[0], w0);
   pattern_of((lane & 31) + 32, u[1], v[1], wb);
   const int it = 2 * k + (lane >> 5);
   process_pair<L>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + it, it < n_items, lane, u, v, wb,
-                  (lds_words)sWin + uniform((int)threadIdx.x / kW) * (4 * L * kWinWords), sPlan[threadIdx.x / kW]);
+                  lds.win, lds.plans);
 }
 
 // The persistent grid with two items per wave: each pop takes two items.
@@ -1813,8 +1821,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const Cam
                                                                       const Prediction* __restrict__ pred,
                                                                       Tuning tune, int queue) {
   const int lane = threadIdx.x & (kW - 1);
-  __shared__ __align__(kWinBytes) uint32_t sWin[kWinBlock<L, 2>];
-  __shared__ Plan sPlan[kTrackWaves][2];
+  const TrackLds<L, 2, false> lds;
   float u[2], v[2], w0, wb;
   pattern_of(lane & 31, u[0], v[0], w0);
   pattern_of((lane & 31) + 32, u[1], v[1], wb);
@@ -1823,7 +1830,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const Cam
     if (k >= n_items) break;
     const int it = k + (lane >> 5);
     process_pair<L>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + it, it < n_items, lane, u, v, wb,
-                    (lds_words)sWin + uniform((int)threadIdx.x / kW) * (4 * L * kWinWords), sPlan[threadIdx.x / kW]);
+                    lds.win, lds.plans);
     wave_sync_lds();  // the next item's plan overwrites this one's
   }
 }
@@ -1838,23 +1845,23 @@ hipError_t launch_LF(const CamDesc* d_cams, FrameTable* d_frame, Counters* d_cnt
     const int blocks = (waves + bw - 1) / bw;
     if constexpr (!F) {
       if (sh.kp_per_wave == 2) {
-        launch_kernel(k_track2_persistent<L>, dim3(blocks), dim3(kW * bw), 0, s, d_cams, d_frame, d_cnt, d_segs,
+        launch_kernel(k_track2_persistent<L>, dim3(blocks), dim3(kW * bw), TrackLds<L, 2, false>::bytes(bw), s, d_cams, d_frame, d_cnt, d_segs,
                       n_segs, item_base, n_items, d_pred, tune, sh.queue);
         return hipGetLastError();
       }
     }
-    launch_kernel(k_track_persistent<L, F>, dim3(blocks), dim3(kW * bw), 0, s, d_cams, d_frame, d_cnt, d_segs,
+    launch_kernel(k_track_persistent<L, F>, dim3(blocks), dim3(kW * bw), TrackLds<L, 1, F>::bytes(bw), s, d_cams, d_frame, d_cnt, d_segs,
                   n_segs, item_base, n_items, d_pred, tune, sh.queue);
   } else {
     const int blocks = (item_waves + bw - 1) / bw;
     if constexpr (!F) {
       if (sh.kp_per_wave == 2) {
-        launch_kernel(k_track2<L>, dim3(blocks), dim3(kW * bw), 0, s, d_cams, d_frame, d_cnt, d_segs, n_segs,
+        launch_kernel(k_track2<L>, dim3(blocks), dim3(kW * bw), TrackLds<L, 2, false>::bytes(bw), s, d_cams, d_frame, d_cnt, d_segs, n_segs,
                       item_base, n_items, d_pred, tune);
         return hipGetLastError();
       }
     }
-    launch_kernel(k_track<L, F>, dim3(blocks), dim3(kW * bw), 0, s, d_cams, d_frame, d_cnt, d_segs, n_segs,
+    launch_kernel(k_track<L, F>, dim3(blocks), dim3(kW * bw), TrackLds<L, 1, F>::bytes(bw), s, d_cams, d_frame, d_cnt, d_segs, n_segs,
                   item_base, n_items, d_pred, tune);
   }
   return hipGetLastError();
