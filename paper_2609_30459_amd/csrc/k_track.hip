@@ -1764,13 +1764,32 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track(const CamDesc* __rest
                      lds.win, lds.plans);
 }
 
-// Persistent grid: every wave pops items from the frame's queue counter until
-// it runs past n_items (each pop advances the counter, so every wave exits).
-// The pop is branch-free: all lanes issue the atomic, lane 0 adding one and
-// the others zero, and the first lane's (lane 0's) old value is the item, so
-// no lane-dependent control flow enters the loop.
+// Persistent grid: a wave's first KP items are those of its number, and then it
+// takes the next ones of the frame's queue counter until it runs past n_items
+// (each take advances the counter, so every wave exits). The counter is the
+// bound of many waves (an atomic on it ends every 13 ns or so), so the first items do
+// not pass through it. 15,360 items of 4 levels, 4 and 16 waves to a compute unit:
+// one keypoint a wave 342 and 286 us with all items from the counter, 309 and 258
+// so; two 244 and 176, and 241 and 142. (One keypoint, 4 levels: 137 registers, three
+// waves to a SIMD; held to four, 16 waves to a compute unit take 115 us for 7,680
+// items instead of 133, 4 take 167 instead of 162.)
+template <int KP>
+__device__ __forceinline__ int first_item() {
+  return uniform(KP * ((int)blockIdx.x * ((int)blockDim.x / kW) + (int)threadIdx.x / kW));
+}
+// The take is branch-free: a buffer of one word, in whose range only lane 0's
+// atomic falls (the hardware drops the others), so no lane-dependent control flow
+// enters the loop. (An atomic of all lanes, the others adding zero, becomes a loop
+// over the 64 lanes' values.)
+template <int KP>
+__device__ __forceinline__ int next_items(int32_t* head, int lane) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(head, (short)0, 4, kBufferWord3);
+  return KP * (int)gridDim.x * ((int)blockDim.x / kW) +
+         uniform(__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(KP, rs, lane * 4, 0, 0));
+}
+
 template <int L, bool F>
-__global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamDesc* __restrict__ cams,
+__global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu(!F && L == 4 ? 4 : 1))) void k_track_persistent(const CamDesc* __restrict__ cams,
                                                                      FrameTable* __restrict__ frame,
                                                                      const Counters* __restrict__ cnt,
                                                                      const TrackSeg* __restrict__ segs, int n_segs,
@@ -1781,9 +1800,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track_persistent(const CamD
   const TrackLds<L, 1, F> lds;
   float u, v, wgt;
   pattern_of(lane, u, v, wgt);
-  for (;;) {
-    const int k = __builtin_amdgcn_readfirstlane(atomicAdd(&frame->queue_head[queue], lane == 0 ? 1 : 0));
-    if (k >= n_items) break;
+  for (int k = first_item<1>(); k < n_items; k = next_items<1>(&frame->queue_head[queue], lane)) {
     process_item<L, F>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + k, lane, u, v, wgt, lds.row,
                        lds.win, lds.plans);
     wave_sync_lds();  // the next item's plan overwrites this one's
@@ -1813,7 +1830,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu
 
 // The persistent grid with two items per wave: each pop takes two items.
 template <int L>
-__global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const CamDesc* __restrict__ cams,
+__global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_track2_persistent(const CamDesc* __restrict__ cams,
                                                                       FrameTable* __restrict__ frame,
                                                                       const Counters* __restrict__ cnt,
                                                                       const TrackSeg* __restrict__ segs, int n_segs,
@@ -1825,9 +1842,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) void k_track2_persistent(const Cam
   float u[2], v[2], w0, wb;
   pattern_of(lane & 31, u[0], v[0], w0);
   pattern_of((lane & 31) + 32, u[1], v[1], wb);
-  for (;;) {
-    const int k = __builtin_amdgcn_readfirstlane(atomicAdd(&frame->queue_head[queue], lane == 0 ? 2 : 0));
-    if (k >= n_items) break;
+  for (int k = first_item<2>(); k < n_items; k = next_items<2>(&frame->queue_head[queue], lane)) {
     const int it = k + (lane >> 5);
     process_pair<L>(cams, frame, cnt, segs, n_segs, pred, tune, item_base + it, it < n_items, lane, u, v, wb,
                     lds.win, lds.plans);
