@@ -173,10 +173,10 @@ typedef struct vio_frontend_params {
    * pyramid. */
   int32_t pyramid_stream;
   /* Launch choice that never changes the records: keypoints per tracking
-   * wavefront. 0: by the number of keypoints a launch may hold (about six per
-   * SIMD: 2 from there on). 1: one wave64 per keypoint, a lane per pattern point
-   * (the shortest chain per keypoint: few keypoints, one frame at a time);
-   * 2: two keypoints per wave, one per 32-lane half, two pattern points per
+   * wavefront. 0: by the number of keypoints a launch may hold (2 from about six
+   * per SIMD on, at five and six levels from three). 1: one wave64 per keypoint, a
+   * lane per pattern point (the shortest chain per keypoint: few keypoints, one
+   * frame at a time); 2: two keypoints per wave, one per 32-lane half, two pattern points per
    * lane (fewer instructions per keypoint: many keypoints, batched streams).
    * 2 needs learned_fused = 0 when init_mode is VIO_INIT_LEARNED. */
   int32_t track_kp_per_wave;

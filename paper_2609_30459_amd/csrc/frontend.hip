@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "fe_common.h"
+#include "launch_rules.h"
 #include "vio_mlp.h"
 
 using namespace vio;
@@ -760,18 +761,14 @@ static LaunchSet all_set(const vio_frontend* h) {
 // `queue`: the frame's work-queue counter this launch's persistent grid pops
 // (each tracking launch of a frame has its own).
 //
-// Keypoints per wave, unless the caller chose: two are bound by half the waves'
-// longer chains, one by instruction issue, so two from about six items per SIMD
-// on: 2 x 752x480 streams of 960 items: four 42.7 us with one and 46.5 with two,
-// six 61.5 and 58.1, twelve 101.8 and 93.6; mono 320x240 of 200 items, sixteen
-// 32.9 and 35.4, 32 53.2 and 52.0; a rig of 10,560 items of five levels 128.8
-// and 114.6. Deferred matches are few however many items they could be (the rig
-// 101.8 and 115.3 in all); the fused learned stage and a caller's persistent
+// Keypoints per wave, unless the caller chose: by the items (launch_rules.h).
+// Deferred matches are few however many items they could be (the rig 101.8 us with
+// one and 115.3 with two in all); the fused learned stage and a caller's persistent
 // grid take one.
 static hipError_t track_range(vio_frontend* h, const LaunchSet& ls, int seg_begin, int n_segs, int item_begin,
                               int n_items, const Tuning& tune, int queue, hipStream_t st) {
-  const bool many = n_items > 24 * h->n_cus && !(tune.deferred && queue == 1) && !(tune.learned && tune.fused) &&
-                    h->P.track_waves_per_cu == 0;
+  const bool many = two_keypoints_a_wave(n_items, h->n_cus, tune.levels) && !(tune.deferred && queue == 1) &&
+                    !(tune.learned && tune.fused) && h->P.track_waves_per_cu == 0;
   return launch_track(h->d_cams, h->d_frame, h->d_cnt, (ls.all ? h->d_segs_all : h->d_segs) + seg_begin, n_segs,
                       item_begin, n_items, h->d_pred, tune,
                       TrackShape{h->P.track_waves_per_cu,
