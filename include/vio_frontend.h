@@ -100,8 +100,8 @@ typedef struct vio_frontend_params {
                                  of this many waves per compute unit over a shared work queue */
   int32_t track_block_waves;  /* waves per tracking workgroup: 1, 2 or 4 (0 = 4) */
   int32_t pyr_tile;           /* level-0 tile edge of the pyramid/detector kernel: 32 (256-thread workgroups)
-                                 or 64 (1024 or 512); 0 = by the number of tiles (64, or 32 when the handle's
-                                 cameras have few; the same records) */
+                                 or 64 (1024 or 512); 0 = by the number of tiles and levels (64, or 32 up to four levels
+                                 when the handle's cameras have few; the same records) */
   int32_t stereo_mode;        /* VIO_STEREO_SPECULATIVE: the tracking launch also matches every cell
                                  winner left to right, selection keeps the selected ones' matches (fewest
                                  dependent launches); VIO_STEREO_DEFERRED: only the selected detections are

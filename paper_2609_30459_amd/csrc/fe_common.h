@@ -13,11 +13,6 @@ namespace vio {
 constexpr int kMaxLevels = VIO_MAX_LEVELS;
 constexpr int kMaxCams = VIO_MAX_CAMERAS;
 constexpr int kPatch = 52;      // pattern points (Sec. III-E)
-constexpr int kTileDefault = 64;  // level-0 tile edge of the pyramid/detector kernel unless chosen
-// Handles of at most so many 64-px tiles (half the compute units) take 32-px ones unless chosen:
-// mono 320x240 (20) 7.4 us with 64-px tiles, 6.3 with 32-px ones; 641x479 (88) 13.2 and 12.6;
-// two 752x480 (192) 10.5 and 11.3.
-constexpr int kFewTiles = 128;
 // Row pitch of a pyramid level `width` pixels wide.
 __host__ __device__ constexpr int level_pitch(int width) { return (width + 63) & ~63; }
 // Kernel timing: while set, the frontend's kernel launches on this thread

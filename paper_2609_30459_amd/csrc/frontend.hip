@@ -86,7 +86,7 @@ enum {
 struct vio_frontend {
   vio_frontend_params P{};
   int n_cus = 256;
-  int tile = kTileDefault;  // pyramid/detector tile edge
+  int tile = 64;  // pyramid/detector tile edge
   std::vector<StreamInfo> streams;
   std::vector<CamDesc> cams;
   std::vector<TrackSeg> segs;      // per stream: the stream's items are contiguous
@@ -317,20 +317,17 @@ SelectGroups select_groups(const vio_frontend* h, const LaunchSet& ls) {
 }
 
 // The pyramid launch: a tile's detection and levels in one workgroup, one after
-// the other, or in two. Two stage the tile twice and so take longer when the chip
-// is full, but halve the chain while all of them fit at once: two 1,024-thread
-// workgroups to a compute unit; of the 256-thread ones, whose chains are short,
-// four by measurement. With 64-px tiles: mono 320x240 (40 workgroups) 9.2 -> 7.8
-// us, stereo 752x480 (384) 13.1 -> 10.7, star 752x480 (480) 14.1 -> 11.9, but
-// stereo 1280x720 (960) 13.8 -> 20.9; with 32-px ones mono 320x240 (160) 8.6 ->
-// 6.8, mono 641x479 (630) 16.3 -> 14.4, star 752x480 (1,800) 12.3 -> 12.8.
+// the other, or in two (launch_rules.h).
 LaunchCams pyramid_args(const vio_frontend* h, const LaunchSet& ls) {
   LaunchCams a{};
   const auto tiles = [](const CamDesc& c) { return c.tiles_x * c.tiles_y; };
-  int split = 0;  // workgroups of a split launch
+  int split = 0, joined = 0;  // workgroups of a launch of either kind
   for (int c = ls.cam_begin; c < ls.cam_end; ++c)
-    if (h->h_frame->cam[c].active) split += tiles(h->cams[c]) * (h->cams[c].detect ? 2 : 1);
-  if (split <= h->n_cus * (h->tile == 32 ? 4 : 2) && 2 * (ls.cam_end - ls.cam_begin) <= kMaxCams) {
+    if (h->h_frame->cam[c].active) {
+      joined += tiles(h->cams[c]);
+      split += tiles(h->cams[c]) * (h->cams[c].detect ? 2 : 1);
+    }
+  if (split_pyramid(split, joined, h->tile, h->P.levels, h->n_cus) && 2 * (ls.cam_end - ls.cam_begin) <= kMaxCams) {
     add_launch_cams(h, ls, kArgDetect, [&](const CamDesc& c) { return c.detect ? tiles(c) : 0; }, a);
     add_launch_cams(h, ls, kArgLevels, tiles, a);
   } else {
@@ -697,7 +694,7 @@ int vio_frontend_create(const vio_stream_desc* streams, int32_t n_streams, const
   int tiles = 0;
   for (int s = 0; s < n_streams; ++s)
     tiles += streams[s].n_cameras * ((streams[s].width + 63) / 64) * ((streams[s].height + 63) / 64);
-  h->tile = params->pyr_tile ? params->pyr_tile : tiles <= kFewTiles ? 32 : kTileDefault;
+  h->tile = params->pyr_tile ? params->pyr_tile : default_pyr_tile(tiles, params->levels);
   const int rc = create_impl(h, streams, n_streams);
   if (rc != VIO_OK) {
     vio_frontend_destroy(h);

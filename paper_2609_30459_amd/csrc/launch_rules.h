@@ -21,4 +21,32 @@ inline bool two_keypoints_a_wave(int n_items, int n_cus, int levels) {
   return n_items > (levels >= 5 ? 12 : 24) * n_cus;
 }
 
+// Level-0 tile edge of the pyramid and detector for a handle whose cameras have so
+// many 64-px tiles: 32 px for few of them (up to about half the compute units) up to
+// four levels. Above, a 32-px tile's apron and its 256 threads cost more than the
+// larger number of workgroups gives (it stages 8.6 bytes a pixel at five levels and
+// 24 at six, a 64-px one 3.9 and 8.8). 64 and 32 px: mono 160x120 (6 tiles) 6.3 and
+// 5.7 us at three levels, 7.3 and 7.5 at four, 9.5 and 11.8 at five, 15.7 and 23.0 at
+// six; 320x240 (20) 7.3 and 7.2, 7.9 and 7.7, 11.1 and 12.4, 20.3 and 28.0; 641x479
+// (88) 7.9 and 7.8, 8.3 and 8.5, 11.5 and 14.5, 20.9 and 36.5; two 752x480 (192) 8.1
+// and 7.9, 10.1 and 10.4, 14.2 and 15.7, 24.0 and 45.9.
+inline int default_pyr_tile(int tiles64, int levels) { return tiles64 <= 128 && levels <= 4 ? 32 : 64; }
+
+// Whether a tile's detection and levels run in a workgroup each (`split` workgroups
+// in all) instead of one after the other in one (`joined`). Two stage the tile
+// twice, but halve the chain while all of them have a place at once: to a compute
+// unit as many as the chains of their threads and their LDS allow, by measurement.
+// In one and in two, 64-px tiles of four levels: 240 (joined 160) 11.0 and 8.5 us,
+// 288 (192) 10.7 and 10.1, 480 (320) 12.7 and 11.9, 576 (384) 13.3 and 13.8; but 480
+// (240) 11.4 and 12.6: where the joined ones have a compute unit each, up to 1.5 to one.
+// Five levels: 240 14.5 and 11.9, 288 14.2 and 15.2, 480 (240) 14.3 and 18.8; six: 240
+// 23.7 and 21.3, 288 24.0 and 27.0. 32-px tiles: four levels, 900 10.6 and 9.3, 1,080
+// 10.4 and 10.6; five, 720 15.9 and 15.6, 900 15.9 and 16.1; six, 390 31.0 and 29.3,
+// 600 33.4 and 36.6.
+inline bool split_pyramid(int split, int joined, int tile, int levels, int n_cus) {
+  if (tile == 32) return split <= n_cus * (levels <= 4 ? 4 : levels == 5 ? 3 : 2);
+  if (levels > 4) return split <= n_cus;
+  return split <= 2 * n_cus && (joined > n_cus || 2 * split <= 3 * n_cus);
+}
+
 }  // namespace vio

@@ -34,6 +34,16 @@ def test_keypoints_per_wave_rule(rule):
     assert got == 4 * [0, 0, 0, 0, 1, 1] + 2 * [0, 0, 1, 1, 1, 1]
 
 
+def test_pyramid_rules(rule):
+    got = rule("for (int l = 1; l <= 6; ++l) for (int n : {1, 128, 129, 4000}) printf(\"%d \", default_pyr_tile(n, l));")
+    assert got == 4 * [32, 32, 64, 64] + 2 * [64, 64, 64, 64]
+    # the largest split launch whose joined one has 300 workgroups, and 200
+    body = ("for (int j : {300, 200}) for (int t : {32, 64}) for (int l = 1; l <= 6; ++l) { int m = 0;"
+            "for (int s = 1; s < 5000; ++s) if (split_pyramid(s, j, t, l, 256)) m = s; printf(\"%d \", m); }")
+    small = [1024] * 4 + [768, 512]
+    assert rule(body) == small + [512] * 4 + [256] * 2 + small + [384] * 4 + [256] * 2
+
+
 def kernels_of(step):
     """Names of the library's kernels that step() launches."""
     import torch
@@ -76,3 +86,19 @@ def test_keypoints_per_wave_taken(n, extra, name):
             for s in range(n):
                 ra, rb = a.get_tracks(s), b.get_tracks(s)
                 assert len(ra) > 100 and ra.tobytes() == rb.tobytes(), (t, s)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cams,w,h,levels,name", [
+    (1, 320, 240, 4, "k_pyr_detect<4, 32, 256>"), (1, 320, 240, 5, "k_pyr_detect<5, 64, 1024>"),
+    (1, 320, 240, 6, "k_pyr_detect<6, 64, 1024>"), (2, 1280, 720, 4, "k_pyr_detect<4, 64, 1024>"),
+    (2, 1920, 1080, 4, "k_pyr_detect<4, 64, 512>"), (2, 1920, 1080, 6, "k_pyr_detect<6, 64, 1024>")])
+def test_pyramid_taken(cams, w, h, levels, name):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_30459_amd as vf
+    dev = torch.randint(0, 256, (cams, h, w), dtype=torch.uint8, device="cuda")
+    with vf.Frontend([(cams, w, h, 300, 48)], vf.make_params(levels=levels)) as fe:
+        ks = kernels_of(lambda: fe.push_stereo_frame_device(0, 1, list(dev)))
+    assert [k for k in ks if k.startswith("k_pyr")] == [name], ks
