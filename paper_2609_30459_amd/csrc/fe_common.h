@@ -81,7 +81,7 @@ struct CamDesc {
                        // (1: a stereo pair's right camera, 3: a star rig's other cameras)
   int stream;
   int local;           // camera index within its stream
-  int tiles_x, tiles_y, tile_begin;  // pyramid/detector tiles of this camera
+  int tiles_x, tiles_y;  // pyramid/detector tiles of this camera
   int pitch[kMaxLevels];
   uint8_t* lvl[kPyrSlots][kMaxLevels];  // pyramid slots (frame index mod kPyrSlots: the frames in flight
                                         // and the one before them)

@@ -46,7 +46,6 @@ struct StreamInfo {
   int first_cam, n_cams, w, h, cap, cell;
   int64_t frames = 0;
   int64_t last_t = 0;
-  int tile_begin = 0, n_tiles = 0;
   int seg_begin = 0, n_segs = 0, item_begin = 0, n_items = 0;
   int st_segs = 0, st_items = 0;  // the stream's stereo segments/items come first
   int64_t done = 0;        // frames whose records are ready (frames - done are in flight)
@@ -66,7 +65,7 @@ thread_local KernelTiming vio::tl_timing;
 
 // A set of cameras/streams launched together: one stream (push) or all (step).
 struct LaunchSet {
-  int cam_begin, cam_end, tile_begin, n_tiles, seg_begin, n_segs, item_begin, n_items, stream_begin, n_streams;
+  int cam_begin, cam_end, seg_begin, n_segs, item_begin, n_items, stream_begin, n_streams;
   bool all;               // every stream: the batched item order (segs_all)
   int st_segs, st_items;  // the leading stereo segments/items of the range
 };
@@ -91,7 +90,6 @@ struct vio_frontend {
   std::vector<CamDesc> cams;
   std::vector<TrackSeg> segs;      // per stream: the stream's items are contiguous
   std::vector<TrackSeg> segs_all;  // the same items in the batched step's order
-  int total_tiles = 0;
   size_t rec_total = 0;
   // device
   void* arena = nullptr;
@@ -415,7 +413,7 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
   // parallel fallbacks exist where a temporal track may first run a short budget
   const bool par_fb = P.track_parallel_fallback && (P.init_mode == VIO_INIT_LEARNED || P.pred_levels > 0);
   std::vector<CamOffs> co(n_cams);
-  int cam = 0, tiles = 0, rows_total = 0, items = 0;
+  int cam = 0, rows_total = 0, items = 0;
   size_t rec_total = 0, stage = 0;
   for (int s = 0; s < n_streams; ++s) {
     StreamInfo si;
@@ -425,7 +423,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
     si.h = sd[s].height;
     si.cap = sd[s].max_keypoints > 0 ? sd[s].max_keypoints : P.max_keypoints;
     si.cell = sd[s].cell_size > 0 ? sd[s].cell_size : P.cell_size;
-    si.tile_begin = tiles;
     si.rec_off = rec_total;
     si.seg_begin = (int)h->segs.size();
     si.item_begin = items;
@@ -451,8 +448,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
       c.local = k;
       c.tiles_x = (si.w + h->tile - 1) / h->tile;
       c.tiles_y = (si.h + h->tile - 1) / h->tile;
-      c.tile_begin = tiles;
-      tiles += c.tiles_x * c.tiles_y;
       for (int l = 0; l < P.levels; ++l) {
         c.pitch[l] = level_pitch(si.w >> l);
         // one guard row: the tracker's template window reads up to one row and
@@ -506,7 +501,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
     }
     si.n_segs = (int)h->segs.size() - si.seg_begin;
     si.n_items = items - si.item_begin;
-    si.n_tiles = tiles - si.tile_begin;
     si.rec_n = rec_total - si.rec_off;
     h->streams.push_back(si);
   }
@@ -520,7 +514,6 @@ static int create_impl(vio_frontend* h, const vio_stream_desc* sd, int32_t n_str
           at += g.count;
         }
   }
-  h->total_tiles = tiles;
   h->rec_total = rec_total;
   h->pred_cap = 0;
   for (auto& c : h->cams) h->pred_cap += c.cap;
@@ -741,16 +734,16 @@ static Tuning tuning(const vio_frontend* h) {
 
 static LaunchSet stream_set(const vio_frontend* h, int s) {
   const StreamInfo& si = h->streams[s];
-  return {si.first_cam, si.first_cam + si.n_cams, si.tile_begin, si.n_tiles, si.seg_begin, si.n_segs,
-          si.item_begin, si.n_items, s, 1, false, si.st_segs, si.st_items};
+  return {si.first_cam, si.first_cam + si.n_cams, si.seg_begin, si.n_segs, si.item_begin, si.n_items, s, 1, false,
+          si.st_segs, si.st_items};
 }
 
 static LaunchSet all_set(const vio_frontend* h) {
   const StreamInfo& last = h->streams.back();
   int st_segs = 0, st_items = 0;
   for (const StreamInfo& si : h->streams) st_segs += si.st_segs, st_items += si.st_items;
-  return {0, (int)h->cams.size(), 0, h->total_tiles, 0, (int)h->segs_all.size(), 0, last.item_begin + last.n_items, 0,
-          (int)h->streams.size(), true, st_segs, st_items};
+  return {0, (int)h->cams.size(), 0, (int)h->segs_all.size(), 0, last.item_begin + last.n_items, 0, (int)h->streams.size(),
+          true, st_segs, st_items};
 }
 
 // Tracking launch over segments [seg_begin, seg_begin + n_segs) of the set's
