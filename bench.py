@@ -210,9 +210,9 @@ def main():
     ap.add_argument("--learned-fused", type=int, choices=[0, 1], default=None,
                     help="learned stage inside the tracker launch (default: on for one stream, off when batched)")
     ap.add_argument("--kp-per-wave", type=int, choices=[1, 2], default=None,
-                    help="keypoints per tracking wavefront (default: the autotuned choice, else 1); 2 needs the "
-                         "learned stage in its own launch")
-    ap.add_argument("--tile", type=int, default=None, help="pyramid/detector tile edge (32, 64)")
+                    help="keypoints per tracking wavefront (default: the autotuned choice, else the library's); 2 needs "
+                         "the learned stage in its own launch")
+    ap.add_argument("--tile", type=int, default=None, help="pyramid/detector tile edge (32, 64; default: the autotuned choice, else the library's)")
     ap.add_argument("--stereo-mode", type=int, default=None, help="0 speculative, 1 deferred stereo matching")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="BYTES",
                     help="only run device-to-device copies of BYTES bytes (counter calibration)")
@@ -270,7 +270,8 @@ def main():
                        not args.levels and not args.iters)
 
     def launch_choice(init):
-        """Launch parameters (never change the records): explicit flags, else the autotuned choice."""
+        """Launch parameters (never change the records): explicit flags, else the autotuned choice, else the
+        library's own (0)."""
         wpc, bw, tile, smode = args.waves_per_cu, args.block_waves, args.tile, args.stereo_mode
         pfb, lbw, lfu, kpw = args.parallel_fallback, args.learned_block_waves, args.learned_fused, args.kp_per_wave
         tuned = None
@@ -279,7 +280,7 @@ def main():
             tuned = autotune.lookup(args.workload, init)
             if tuned:
                 wpc, bw = tuned["track_waves_per_cu"], tuned["track_block_waves"]
-                tile, smode = tuned.get("pyr_tile", 64), tuned.get("stereo_mode", 0)
+                tile, smode = tuned.get("pyr_tile", 0), tuned.get("stereo_mode", 0)
                 if pfb is None and "track_parallel_fallback" in tuned:
                     pfb = tuned["track_parallel_fallback"]
                 if lbw is None and "learned_block_waves" in tuned:
@@ -294,11 +295,11 @@ def main():
             lfu = 0  # the fused learned stage runs one keypoint per wave
         if lfu is None:
             lfu = 0 if batched else 1
-        return dict(track_waves_per_cu=wpc or 0, track_block_waves=bw or 4, pyr_tile=tile or 64,
+        return dict(track_waves_per_cu=wpc or 0, track_block_waves=bw or 0, pyr_tile=tile or 0,
                     stereo_mode=smode or 0, track_parallel_fallback=pfb if init == "learned" else 0,
                     learned_block_waves=(lbw or 0) if init == "learned" else 0,
                     learned_fused=lfu if init == "learned" else 0, pyramid_stream=args.pyramid_stream,
-                    track_kp_per_wave=kpw or 1), \
+                    track_kp_per_wave=kpw or 0), \
             tuned is not None
 
     mlp = None
