@@ -1063,9 +1063,13 @@ static void fill_frame(vio_frontend* h, int s) {
 // Copies host images of stream s into pinned staging and queues their upload
 // on `st` into the current pyramid slot's level 0: rows at the level's pitch, so
 // that the upload is a linear copy (a two-dimensional one of 641-byte rows took
-// 3.4 ms, row by row, against 14 us): one kernel for all cameras of small frames,
-// one per camera beside the next one's staging for larger ones.
-constexpr size_t kUploadSplit = 1 << 20;  // bytes of a frame from which its cameras go up one by one
+// 3.4 ms, row by row, against 14 us): one kernel for all of a stream's cameras, or
+// one per camera beside the next one's staging from kUploadSplit bytes a camera on,
+// where that outweighs the launches. A pushed frame with one and with several: 2 x
+// 320x240 59.5 and 61.7 us, 4 x 400x300 82.2 and 84.4, 2 x 480x360 68.8 and 68.9, 2 x
+// 640x480 76.9 and 75.8, 2 x 752x480 84.1 and 81.4, 4 x 640x480 110 and 106, 2 x
+// 1280x720 123 and 113, 4 x 1920x1200 465 and 367.
+constexpr size_t kUploadSplit = 1 << 18;
 static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* images, const int32_t* strides,
                               hipStream_t st) {
   const StreamInfo& si = h->streams[s];
@@ -1075,7 +1079,7 @@ static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* imag
   const uint8_t* from = h->hm_stage + at;
   uint8_t* dst = h->cams[si.first_cam].lvl[ps][0];
   const size_t pitch = (size_t)h->cams[si.first_cam].pitch[0], bytes = pitch * si.h;
-  const bool split = si.l0_stride * si.n_cams >= kUploadSplit;
+  const bool split = bytes >= kUploadSplit;
   for (int k = 0; k < si.n_cams; ++k) {
     const CamDesc& cd = h->cams[si.first_cam + k];
     uint8_t* to = stg + k * si.l0_stride;
