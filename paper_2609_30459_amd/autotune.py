@@ -6,9 +6,10 @@ Four choices are free and leave the records bit for bit the same:
     items from a shared queue;
   * keypoints per tracking wavefront: one (a lane per pattern point) or two
     (one per 32-lane half, two pattern points per lane);
-  * the pyramid/detector tile: 64x64 level-0 pixels per 1024-thread workgroup
-    or 32x32 per 256-thread workgroup (more, smaller workgroups, at the cost
-    of a larger share of recomputed apron);
+  * the pyramid/detector tile: 64x64 level-0 pixels per workgroup of 1024
+    threads (512 where the workgroups come in rounds) or 32x32 per 256-thread
+    workgroup (more, smaller workgroups, at the cost of a larger share of
+    recomputed apron);
   * the stereo mode: match every cell winner speculatively in the tracking
     launch (fewest dependent launches) or only the selected detections after
     selection (least work).
@@ -21,9 +22,9 @@ per item). Then, with that grid, the tile, the stereo mode and keypoints per
 wave are decided together in the production setting -- the benchmark's
 pipelined loop, three frames in flight, the next frames' pyramids running
 beside this frame's tracking, one process per candidate -- by its time per
-step: kernels alone on the chip and kernels sharing it favour different
-choices (two keypoints per wave are faster alone on batch16, and slower in
-the benchmark's loop). The winners go into a JSON cache keyed by the device's
+step: kernels alone on the chip and kernels sharing it can favour different
+choices (before the two-keypoint kernel read its pixels through LDS, two per
+wave were faster alone on batch16 and slower in the benchmark's loop). The winners go into a JSON cache keyed by the device's
 architecture and compute-unit count, which the benchmark reads.
 
     python -m paper_2609_30459_amd.autotune --workload batch16 --init const_vel

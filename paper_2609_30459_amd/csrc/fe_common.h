@@ -273,14 +273,14 @@ hipError_t launch_upload(const void* d_src, void* d_dst, size_t bytes, hipStream
 // Tracking work items [item_base, item_base + n_items) over the segments
 // d_segs[0..n_segs) (segment begins are global item indices). waves_per_cu = 0
 // launches one wave per item; > 0 launches a persistent grid of that many
-// waves per compute unit that pops items from FrameTable::queue_head[shape.queue].
+// waves per compute unit that takes items from FrameTable::queue_head[shape.queue].
 // Launch shape of the tracker: waves_per_cu = 0 gives one wave per work item
 // (kp_per_wave = 1) or per two (kp_per_wave = 2, one per 32-lane half), > 0 a
 // persistent grid of waves_per_cu * n_cus waves; block_waves waves (1, 2 or
 // kTrackWaves) per workgroup.
 struct TrackShape {
   int waves_per_cu, block_waves, n_cus;
-  int queue;  // the frame's work-queue counter the persistent grid pops (one per tracking launch)
+  int queue;  // the frame's work-queue counter the persistent grid takes from (one per tracking launch)
   int kp_per_wave;
 };
 hipError_t launch_track(const CamDesc* d_cams, FrameTable* d_frame, Counters* d_cnt, const TrackSeg* d_segs,

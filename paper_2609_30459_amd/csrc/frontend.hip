@@ -748,7 +748,7 @@ static LaunchSet all_set(const vio_frontend* h) {
 
 // Tracking launch over segments [seg_begin, seg_begin + n_segs) of the set's
 // table and items [item_begin, item_begin + n_items).
-// `queue`: the frame's work-queue counter this launch's persistent grid pops
+// `queue`: the frame's work-queue counter this launch's persistent grid takes from
 // (each tracking launch of a frame has its own).
 //
 // Keypoints per wave, unless the caller chose: by the items (launch_rules.h).

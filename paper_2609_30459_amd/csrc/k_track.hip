@@ -1828,7 +1828,7 @@ __global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu
                   lds.win, lds.plans);
 }
 
-// The persistent grid with two items per wave: each pop takes two items.
+// The persistent grid with two items per wave.
 template <int L>
 __global__ __launch_bounds__(kW* kTrackWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_track2_persistent(const CamDesc* __restrict__ cams,
                                                                       FrameTable* __restrict__ frame,
