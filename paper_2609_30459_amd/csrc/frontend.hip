@@ -1064,14 +1064,11 @@ static void fill_frame(vio_frontend* h, int s) {
 // on `st` into the current pyramid slot's level 0: rows at the level's pitch, so
 // that the upload is a linear copy (a two-dimensional one of 641-byte rows took
 // 3.4 ms, row by row, against 14 us): one kernel for all of a stream's cameras, or
-// one per camera beside the next one's staging from kUploadSplit bytes a camera on,
-// where that outweighs the launches. A pushed frame with one and with several: 2 x
-// 320x240 59.5 and 61.7 us, 4 x 400x300 82.2 and 84.4, 2 x 480x360 68.8 and 68.9, 2 x
-// 640x480 76.9 and 75.8, 2 x 752x480 84.1 and 81.4, 4 x 640x480 110 and 106, 2 x
-// 1280x720 123 and 113, 4 x 1920x1200 465 and 367.
-constexpr size_t kUploadSplit = 1 << 18;
+// one per camera beside the next one's staging where that outweighs the launches
+// (split_upload in launch_rules.h; among: other streams of the handle are staged
+// beside this one).
 static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* images, const int32_t* strides,
-                              hipStream_t st) {
+                              hipStream_t st, bool among) {
   const StreamInfo& si = h->streams[s];
   const int ps = (int)(si.frames % kPyrSlots);
   const size_t at = (h->sub % kInFlight) * h->stage_bytes + si.stage_off;
@@ -1079,7 +1076,7 @@ static int upload_host_images(vio_frontend* h, int s, const uint8_t* const* imag
   const uint8_t* from = h->hm_stage + at;
   uint8_t* dst = h->cams[si.first_cam].lvl[ps][0];
   const size_t pitch = (size_t)h->cams[si.first_cam].pitch[0], bytes = pitch * si.h;
-  const bool split = bytes >= kUploadSplit;
+  const bool split = split_upload(bytes, si.n_cams, among);
   for (int k = 0; k < si.n_cams; ++k) {
     const CamDesc& cd = h->cams[si.first_cam + k];
     uint8_t* to = stg + k * si.l0_stride;
@@ -1137,7 +1134,7 @@ int vio_frontend_push_stereo_frame(vio_frontend* h, int32_t s, int64_t t_ns, con
   rc = stage_motion(h, s, h->stream);
   if (rc != VIO_OK) return rc;
   const bool single = one_stream(h);
-  rc = upload_host_images(h, s, images, strides, single ? h->stream : h->pstream);
+  rc = upload_host_images(h, s, images, strides, single ? h->stream : h->pstream, false);
   if (rc == VIO_OK) rc = complete_all(h);
   if (rc != VIO_OK) return rc;
   rc = run_frame(h, s, h->stream, single);
@@ -1181,7 +1178,7 @@ int vio_frontend_stage_frame(vio_frontend* h, int32_t s, int64_t t_ns, const uin
   for (int k = 0; k < si.n_cams; ++k)
     if (!images[k] || strides[k] < si.w) return fail(h, VIO_EINVAL, "camera %d: null image or stride < width", k);
   fill_stream(h, s);
-  rc = upload_host_images(h, s, images, strides, h->pstream);
+  rc = upload_host_images(h, s, images, strides, h->pstream, h->streams.size() > 1);
   if (rc != VIO_OK) return rc;
   h->staged_uploads = true;
   rc = stage_motion(h, s, h->stream);

@@ -44,6 +44,12 @@ def test_pyramid_rules(rule):
     assert rule(body) == small + [512] * 4 + [256] * 2 + small + [384] * 4 + [256] * 2
 
 
+def test_upload_rule(rule):
+    got = rule("for (bool among : {false, true}) for (int c : {1, 2, 4}) for (int b : {262143, 262144, 393215, 393216, 786432})"
+               " printf(\"%d \", split_upload(b, c, among));")
+    assert got == 3 * [0, 1, 1, 1, 1] + [0, 0, 0, 0, 0] + [0, 0, 0, 0, 1] + [0, 0, 0, 1, 1]
+
+
 def kernels_of(step):
     """Names of the library's kernels that step() launches."""
     import torch
