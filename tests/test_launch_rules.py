@@ -64,6 +64,7 @@ def kernels_of(step):
 @pytest.mark.parametrize("n,extra,name", [
     (1, {}, "k_track<4, false>"), (4, {}, "k_track<4, false>"), (5, {}, "k_track2<4>"),
     (2, dict(levels=5), "k_track<5, false>"), (3, dict(levels=5), "k_track2<5>"), (3, dict(levels=6), "k_track2<6>"),
+    (3, dict(levels=5, track_kp_per_wave=1), "k_track<5, false>"),
     (5, dict(track_kp_per_wave=1), "k_track<4, false>"), (1, dict(track_kp_per_wave=2), "k_track2<4>"),
     (5, dict(track_waves_per_cu=4), "k_track_persistent<4, false>"),
     (1, dict(track_waves_per_cu=4, track_kp_per_wave=2), "k_track2_persistent<4>")])
